@@ -20,9 +20,7 @@
 // layout the weight operand of the PV MFMA needs: no shuffles between the two
 // products.
 //
-// float path (VALU): one thread per (query, head) walks its window with an
-// online softmax. It serves the float element type, where the band is too
-// narrow for float MFMA to pay.
+// float tensors: band_f32.hip.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -261,76 +259,6 @@ __global__ __launch_bounds__(kThreads) void band_fwd_bf16_kernel(DevArgs a) {
     }
     if (lse && g == 0)
       lse[(static_cast<size_t>(b) * H + h) * T + t] = qvalid ? (m + log2f(lsum)) * kLn2 : kNegInf;
-  }
-}
-
-template <int D>
-__global__ __launch_bounds__(kThreads) void band_fwd_f32_kernel(DevArgs a, int njobs) {
-  const size_t total = static_cast<size_t>(njobs) * a.B * a.T * a.H;
-  for (size_t gid = static_cast<size_t>(blockIdx.x) * kThreads + threadIdx.x; gid < total;
-       gid += static_cast<size_t>(gridDim.x) * kThreads) {
-    size_t r = gid;
-    const int h = static_cast<int>(r % a.H);
-    r /= a.H;
-    const int t = static_cast<int>(r % a.T);
-    r /= a.T;
-    const int b = static_cast<int>(r % a.B);
-    const bool second = (r / a.B) != 0;
-    const DevJob& job = second ? a.job1 : a.job0;
-    const int T = a.T, H = a.H;
-    const int len = clamp_len(a.lengths, b, T);
-    float* orow = static_cast<float*>(job.out) + row_index(b, t, h, T, H, D);
-    float* lrow = job.lse ? job.lse + (static_cast<size_t>(b) * H + h) * T + t : nullptr;
-    if (t >= len) {
-#pragma unroll
-      for (int i = 0; i < D; i += 4) *reinterpret_cast<float4*>(orow + i) = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (lrow) *lrow = kNegInf;
-      continue;
-    }
-    float qv[D], acc[D];
-    const float* qrow = static_cast<const float*>(job.q) + row_index(b, t, h, T, H, D);
-#pragma unroll
-    for (int i = 0; i < D; i += 4) {
-      const float4 x = *reinterpret_cast<const float4*>(qrow + i);
-      qv[i] = x.x; qv[i + 1] = x.y; qv[i + 2] = x.z; qv[i + 3] = x.w;
-      acc[i] = acc[i + 1] = acc[i + 2] = acc[i + 3] = 0.f;
-    }
-    float m = kNegInf, l = 0.f;
-    for (int si = 0; si < job.nseg; ++si) {
-      const DevSeg& sg = si ? job.seg1 : job.seg0;
-      const int lo = max(0, t + sg.lo_off), hi = min(len - 1, t + sg.hi_off);
-      const float* kp = static_cast<const float*>(sg.k);
-      const float* vp = static_cast<const float*>(sg.v);
-      for (int key = lo; key <= hi; ++key) {
-        const float* krow = kp + row_index(b, key, h, T, H, D);
-        float s = 0.f;
-#pragma unroll
-        for (int i = 0; i < D; i += 4) {
-          const float4 x = *reinterpret_cast<const float4*>(krow + i);
-          s += qv[i] * x.x + qv[i + 1] * x.y + qv[i + 2] * x.z + qv[i + 3] * x.w;
-        }
-        s *= a.scale_log2;
-        const float mnew = fmaxf(m, s);
-        const float alpha = fast_exp2(m - mnew);
-        const float pw = fast_exp2(s - mnew);
-        l = l * alpha + pw;
-        m = mnew;
-        const float* vrow = vp + row_index(b, key, h, T, H, D);
-#pragma unroll
-        for (int i = 0; i < D; i += 4) {
-          const float4 x = *reinterpret_cast<const float4*>(vrow + i);
-          acc[i] = acc[i] * alpha + pw * x.x;
-          acc[i + 1] = acc[i + 1] * alpha + pw * x.y;
-          acc[i + 2] = acc[i + 2] * alpha + pw * x.z;
-          acc[i + 3] = acc[i + 3] * alpha + pw * x.w;
-        }
-      }
-    }
-    const float inv = 1.f / l;
-#pragma unroll
-    for (int i = 0; i < D; i += 4)
-      *reinterpret_cast<float4*>(orow + i) = make_float4(acc[i] * inv, acc[i + 1] * inv, acc[i + 2] * inv, acc[i + 3] * inv);
-    if (lrow) *lrow = (m + log2f(l)) * kLn2;
   }
 }
 
@@ -1206,8 +1134,9 @@ bool launch_tile(const BandForwardArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_band_forward(const BandForwardArgs& a, ElemType et, hipStream_t stream) {
-  if (et == kBF16 && (a.d == 64 ? launch_tile<64>(a, stream) : launch_tile<32>(a, stream)))
-    return hipGetLastError();
+  if (et == kF32) return launch_band_forward_f32(a, stream);
+  if (a.d == 64 ? launch_tile<64>(a, stream) : launch_tile<32>(a, stream)) return hipGetLastError();
+  // windows too wide for the tile kernel's bands: chunked sweep
   DevArgs d;
   d.job0 = to_dev(a.job[0]);
   d.job1 = a.njobs > 1 ? to_dev(a.job[1]) : d.job0;
@@ -1217,24 +1146,12 @@ hipError_t launch_band_forward(const BandForwardArgs& a, ElemType et, hipStream_
   d.H = a.H;
   d.lengths = a.lengths;
   d.scale_log2 = kLog2e / sqrtf(static_cast<float>(a.d));
-  if (et == kBF16) {
-    // windows too wide for the tile kernel's bands: chunked sweep
-    d.ntiles = (a.T + kTq - 1) / kTq;
-    const int grid = xcd_slice_grid(a.B * a.H, a.njobs * d.ntiles);
-    if (a.d == 64)
-      hipLaunchKernelGGL(band_fwd_bf16_kernel<64>, dim3(grid), dim3(kThreads), 0, stream, d);
-    else
-      hipLaunchKernelGGL(band_fwd_bf16_kernel<32>, dim3(grid), dim3(kThreads), 0, stream, d);
-  } else {
-    d.ntiles = 0;
-    const size_t total = static_cast<size_t>(a.njobs) * a.B * a.T * a.H;
-    const size_t blocks = (total + kThreads - 1) / kThreads;
-    const int grid = static_cast<int>(blocks < 65536 ? blocks : 65536);
-    if (a.d == 64)
-      hipLaunchKernelGGL(band_fwd_f32_kernel<64>, dim3(grid), dim3(kThreads), 0, stream, d, a.njobs);
-    else
-      hipLaunchKernelGGL(band_fwd_f32_kernel<32>, dim3(grid), dim3(kThreads), 0, stream, d, a.njobs);
-  }
+  d.ntiles = (a.T + kTq - 1) / kTq;
+  const int grid = xcd_slice_grid(a.B * a.H, a.njobs * d.ntiles);
+  if (a.d == 64)
+    hipLaunchKernelGGL(band_fwd_bf16_kernel<64>, dim3(grid), dim3(kThreads), 0, stream, d);
+  else
+    hipLaunchKernelGGL(band_fwd_bf16_kernel<32>, dim3(grid), dim3(kThreads), 0, stream, d);
   return hipGetLastError();
 }
 

@@ -41,6 +41,8 @@ struct BandForwardArgs {
 };
 
 hipError_t launch_band_forward(const BandForwardArgs& a, ElemType et, hipStream_t stream);
+// float32 tensors, any window (band_f32.hip).
+hipError_t launch_band_forward_f32(const BandForwardArgs& a, hipStream_t stream);
 
 // The paper's LLSA forward with La + 1 channels: q, k, v, out are
 // [La+1][B][T][H][d], lse [La+1][B][H][T] (required).

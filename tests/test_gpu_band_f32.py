@@ -1,0 +1,85 @@
+"""The float32-arithmetic matrix-core kernels (16 rows per wave, blocks of 16
+frames from the window's first row) at the sizes where they can go wrong:
+windows around one and two blocks, last rows of a wave and a tile, more
+sequences than compute units, against the fp64 oracle; and infinities and NaN,
+which must reach exactly the rows whose window holds them.
+
+Tolerance: parity.TOL["f32"] = 1e-5 of the slice's maximum. A result is a sum
+of at most W products of float32 values; rounding each score (a sum of d
+products of N(0, 1) / d^(1/2) terms) moves a weight by about
+sqrt(d) 2^-24 = 5e-7 of itself, and the sums add sqrt(W) 2^-24 <= 1.3e-6."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2302_13451_amd import binding as bd
+from paper_2302_13451_amd.inputs import llsa_inputs, sa_inputs
+from parity import assert_lse_close, assert_slices_close, f64, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # B, T, H, d, Lb, La, lengths: one frame of context, windows of a block
+    # less one, one block and one more, of two blocks and one more
+    (2, 65, 1, 64, 1, 0, (16, 65)),
+    (2, 64, 2, 32, 0, 1, (1, 64)),
+    (1, 81, 1, 64, 10, 4, "full"),
+    (2, 79, 1, 32, 8, 7, (15, 79)),
+    (2, 80, 1, 64, 16, 0, (17, 80)),
+    (1, 130, 2, 64, 20, 12, "full"),
+    # window longer than the sequence, wider than any staged kernel takes
+    (2, 50, 1, 64, 481, 8, (3, 50)),
+    (1, 403, 1, 64, 250, 30, "full"),
+    # more (sequence, head) slices than compute units, not a multiple of 8
+    (91, 33, 3, 32, 12, 3, (0, 33)),
+]
+
+
+@pytest.mark.parametrize("B,T,H,d,Lb,La,lengths", SHAPES)
+def test_sa_forward_float32(oracle_mod, B, T, H, d, Lb, La, lengths):
+    print("f32 forward B=%d T=%d H=%d d=%d Lb=%d La=%d" % (B, T, H, d, Lb, La), flush=True)
+    x = sa_inputs(B, T, H, d, 61, dtype="f32", scale="unit", lengths=lengths, pad_value=float("nan"))
+    q, k, v = (to_gpu(x[n], "f32") for n in ("q", "k", "v"))
+    out, lse = bd.sa_forward(q, k, v, Lb, La, x["lengths"].cuda())
+    L = x["lengths"].numpy()
+    yr, lr = oracle_mod.sa_forward(*(np.nan_to_num(f64(x[n])) for n in ("q", "k", "v")), Lb, La, L)
+    assert_slices_close(f64(out), yr, "f32", L, "out")
+    assert_lse_close(lse.cpu().numpy(), lr, "f32")
+
+
+@pytest.mark.parametrize("where", ["k", "v"])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_sa_forward_float32_nonfinite_frames_stay_in_their_windows(where, bad):
+    B, T, H, d, Lb, La, at = 1, 90, 2, 64, 7, 3, 41
+    x = sa_inputs(B, T, H, d, 62, dtype="f32", scale="unit")
+    g = {n: to_gpu(x[n], "f32") for n in ("q", "k", "v")}
+    clean, _ = bd.sa_forward(g["q"], g["k"], g["v"], Lb, La)
+    g[where][0, at, 0, 5] = bad
+    out, _ = bd.sa_forward(g["q"], g["k"], g["v"], Lb, La)
+    out, clean = out.cpu(), clean.cpu()
+    t = torch.arange(T)
+    sees = (t - Lb <= at) & (at <= t + La)
+    assert torch.equal(out[0, :, 1], clean[0, :, 1])
+    hit = sees
+    if where == "k" and bad == float("inf"):  # a score of -inf is a weight of zero
+        hit = sees & (x["q"][0, :, 0, 5] > 0)
+    assert hit.any() and not torch.isfinite(out[0, hit, 0]).all(dim=1).any()
+    # rows of the same wave are computed one by one: equal up to rounding
+    torch.testing.assert_close(out[0, ~sees, 0], clean[0, ~sees, 0], rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("La", [0, 4])
+@pytest.mark.parametrize("B,T,H,d,Lb", [(2, 65, 1, 64, 14), (1, 129, 2, 32, 40), (2, 47, 1, 64, 200)])
+def test_llsa_forward_float32(oracle_mod, B, T, H, d, Lb, La):
+    print("f32 llsa forward B=%d T=%d H=%d d=%d Lb=%d La=%d" % (B, T, H, d, Lb, La), flush=True)
+    x = llsa_inputs(B, T, H, d, 63, dtype="f32", scale="unit", lengths=(T // 2, T),
+                    pad_value=float("nan"))
+    q, k, v = (to_gpu(x[n], "f32") for n in ("q", "k", "v"))
+    out, lse = bd.llsa_forward(q, k, v, Lb, La, x["lengths"].cuda())
+    L = x["lengths"].numpy()
+    yr, lr = oracle_mod.llsa_two_branch(*(np.nan_to_num(f64(x[n])) for n in ("q", "k", "v")), Lb,
+                                        La, L)
+    assert_slices_close(f64(out), yr, "f32", L, "out")
+    assert_lse_close(lse.cpu().numpy(), lr, "f32")
+
