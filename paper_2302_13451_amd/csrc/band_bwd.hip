@@ -26,8 +26,7 @@
 // MFMA's N operand, so every lane owns one key (key role) or one query (query
 // role) and the softmax statistics it needs are per lane.
 //
-// float path (VALU): one thread per query row computes dq, one thread per key
-// row computes dk and dv.
+// float tensors, and the LLSA windows no kernel here takes: band_f32.hip.
 #include <type_traits>
 
 #include "device_common.h"
@@ -37,140 +36,6 @@ namespace sa {
 namespace {
 
 constexpr int kThreads = 256;
-
-template <typename E>
-__device__ __forceinline__ void load4(const E* p, float* x);
-template <>
-__device__ __forceinline__ void load4<float>(const float* p, float* x) {
-  const float4 v = *reinterpret_cast<const float4*>(p);
-  x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-}
-
-template <typename E>
-__device__ __forceinline__ void store4(E* p, const float* x);
-template <>
-__device__ __forceinline__ void store4<float>(float* p, const float* x) {
-  *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
-}
-
-template <typename E, int D>
-__device__ __forceinline__ float dot_row(const float* x, const E* row) {
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < D; i += 4) {
-    float y[4];
-    load4<E>(row + i, y);
-    s += x[i] * y[0] + x[i + 1] * y[1] + x[i + 2] * y[2] + x[i + 3] * y[3];
-  }
-  return s;
-}
-
-template <typename E, int D>
-__device__ __forceinline__ float dot_rows(const E* r0, const E* r1) {
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < D; i += 4) {
-    float x[4], y[4];
-    load4<E>(r0 + i, x);
-    load4<E>(r1 + i, y);
-    s += x[0] * y[0] + x[1] * y[1] + x[2] * y[2] + x[3] * y[3];
-  }
-  return s;
-}
-
-template <typename E, int D>
-__global__ __launch_bounds__(kThreads) void sa_bwd_valu_kernel(SaBackwardArgs a) {
-  const int T = a.T, H = a.H;
-  const size_t rows = static_cast<size_t>(a.B) * T * H;
-  const float scale = 1.f / sqrtf(static_cast<float>(D));
-  const float scale_log2 = kLog2e * scale;
-  const E* q = static_cast<const E*>(a.q);
-  const E* k = static_cast<const E*>(a.k);
-  const E* v = static_cast<const E*>(a.v);
-  const E* o = static_cast<const E*>(a.out);
-  const E* dout = static_cast<const E*>(a.dout);
-  for (size_t gid = static_cast<size_t>(blockIdx.x) * kThreads + threadIdx.x; gid < 2 * rows;
-       gid += static_cast<size_t>(gridDim.x) * kThreads) {
-    const bool key_role = gid >= rows;
-    size_t r = key_role ? gid - rows : gid;
-    const int h = static_cast<int>(r % H);
-    r /= H;
-    const int t = static_cast<int>(r % T);
-    const int b = static_cast<int>(r / T);
-    const int len = clamp_len(a.lengths, b, T);
-    const size_t ro = row_index(b, t, h, T, H, D);
-    float acc0[D], acc1[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) acc0[i] = acc1[i] = 0.f;
-    if (t < len && !key_role) {
-      // dq of query t
-      float qv[D], dov[D];
-#pragma unroll
-      for (int i = 0; i < D; i += 4) {
-        load4<E>(q + ro + i, qv + i);
-        load4<E>(dout + ro + i, dov + i);
-      }
-      const float Dt = dot_row<E, D>(dov, o + ro);
-      const float lse2 = a.lse[(static_cast<size_t>(b) * H + h) * T + t] * kLog2e;
-      const int lo = max(0, t - a.Lb), hi = min(len - 1, t + a.La);
-      for (int key = lo; key <= hi; ++key) {
-        const size_t kr = row_index(b, key, h, T, H, D);
-        const float p = fast_exp2(dot_row<E, D>(qv, k + kr) * scale_log2 - lse2);
-        const float ds = p * (dot_row<E, D>(dov, v + kr) - Dt);
-#pragma unroll
-        for (int i = 0; i < D; i += 4) {
-          float y[4];
-          load4<E>(k + kr + i, y);
-          acc0[i] += ds * y[0]; acc0[i + 1] += ds * y[1];
-          acc0[i + 2] += ds * y[2]; acc0[i + 3] += ds * y[3];
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < D; ++i) acc0[i] *= scale;
-    } else if (t < len) {
-      // dk (acc0) and dv (acc1) of key t
-      float kv[D], vv[D];
-#pragma unroll
-      for (int i = 0; i < D; i += 4) {
-        load4<E>(k + ro + i, kv + i);
-        load4<E>(v + ro + i, vv + i);
-      }
-      const int lo = max(0, t - a.La), hi = min(len - 1, t + a.Lb);
-      for (int n = lo; n <= hi; ++n) {
-        const size_t nr = row_index(b, n, h, T, H, D);
-        const float Dn = dot_rows<E, D>(dout + nr, o + nr);
-        const float lse2 = a.lse[(static_cast<size_t>(b) * H + h) * T + n] * kLog2e;
-        const float p = fast_exp2(dot_row<E, D>(kv, q + nr) * scale_log2 - lse2);
-        const float ds = p * (dot_row<E, D>(vv, dout + nr) - Dn);
-#pragma unroll
-        for (int i = 0; i < D; i += 4) {
-          float x[4], y[4];
-          load4<E>(q + nr + i, x);
-          load4<E>(dout + nr + i, y);
-          acc0[i] += ds * x[0]; acc0[i + 1] += ds * x[1];
-          acc0[i + 2] += ds * x[2]; acc0[i + 3] += ds * x[3];
-          acc1[i] += p * y[0]; acc1[i + 1] += p * y[1];
-          acc1[i + 2] += p * y[2]; acc1[i + 3] += p * y[3];
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < D; ++i) acc0[i] *= scale;
-    }
-    if (!key_role) {
-      E* dq = static_cast<E*>(a.dq) + ro;
-#pragma unroll
-      for (int i = 0; i < D; i += 4) store4<E>(dq + i, acc0 + i);
-    } else {
-      E* dk = static_cast<E*>(a.dk) + ro;
-      E* dv = static_cast<E*>(a.dv) + ro;
-#pragma unroll
-      for (int i = 0; i < D; i += 4) {
-        store4<E>(dk + i, acc0 + i);
-        store4<E>(dv + i, acc1 + i);
-      }
-    }
-  }
-}
 
 constexpr int kC = 64;    // frames per tile
 constexpr int kSub = 32;  // frames per sub-block: the contraction length of one MFMA
@@ -1177,23 +1042,11 @@ hipError_t launch_mfma(const SaBackwardArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <typename E>
-hipError_t launch_valu(const SaBackwardArgs& a, hipStream_t stream) {
-  const size_t total = 2 * static_cast<size_t>(a.B) * a.T * a.H;
-  const size_t blocks = (total + kThreads - 1) / kThreads;
-  const int grid = static_cast<int>(blocks < 65536 ? blocks : 65536);
-  if (a.d == 64)
-    hipLaunchKernelGGL((sa_bwd_valu_kernel<E, 64>), dim3(grid), dim3(kThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL((sa_bwd_valu_kernel<E, 32>), dim3(grid), dim3(kThreads), 0, stream, a);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t launch_sa_backward(const SaBackwardArgs& a, ElemType et, hipStream_t stream) {
   if (et == kBF16) return launch_mfma(a, stream);
-  return launch_valu<float>(a, stream);
+  return launch_sa_backward_f32(a, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -2144,9 +1997,9 @@ bool llsa_backward_fits(int d, int Lb, int La) {
 hipError_t launch_llsa_backward(const LlsaBackwardArgs& x, ElemType et, hipStream_t stream) {
   LlsaBwdDev a{};
   // bfloat16 windows whose bands fit the persistent kernel's rings (up to 64
-  // sequences, d = 64) or one staged segment run on MFMA, the rest on the
-  // vector ALUs (the segments and origins are set whether or not the staged
-  // segment fits)
+  // sequences, d = 64) or one staged segment run on bfloat16 MFMA, the rest in
+  // float32 arithmetic (the segments and origins are set whether or not the
+  // staged segment fits)
   const bool staged = llsa_bwd_geometry(x.d, x.Lb, x.La, a);
   const bool ring = et == kBF16 && x.d == 64 && x.B <= kPersistMaxB && llsa_bwd_ring_geometry(a);
   if (!ring && (et != kBF16 || !staged)) return launch_llsa_backward_general(x, et, stream);

@@ -1,7 +1,10 @@
 // Band attention in float32 arithmetic on the matrix cores
-// (v_mfma_f32_16x16x4_f32), any window: the float32 SA and LLSA forward.
+// (v_mfma_f32_16x16x4_f32), any window: the float32 SA and LLSA forward, and
+// the backward of SA, two-branch LLSA and the paper's LLSA for float32 tensors
+// and for the bfloat16 windows that no staged kernel takes.
 //
-// One wave owns 16 rows (queries), one row per lane column of the MFMA's N dimension, and sweeps the rows its window
+// One wave owns 16 rows (queries, or keys in the backward's key role), one row
+// per lane column of the MFMA's N dimension, and sweeps the rows its window
 // reads in blocks of 16 that start exactly at the window's first row. Operands
 // go from memory straight into the operand registers, in two patterns:
 //   * rows (products that contract over the head dim): lane (g, col) loads
@@ -25,6 +28,7 @@
 // that an infinity or NaN reaches exactly the rows whose window holds it.
 #include "device_common.h"
 #include "kernels.h"
+#include "sa.h"
 
 namespace sa {
 namespace {
@@ -33,6 +37,7 @@ constexpr int kThreads = 256;
 constexpr int kRowsPerWave = 16;
 constexpr int kTileRows = 64;          // rows of a workgroup (four waves)
 constexpr int kMaxGrid = 1 << 20;      // workgroups per launch; more items loop
+constexpr int kMaxOut = SA_LLSA_PAPER_MAX_LA + 1;  // outputs and branches of one backward call
 
 __device__ __forceinline__ float lo_bf(uint32_t x) { return __uint_as_float(x << 16); }
 __device__ __forceinline__ float hi_bf(uint32_t x) { return __uint_as_float(x & 0xffff0000u); }
@@ -335,6 +340,295 @@ __global__ __launch_bounds__(kThreads) void band_fwd_f32_kernel(FwdDev a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Backward, in the general channel form (Eq. 7-13 per output row; the paper's
+// Eq. 16 prints only the value part of the LLSA gradient). Channels
+// c = 0 .. La, each held by a branch (tensor); output o computes channel c_o
+// with the query of branch qb_o. Query t of output o reads the frames tau in
+// [t + c_o - La - Lb, t + c_o] (clipped to the sequence), frame tau from the
+// branch whose interval [elo, ehi] holds e = t + c_o - tau, so that output o
+// reads from branch i the band t + c_o - ehi_i .. t + c_o - elo_i. SA is one
+// output and one branch. With P the attention weights of a row,
+// dP_tau = dout . v_tau, D = dout . out and dS = P (dP - D):
+//   dq[qb_o]_t  += (1/sqrt d) sum_tau dS_(t,tau) k[i]_tau
+//   dk[i]_tau   += (1/sqrt d) sum over the (o, t) that read tau from i of dS_(t,tau) q[qb_o]_t
+//   dv[i]_tau   += sum over the same (o, t) of P_(t,tau) dout[o]_t
+// A query role per (output, 16 frames) gathers dq over its bands, a key role
+// per (branch, 16 frames) gathers dk and dv over the outputs' queries that
+// read it. Each output's query branch is distinct, so every gradient row has
+// one writer: no atomics, no workspace, deterministic.
+struct BwdDev {
+  const void *q, *k, *v, *out, *dout;
+  const float* lse;
+  void *dq, *dk, *dv;
+  int B, T, H, ntiles, items;
+  int nout, nbranch;
+  int c[kMaxOut];    // channel of output o
+  int qb[kMaxOut];   // branch of output o's query
+  int elo[kMaxOut];  // e-interval of branch i (empty: elo > ehi)
+  int ehi[kMaxOut];
+  size_t bstride;  // elements of one branch (or output) tensor
+  size_t lstride;  // floats of one output's lse
+  const int32_t* lengths;
+  float scale, scale_log2;
+};
+
+template <typename E, int D>
+__device__ __forceinline__ float feat_dot(const float* x, const E* row, int col) {
+  constexpr int F = D / 16;
+  float y[F], s = 0.f;
+  feat_frag<D>(row, col, y);
+#pragma unroll
+  for (int f = 0; f < F; ++f) s += x[f] * y[f];
+  return group_sum<16>(s);
+}
+
+// The wave's gradient rows one by one (as fwd_rows_slow): the query role of
+// output x, or the key role of branch x.
+template <typename E, int D>
+__device__ void bwd_rows_slow(const BwdDev& a, bool key_role, int x, int b, int h, int r0, int len, int lane) {
+  constexpr int F = D / 16;
+  const int col = lane & 15, g = lane >> 4;
+  const int T = a.T, fs = a.H * D;
+  const size_t slice = row_index(b, 0, h, T, a.H, D);
+  const E *q = static_cast<const E*>(a.q) + slice, *k = static_cast<const E*>(a.k) + slice;
+  const E *v = static_cast<const E*>(a.v) + slice, *o = static_cast<const E*>(a.out) + slice;
+  const E* dout = static_cast<const E*>(a.dout) + slice;
+  const float* lse = a.lse + (static_cast<size_t>(b) * a.H + h) * T;
+  for (int it = 0; it < 4; ++it) {
+    const int t = r0 + 4 * it + g;
+    if (t >= len) continue;
+    float acc0[F], acc1[F], x0[F], x1[F], y[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f) acc0[f] = acc1[f] = 0.f;
+    if (!key_role) {
+      const size_t qo = a.qb[x] * a.bstride, oo = x * a.bstride;
+      feat_frag<D>(q + qo + t * fs, col, x0);
+      feat_frag<D>(dout + oo + t * fs, col, x1);
+      const float dn = feat_dot<E, D>(x1, o + oo + t * fs, col);
+      const float lse2 = lse[x * a.lstride + t] * kLog2e;
+      for (int i = 0; i < a.nbranch; ++i) {
+        const size_t ko = i * a.bstride;
+        const int lo = max(0, t + a.c[x] - a.ehi[i]), hi = min(len - 1, t + a.c[x] - a.elo[i]);
+        for (int tau = lo; tau <= hi; ++tau) {
+          const float p = fast_exp2(feat_dot<E, D>(x0, k + ko + tau * fs, col) * a.scale_log2 - lse2);
+          const float ds = p * (feat_dot<E, D>(x1, v + ko + tau * fs, col) - dn);
+          feat_frag<D>(k + ko + tau * fs, col, y);
+#pragma unroll
+          for (int f = 0; f < F; ++f) acc0[f] += ds * y[f];
+        }
+      }
+#pragma unroll
+      for (int f = 0; f < F; ++f) acc0[f] *= a.scale;
+      store_feat(static_cast<E*>(a.dq) + slice + qo + t * fs + F * col, acc0, F);
+      continue;
+    }
+    const size_t ko = x * a.bstride;
+    feat_frag<D>(k + ko + t * fs, col, x0);
+    feat_frag<D>(v + ko + t * fs, col, x1);
+    for (int oi = 0; oi < a.nout; ++oi) {
+      const size_t qo = a.qb[oi] * a.bstride, oo = oi * a.bstride;
+      const int lo = max(0, t - a.c[oi] + a.elo[x]), hi = min(len - 1, t - a.c[oi] + a.ehi[x]);
+      for (int n = lo; n <= hi; ++n) {
+        float dr[F];
+        feat_frag<D>(dout + oo + n * fs, col, dr);
+        feat_frag<D>(q + qo + n * fs, col, y);
+        const float dn = feat_dot<E, D>(dr, o + oo + n * fs, col);
+        float s = 0.f, dp = 0.f;
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+          s += x0[f] * y[f];
+          dp += x1[f] * dr[f];
+        }
+        const float p = fast_exp2(group_sum<16>(s) * a.scale_log2 - lse[oi * a.lstride + n] * kLog2e);
+        const float ds = p * (group_sum<16>(dp) - dn);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+          acc0[f] += ds * y[f];
+          acc1[f] += p * dr[f];
+        }
+      }
+    }
+#pragma unroll
+    for (int f = 0; f < F; ++f) acc0[f] *= a.scale;
+    store_feat(static_cast<E*>(a.dk) + slice + ko + t * fs + F * col, acc0, F);
+    store_feat(static_cast<E*>(a.dv) + slice + ko + t * fs + F * col, acc1, F);
+  }
+}
+
+template <typename E, int D>
+__global__ __launch_bounds__(kThreads) void band_bwd_f32_kernel(BwdDev a) {
+  constexpr int N = D / 4, F = D / 16;
+  const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int T = a.T, H = a.H, fs = H * D;
+  const int nroles = a.nbranch + a.nout;
+  const float c2 = a.scale_log2;
+  for (int bid = blockIdx.x; bid < a.items; bid += gridDim.x) {
+    // items of a slice: the key roles and query roles of tile 0, of tile 1, ...
+    int bh, item;
+    if (!xcd_slice_item(bid, a.B * H, nroles * a.ntiles, bh, item)) continue;
+    const int tile = item / nroles, role = item - tile * nroles;
+    const bool key_role = role < a.nbranch;
+    const int x = key_role ? role : role - a.nbranch;  // branch or output
+    const int b = bh / H, h = bh - b * H;
+    const int len = clamp_len_uniform(a.lengths, b, T);
+    const int r0 = tile * kTileRows + kRowsPerWave * w;
+    if (r0 >= T) continue;
+    const size_t slice = row_index(b, 0, h, T, H, D);
+    const int r1 = min(r0 + kRowsPerWave, T);
+    E* const d0 = static_cast<E*>(key_role ? a.dk : a.dq) + slice + (key_role ? x : a.qb[x]) * a.bstride;
+    E* const d1 = static_cast<E*>(a.dv) + slice + x * a.bstride;  // key role only
+    if (r0 >= len) {
+      zero_rows<D>(d0, fs, r0, r1, lane);
+      if (key_role) zero_rows<D>(d1, fs, r0, r1, lane);
+      continue;
+    }
+    const E *q = static_cast<const E*>(a.q) + slice, *k = static_cast<const E*>(a.k) + slice;
+    const E *v = static_cast<const E*>(a.v) + slice, *o = static_cast<const E*>(a.out) + slice;
+    const E* dout = static_cast<const E*>(a.dout) + slice;
+    const float* lse = a.lse + (static_cast<size_t>(b) * H + h) * T;
+    const int me = r0 + col, last = len - 1;
+    const bool valid = me < len;
+    const int wmax = min(r0 + kRowsPerWave - 1, last);
+    const int own = min(me, last) * fs;
+    f32x4 acc0[F], acc1[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f) acc0[f] = acc1[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (key_role) {
+      float kf[N], vf[N];
+      row_frag<D>(k + x * a.bstride + own, g, kf);
+      row_frag<D>(v + x * a.bstride + own, g, vf);
+      for (int oi = 0; oi < a.nout; ++oi) {
+        const int lo = a.c[oi] - a.ehi[x], hi = a.c[oi] - a.elo[x];
+        const int wlo = max(0, r0 - hi), whi = min(last, wmax - lo);
+        if (lo > hi || wlo > whi) continue;
+        const Span see(valid, max(0, me - hi), min(last, me - lo));  // queries that see this lane's key
+        const E *qp = q + a.qb[oi] * a.bstride, *dp = dout + oi * a.bstride, *op = o + oi * a.bstride;
+        const float* lp = lse + oi * a.lstride;
+        for (int qb = wlo; qb <= whi; qb += 16) {
+          float qr[N], dr[N], orow[N], qt[4][F], dt[4][F], l2[4];
+          const int rr = min(qb + col, last) * fs;
+          row_frag<D>(qp + rr, g, qr);
+          row_frag<D>(dp + rr, g, dr);
+          row_frag<D>(op + rr, g, orow);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int n = min(qb + 4 * g + i, last);
+            l2[i] = lp[n];
+            feat_frag<D>(dp + n * fs, col, dt[i]);
+            feat_frag<D>(qp + n * fs, col, qt[i]);
+          }
+          const f32x4 s = row_product<N>(qr, kf), dpv = row_product<N>(dr, vf);
+          // D of query col in every lane of the column, then of the queries
+          // 4g + i whose scores this lane holds
+          float dn = 0.f;
+#pragma unroll
+          for (int n = 0; n < N; ++n) dn += dr[n] * orow[n];
+          dn = sum_over_column(dn);
+          float p[4], ds[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float di =
+                __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (4 * g + i), __float_as_int(dn)));
+            const bool in = see.has(qb + 4 * g + i);
+            const float pw = fast_exp2(__builtin_fmaf(s[i], c2, -l2[i] * kLog2e));
+            p[i] = in ? pw : 0.f;
+            ds[i] = in ? pw * (dpv[i] - di) : 0.f;
+          }
+          col_product<F>(dt, p, acc1);
+          col_product<F>(qt, ds, acc0);
+        }
+      }
+    } else {
+      const size_t oo = x * a.bstride;
+      float qf[N], df[N], dn = 0.f;
+      row_frag<D>(q + a.qb[x] * a.bstride + own, g, qf);
+      row_frag<D>(dout + oo + own, g, df);
+      {
+        float of[N];
+        row_frag<D>(o + oo + own, g, of);
+#pragma unroll
+        for (int n = 0; n < N; ++n) dn += df[n] * of[n];
+        dn = sum_over_column(dn);
+      }
+      const float l2 = lse[x * a.lstride + min(me, last)] * kLog2e;
+      for (int i = 0; i < a.nbranch; ++i) {
+        const int lo = a.c[x] - a.ehi[i], hi = a.c[x] - a.elo[i];
+        const int wlo = max(0, r0 + lo), whi = min(last, wmax + hi);
+        if (lo > hi || wlo > whi) continue;
+        const Span win(valid, max(0, me + lo), min(last, me + hi));
+        const E *kp = k + i * a.bstride, *vp = v + i * a.bstride;
+        for (int kb = wlo; kb <= whi; kb += 16) {
+          float kr[N], vr[N], kt[4][F];
+          const int rr = min(kb + col, last) * fs;
+          row_frag<D>(kp + rr, g, kr);
+          row_frag<D>(vp + rr, g, vr);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) feat_frag<D>(kp + min(kb + 4 * g + u, last) * fs, col, kt[u]);
+          const f32x4 s = row_product<N>(kr, qf), dpv = row_product<N>(vr, df);
+          float ds[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float pw = fast_exp2(__builtin_fmaf(s[u], c2, -l2));
+            ds[u] = win.has(kb + 4 * g + u) ? pw * (dpv[u] - dn) : 0.f;
+          }
+          col_product<F>(kt, ds, acc0);
+        }
+      }
+    }
+    if (__any(valid && !(all_finite<F>(acc0) && all_finite<F>(acc1)))) {
+      bwd_rows_slow<E, D>(a, key_role, x, b, h, r0, len, lane);
+      if (len < r1) {
+        zero_rows<D>(d0, fs, len, r1, lane);
+        if (key_role) zero_rows<D>(d1, fs, len, r1, lane);
+      }
+      continue;
+    }
+    store_own_row<D>(d0 + static_cast<ptrdiff_t>(me) * fs, acc0, a.scale, valid, me < T, g);
+    if (key_role) store_own_row<D>(d1 + static_cast<ptrdiff_t>(me) * fs, acc1, 1.f, valid, me < T, g);
+  }
+}
+
+template <typename E>
+hipError_t launch_bwd(BwdDev& a, int d, hipStream_t stream) {
+  a.ntiles = (a.T + kTileRows - 1) / kTileRows;
+  a.items = xcd_slice_grid(a.B * a.H, (a.nbranch + a.nout) * a.ntiles);
+  a.scale = 1.f / sqrtf(static_cast<float>(d));
+  a.scale_log2 = kLog2e * a.scale;
+  const dim3 grid(a.items < kMaxGrid ? a.items : kMaxGrid), block(kThreads);
+  if (d == 64)
+    hipLaunchKernelGGL((band_bwd_f32_kernel<E, 64>), grid, block, 0, stream, a);
+  else
+    hipLaunchKernelGGL((band_bwd_f32_kernel<E, 32>), grid, block, 0, stream, a);
+  return hipGetLastError();
+}
+
+template <typename Args>
+BwdDev common(const Args& x) {
+  BwdDev a{};
+  a.q = x.q;
+  a.k = x.k;
+  a.v = x.v;
+  a.out = x.out;
+  a.dout = x.dout;
+  a.lse = x.lse;
+  a.dq = x.dq;
+  a.dk = x.dk;
+  a.dv = x.dv;
+  a.B = x.B;
+  a.T = x.T;
+  a.H = x.H;
+  a.lengths = x.lengths;
+  a.bstride = static_cast<size_t>(x.B) * x.T * x.H * x.d;
+  a.lstride = static_cast<size_t>(x.B) * x.H * x.T;
+  return a;
+}
+
+hipError_t launch_bwd_typed(BwdDev& a, int d, ElemType et, hipStream_t stream) {
+  return et == kBF16 ? launch_bwd<uint16_t>(a, d, stream) : launch_bwd<float>(a, d, stream);
+}
+
 }  // namespace
 
 hipError_t launch_band_forward_f32(const BandForwardArgs& x, hipStream_t stream) {
@@ -355,6 +649,42 @@ hipError_t launch_band_forward_f32(const BandForwardArgs& x, hipStream_t stream)
   else
     hipLaunchKernelGGL(band_fwd_f32_kernel<32>, grid, block, 0, stream, a);
   return hipGetLastError();
+}
+
+hipError_t launch_sa_backward_f32(const SaBackwardArgs& x, hipStream_t stream) {
+  BwdDev a = common(x);
+  a.nout = a.nbranch = 1;
+  a.c[0] = x.La;
+  a.ehi[0] = x.La + x.Lb;
+  return launch_bwd<float>(a, x.d, stream);
+}
+
+hipError_t launch_llsa_backward_general(const LlsaBackwardArgs& x, ElemType et, hipStream_t stream) {
+  BwdDev a = common(x);
+  // branch 0 (causal) holds channels 0 .. La-1, branch 1 (look-ahead) channel La;
+  // output 0 is channel 0 with branch 0's query, output 1 channel La with branch 1's
+  a.nout = 2;
+  a.nbranch = 2;
+  a.c[1] = x.La;
+  a.qb[1] = 1;
+  a.ehi[0] = x.La - 1;  // empty when La = 0
+  a.elo[1] = x.La;
+  a.ehi[1] = x.La + x.Lb;
+  return launch_bwd_typed(a, x.d, et, stream);
+}
+
+hipError_t launch_llsa_paper_backward_general(const LlsaPaperBwdArgs& x, ElemType et, hipStream_t stream) {
+  BwdDev a = common(x);
+  // every channel a branch of its own, computed with its own query
+  a.nout = x.La + 1;
+  a.nbranch = x.La + 1;
+  for (int c = 0; c <= x.La; ++c) {
+    a.c[c] = c;
+    a.qb[c] = c;
+    a.elo[c] = c;
+    a.ehi[c] = c < x.La ? c : x.La + x.Lb;
+  }
+  return launch_bwd_typed(a, x.d, et, stream);
 }
 
 }  // namespace sa

@@ -83,3 +83,66 @@ def test_llsa_forward_float32(oracle_mod, B, T, H, d, Lb, La):
     assert_slices_close(f64(out), yr, "f32", L, "out")
     assert_lse_close(lse.cpu().numpy(), lr, "f32")
 
+
+@pytest.mark.parametrize("B,T,H,d,Lb,La,lengths", SHAPES)
+def test_sa_backward_float32(oracle_mod, B, T, H, d, Lb, La, lengths):
+    print("f32 backward B=%d T=%d H=%d d=%d Lb=%d La=%d" % (B, T, H, d, Lb, La), flush=True)
+    x = sa_inputs(B, T, H, d, 64, dtype="f32", scale="unit", lengths=lengths, pad_value=float("nan"))
+    q, k, v, do = (to_gpu(x[n], "f32") for n in ("q", "k", "v", "dout"))
+    ln, L = x["lengths"].cuda(), x["lengths"].numpy()
+    out, lse = bd.sa_forward(q, k, v, Lb, La, ln)
+    got = bd.sa_backward(q, k, v, out, lse, do, Lb, La, ln)
+    ref = oracle_mod.sa_backward(*(np.nan_to_num(f64(x[n])) for n in ("q", "k", "v", "dout")), Lb,
+                                 La, L)
+    zero = 1e-5 * float(np.max(np.abs(ref[2])))  # dq, dk of one-frame windows are exactly zero
+    for n, g, r in zip(("dq", "dk", "dv"), got, ref):
+        assert_slices_close(f64(g), r, "f32", L, n, zero_atol=zero)
+
+
+# two-branch LLSA: float32, and bfloat16 at a window no staged kernel takes
+# (held to the bfloat16 tolerance, from the forward's rounded outputs)
+@pytest.mark.parametrize("dtype,B,T,H,d,Lb,La,lengths", [
+    ("f32", 2, 65, 1, 64, 14, 1, (16, 65)),
+    ("f32", 1, 81, 2, 32, 5, 16, "full"),
+    ("f32", 2, 130, 1, 64, 0, 17, (30, 130)),
+    ("f32", 3, 70, 1, 64, 33, 0, (0, 70)),
+    ("bf16", 2, 129, 2, 64, 130, 15, (17, 129)),
+    ("bf16", 1, 210, 1, 64, 97, 33, "full"),
+    ("bf16", 70, 40, 1, 32, 300, 5, (0, 40)),
+])
+def test_llsa_backward_float32_arithmetic(oracle_mod, dtype, B, T, H, d, Lb, La, lengths):
+    print("%s llsa backward B=%d T=%d H=%d d=%d Lb=%d La=%d" % (dtype, B, T, H, d, Lb, La), flush=True)
+    x = llsa_inputs(B, T, H, d, 65, dtype=dtype, scale="unit", lengths=lengths,
+                    pad_value=float("nan"), with_dout=True)
+    names = ("q", "k", "v", "dout")
+    q, k, v, do = (to_gpu(x[n], dtype) for n in names)
+    ln, L = x["lengths"].cuda(), x["lengths"].numpy()
+    clean = [np.nan_to_num(f64(x[n])) for n in names]
+    y, lse = oracle_mod.llsa_two_branch(*clean[:3], Lb, La, L)
+    out = torch.from_numpy(y).to(q.dtype).cuda()
+    got = bd.llsa_backward(q, k, v, out, torch.from_numpy(lse).float().cuda(), do, Lb, La, ln)
+    ref = oracle_mod.llsa_two_branch_backward(*clean, Lb, La, L, y=f64(out))
+    zero = 1e-5 * float(np.max(np.abs(ref[2])))
+    for n, g, r in zip(("dq", "dk", "dv"), got, ref):
+        assert_slices_close(f64(g), r, dtype, L, n, zero_atol=zero, row_scale=dtype == "bf16")
+
+
+@pytest.mark.parametrize("where", ["q", "k", "v", "dout"])
+def test_backward_nonfinite_frames_stay_in_their_windows(where):
+    B, T, H, d, Lb, La, at = 1, 90, 2, 64, 7, 3, 41
+    x = sa_inputs(B, T, H, d, 66, dtype="f32", scale="unit")
+    g = {n: to_gpu(x[n], "f32") for n in ("q", "k", "v", "dout")}
+    out, lse = bd.sa_forward(g["q"], g["k"], g["v"], Lb, La)
+    clean = [t.cpu() for t in bd.sa_backward(g["q"], g["k"], g["v"], out, lse, g["dout"], Lb, La)]
+    g[where][0, at, 0, 5] = float("inf")
+    got = [t.cpu() for t in bd.sa_backward(g["q"], g["k"], g["v"], out, lse, g["dout"], Lb, La)]
+    t = torch.arange(T)
+    q_sees = (t - Lb <= at) & (at <= t + La)      # queries whose window holds frame `at`
+    k_seen = (at - Lb <= t) & (t <= at + La)      # keys in the window of query `at`
+    # gradient rows that read the changed row (with out and lse supplied)
+    reads = {"q": (t == at, k_seen, k_seen), "dout": (t == at, k_seen, k_seen),
+             "k": (q_sees, t == at, t == at), "v": (q_sees, t == at, t == at)}[where]
+    for n, a, c, r in zip(("dq", "dk", "dv"), got, clean, reads):
+        assert torch.equal(a[0, :, 1], c[0, :, 1]), n
+        torch.testing.assert_close(a[0, ~r, 0], c[0, ~r, 0], rtol=1e-5, atol=1e-5, msg=n)
+    assert not torch.isfinite(got[0][0, reads[0], 0]).all()
