@@ -1,0 +1,351 @@
+// Band-attention backward on bfloat16 for any window (the channel form of
+// channel_bwd.h): SA, two-branch LLSA and paper-form LLSA windows that no staged
+// kernel of band_bwd.hip takes.
+//
+// A workgroup of four waves owns 64 rows of one role (a query role gathers dq of
+// an output, a key role dk and dv of a branch), 16 per wave, one row per lane
+// column of the MFMA's N dimension. The rows it reads (keys and values, or
+// queries and output gradients) stream through LDS in chunks of 8 KB per tensor:
+// a chunk's loads are in flight in registers while the chunk before it is
+// computed, and one barrier per chunk hands its buffer over. Every gradient row
+// has one writer: no atomics, no workspace, deterministic.
+//
+// What bounds it: the latency of a block's chain (operand reads, score products,
+// exponentials, transposed reads, gradient products) at three waves per SIMD. At
+// B = 4, T = 1000, H = 16, d = 64, a window of 490 and ragged lengths the SA
+// backward takes 48 us (58 us with the whole band of a tile staged in segments
+// of 144 rows that nothing overlapped), its matrix instructions 7 us and its LDS
+// reads 13 us of that; 9 us per sequence more, so some 12 us are launch, first
+// chunks and the last wave of workgroups. Measured slower there: reading the
+// transposed operands ahead of the products (59 us: 201 registers, two waves per
+// SIMD), four waves per SIMD (62 us, spilling) and 32 rows per wave (51 us;
+// faster only with eight times the sequences, 290 against 303 us).
+//
+// SPLIT: weights and score gradients enter their products as bfloat16 hi + lo
+// (16 bits of each), so that the sums keep the error of float32 weights: the
+// windows served this way were computed in float32 before they ran here, and
+// their gradients' error (1.8e-3 of the gradient, its rounding to bfloat16; with
+// weights rounded to bfloat16 2.5e-3) stays what it was.
+//
+// A matrix product multiplies the rows outside a row's window by a zero weight,
+// and 0 * inf is NaN: a wave that ends with a value that is not finite
+// recomputes its rows one by one over their own windows only (bwd_rows_slow),
+// so that an infinity or NaN reaches exactly the rows whose window holds it.
+#include "channel_bwd.h"
+#include "device_common.h"
+#include "kernels.h"
+#include "rows16.h"
+
+namespace sa {
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int kTileRows = 4 * kRowsPerWave;  // rows of a workgroup
+constexpr int kChunkBytes = 8192;  // of one tensor
+constexpr int kSub = 32;           // rows of a block: the contraction length of one MFMA
+
+// c + x . y of two 16-byte pieces, summed in float32
+__device__ __forceinline__ float dot_pieces(u32x4 x, u32x4 y, float c) {
+  return dot_bf16x8(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c);
+}
+
+__device__ __forceinline__ void split_bf16(f32x8 x, bf16x8& hi, bf16x8& lo) {
+  hi = __builtin_convertvector(x, bf16x8);
+  lo = __builtin_convertvector(x - __builtin_convertvector(hi, f32x8), bf16x8);
+}
+
+// Position of a tile's sweep: relation rel (key role: output, query role:
+// branch) reads rows r + blo .. r + bhi for the tile's row r, in chunks from
+// frame cs on, up to frame end.
+struct Sweep {
+  int rel, cs, end, blo, bhi;
+};
+
+template <int D>
+struct SweepLds {
+  static constexpr int CH = kChunkBytes / (2 * D);  // rows of a chunk
+  __attribute__((aligned(128))) uint16_t x[2][CH * D], y[2][CH * D];
+  __attribute__((aligned(16))) float ndn[2][CH];  // -D_n (key role)
+  __attribute__((aligned(16))) float l2[2][CH];   // lse_n log2(e) (key role)
+};
+
+// One role of one tile. x: its branch (key role) or output (query role); f0: the
+// tile's first frame (f0 < len).
+template <int D, bool SPLIT, bool KEY>
+__device__ __forceinline__ void sweep_role(const BwdDev& a, SweepLds<D>& sm, int x, int b, int h, int f0, int len,
+                                           int w, int lane) {
+  constexpr int F = D / 16, NS = D / 32, CPR = D / 8;
+  constexpr int CH = SweepLds<D>::CH, NP = CH * CPR / kThreads;  // pieces per thread, tensor and chunk
+  constexpr int RW = kRowsPerWave;
+  const int col = lane & 15, g = lane >> 4, tid = 64 * w + lane;
+  const int T = a.T, H = a.H, fs = H * D, last = len - 1;
+  const size_t slice = row_index(b, 0, h, T, H, D);
+  const uint16_t *q = static_cast<const uint16_t*>(a.q) + slice, *k = static_cast<const uint16_t*>(a.k) + slice;
+  const uint16_t *v = static_cast<const uint16_t*>(a.v) + slice, *o = static_cast<const uint16_t*>(a.out) + slice;
+  const uint16_t* dout = static_cast<const uint16_t*>(a.dout) + slice;
+  const float* lse = a.lse + (static_cast<size_t>(b) * H + h) * T;
+  const int fmax = min(f0 + kTileRows - 1, last);
+  const int nrel = KEY ? a.nout : a.nbranch;
+
+  auto open = [&](Sweep& s, int from) {
+    for (s.rel = from; s.rel < nrel; ++s.rel) {
+      const int lo = KEY ? a.c[s.rel] - a.ehi[x] : a.c[x] - a.ehi[s.rel];
+      const int hi = KEY ? a.c[s.rel] - a.elo[x] : a.c[x] - a.elo[s.rel];
+      s.blo = KEY ? -hi : lo;
+      s.bhi = KEY ? -lo : hi;
+      const int base = f0 + s.blo, beg = max(0, base);
+      s.end = min(last, fmax + s.bhi);
+      if (lo > hi || beg > s.end) continue;
+      s.cs = base + (beg - base) / CH * CH;
+      return true;
+    }
+    return false;
+  };
+  u32x4 rx[NP], ry[NP], ro[KEY ? NP : 1];
+  float rl[KEY ? NP : 1];
+  // A thread's pieces: rows tr + i * kThreads / CPR of a chunk, piece tid % CPR.
+  // In a chunk inside the sequence their offsets from the chunk's first row are
+  // the same every time (bytes within 32 bits: a sequence has under 2^31
+  // elements); rows outside it are replaced by its first or last one.
+  constexpr int RPT = kThreads / CPR;
+  const int tr = tid / CPR;
+  uint32_t inoff[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i)
+    inoff[i] = 2u * (static_cast<uint32_t>(tr + i * RPT) * static_cast<uint32_t>(fs) + 8u * (tid % CPR));
+  auto fetch = [&](const Sweep& s) {
+    const int base = min(max(s.cs, 0), last);
+    uint32_t off[NP], lo[KEY ? NP : 1];
+    if (s.cs >= 0 && s.cs + CH - 1 <= last) {
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        off[i] = inoff[i];
+        if constexpr (KEY) lo[i] = 4u * static_cast<uint32_t>(tr + i * RPT);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const uint32_t d = static_cast<uint32_t>(min(max(s.cs + tr + i * RPT, 0), last) - base);
+        off[i] = 2u * (d * static_cast<uint32_t>(fs) + 8u * (tid % CPR));
+        if constexpr (KEY) lo[i] = 4u * d;
+      }
+    }
+    const size_t row = static_cast<size_t>(base) * fs;
+    auto at = [](const void* p, uint32_t bytes) { return static_cast<const char*>(p) + bytes; };
+    const uint16_t* xp = (KEY ? q + a.qb[s.rel] * a.bstride : k + s.rel * a.bstride) + row;
+    const uint16_t* yp = (KEY ? dout : v) + s.rel * a.bstride + row;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      rx[i] = ld16(at(xp, off[i]));
+      ry[i] = ld16(at(yp, off[i]));
+      if constexpr (KEY) {
+        ro[i] = ld16(at(o + s.rel * a.bstride + row, off[i]));
+        rl[i] = *reinterpret_cast<const float*>(at(lse + s.rel * a.lstride + base, lo[i]));
+      }
+    }
+  };
+  auto put = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int e = tid + i * kThreads, r = e / CPR;
+      st16(sm.x[buf] + seg_off<D>(r, 8 * (e % CPR)), rx[i]);
+      st16(sm.y[buf] + seg_off<D>(r, 8 * (e % CPR)), ry[i]);
+      if constexpr (KEY) {
+        const float dn = group_sum<CPR>(dot_pieces(ry[i], ro[i], 0.f));
+        if (e % CPR == 0) {
+          sm.ndn[buf][r] = -dn;
+          sm.l2[buf][r] = rl[i] * kLog2e;
+        }
+      }
+    }
+  };
+  Sweep nxt;
+  bool more = open(nxt, 0);
+  if (more) fetch(nxt);
+
+  // own rows, the N operand of the score products (lanes past the end hold the
+  // last frame's and are masked)
+  const int r0 = f0 + RW * w;
+  const int wmax = min(r0 + RW - 1, last);
+  const uint16_t* own0 = KEY ? k + x * a.bstride : q + a.qb[x] * a.bstride;
+  const uint16_t* own1 = (KEY ? v : dout) + x * a.bstride;
+  bf16x8 b0[NS], b1[NS];
+  float dn = 0.f, l2 = 0.f;
+  const int me = r0 + col;
+  const bool valid = me < len;
+  {
+    const int off = min(me, last) * fs;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+      const u32x4 y = ld16(own1 + off + 32 * j + 8 * g);
+      b0[j] = __builtin_bit_cast(bf16x8, ld16(own0 + off + 32 * j + 8 * g));
+      b1[j] = __builtin_bit_cast(bf16x8, y);
+      if constexpr (!KEY) dn = dot_pieces(y, ld16(o + x * a.bstride + off + 32 * j + 8 * g), dn);
+    }
+    if constexpr (!KEY) {
+      dn = sum_over_column(dn);
+      l2 = lse[x * a.lstride + min(me, last)] * kLog2e;
+    }
+  }
+  f32x4 acc0[F], acc1[F];  // dq, or dk and dv
+#pragma unroll
+  for (int f = 0; f < F; ++f) acc0[f] = acc1[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const SubBlockAddr<D, 0> ad(lane, 0);
+  const float c2 = a.scale_log2;
+
+  // the own rows are in before the loop: a wait for them inside it would also
+  // wait for the chunk loads issued there
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  for (int n = 0; more; ++n) {
+    const Sweep cur = nxt;
+    const int buf = n & 1;
+    put(buf);
+    // chunk n is in; every wave is done with chunk n - 1, whose buffer chunk
+    // n + 1 takes
+    lds_barrier();
+    nxt.cs += CH;
+    more = nxt.cs <= nxt.end || open(nxt, nxt.rel + 1);
+    if (more) fetch(nxt);
+    const int wbeg = max(0, r0 + cur.blo), wend = wmax < r0 ? -1 : min(last, wmax + cur.bhi);
+    const Span see(valid, max(0, me + cur.blo), min(last, me + cur.bhi));
+    // frames that every valid row of the wave sees
+    const int ibeg = max(0, wmax + cur.blo), iend = min(last, r0 + cur.bhi);
+    const uint32_t xb = lds_addr(sm.x[buf]), yb = lds_addr(sm.y[buf]);
+#pragma unroll 1
+    for (int sb = 0; sb < CH; sb += kSub) {
+      const int fb = cur.cs + sb;
+      if (fb > wend || fb + kSub - 1 < wbeg) continue;
+      const uint32_t xa = xb + ad.ua + sb * 2 * D, ya = yb + ad.ua + sb * 2 * D;
+      const uint32_t xt = xb + ad.ut + sb * 2 * D, yt = yb + ad.ut + sb * 2 * D;
+      bf16x8 xr[2 * NS], yr[2 * NS];
+#pragma unroll
+      for (int j = 0; j < NS; ++j) {
+        xr[2 * j] = lds_rd8(xa ^ (64 * j));
+        xr[2 * j + 1] = lds_rd8((xa ^ (64 * j)) + 8 * D);
+        yr[2 * j] = lds_rd8(ya ^ (64 * j));
+        yr[2 * j + 1] = lds_rd8((ya ^ (64 * j)) + 8 * D);
+      }
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+      f32x4 dp0 = {-dn, -dn, -dn, -dn}, dp1 = dp0, ls0 = {l2, l2, l2, l2}, ls1 = ls0;
+      if constexpr (KEY) {  // lane (g, col) holds rows 8g .. 8g + 7
+        dp0 = *reinterpret_cast<const f32x4*>(&sm.ndn[buf][sb + 8 * g]);
+        dp1 = *reinterpret_cast<const f32x4*>(&sm.ndn[buf][sb + 8 * g + 4]);
+        ls0 = *reinterpret_cast<const f32x4*>(&sm.l2[buf][sb + 8 * g]);
+        ls1 = *reinterpret_cast<const f32x4*>(&sm.l2[buf][sb + 8 * g + 4]);
+      }
+#pragma unroll
+      for (int j = 0; j < NS; ++j) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xr[2 * j], b0[j], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xr[2 * j + 1], b0[j], s1, 0, 0, 0);
+        dp0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yr[2 * j], b1[j], dp0, 0, 0, 0);
+        dp1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yr[2 * j + 1], b1[j], dp1, 0, 0, 0);
+      }
+      f32x8 p, ds;
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        p[j] = __builtin_fmaf(j < 4 ? s0[j] : s1[j - 4], c2, j < 4 ? -ls0[j] : -ls1[j - 4]);
+      if (!(fb >= ibeg && fb + kSub - 1 <= iend)) {  // crosses a window edge
+#pragma unroll
+        for (int j = 0; j < 8; ++j) p[j] = see.has(fb + 8 * g + j) ? p[j] : kNegInf;
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        p[j] = fast_exp2(p[j]);
+        ds[j] = p[j] * (j < 4 ? dp0[j] : dp1[j - 4]);
+      }
+      bf16x8 ph, pl, dh, dl;
+      if constexpr (SPLIT) {
+        if constexpr (KEY) split_bf16(p, ph, pl);
+        split_bf16(ds, dh, dl);
+      } else {
+        if constexpr (KEY) ph = __builtin_convertvector(p, bf16x8);
+        dh = __builtin_convertvector(ds, bf16x8);
+      }
+#pragma unroll
+      for (int f = 0; f < F; ++f) {
+        const bf16x8 tx = lds_tr8_at<8 * D>(xt ^ (32 * f));
+        acc0[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tx, dh, acc0[f], 0, 0, 0);
+        if constexpr (SPLIT) acc0[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tx, dl, acc0[f], 0, 0, 0);
+        if constexpr (KEY) {
+          const bf16x8 ty = lds_tr8_at<8 * D>(yt ^ (32 * f));
+          acc1[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ty, ph, acc1[f], 0, 0, 0);
+          if constexpr (SPLIT) acc1[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ty, pl, acc1[f], 0, 0, 0);
+        }
+      }
+    }
+  }
+  uint16_t* const d0 = static_cast<uint16_t*>(KEY ? a.dk : a.dq) + slice + (KEY ? x : a.qb[x]) * a.bstride;
+  uint16_t* const d1 = static_cast<uint16_t*>(a.dv) + slice + x * a.bstride;
+  const int r1 = min(r0 + RW, T);
+  if (r0 < len && __any(valid && !(all_finite<F>(acc0) && (!KEY || all_finite<F>(acc1))))) {
+    bwd_rows_slow<uint16_t, D>(a, KEY, x, b, h, r0, len, lane);
+    if (len < r1) {
+      zero_rows<D>(d0, fs, len, r1, lane);
+      if constexpr (KEY) zero_rows<D>(d1, fs, len, r1, lane);
+    }
+  } else {
+    store_rows_direct<D>(d0, fs, r0, r1 - r0, acc0, a.scale, valid, lane);
+    if constexpr (KEY) store_rows_direct<D>(d1, fs, r0, r1 - r0, acc1, 1.f, valid, lane);
+  }
+}
+
+template <int D, bool SPLIT>
+__global__ __launch_bounds__(kThreads) void band_bwd_sweep_kernel(BwdDev a) {
+  constexpr int TR = kTileRows;
+  __shared__ SweepLds<D> sm;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int T = a.T, H = a.H, fs = H * D;
+  const int nroles = a.nbranch + a.nout;
+  for (int bid = blockIdx.x; bid < a.items; bid += gridDim.x) {
+    // items of a slice: the key roles and query roles of tile 0, of tile 1, ...
+    int bh, item;
+    if (!xcd_slice_item(bid, a.B * H, nroles * a.ntiles, bh, item)) continue;
+    const int tile = item / nroles, role = item - tile * nroles;
+    const bool key_role = role < a.nbranch;
+    const int x = key_role ? role : role - a.nbranch;  // branch or output
+    const int b = bh / H, h = bh - b * H;
+    const int len = clamp_len_uniform(a.lengths, b, T);
+    const int f0 = tile * TR;
+    if (f0 >= len) {
+      const size_t slice = row_index(b, 0, h, T, H, D);
+      const int z0 = f0 + TR / 4 * w, z1 = min(z0 + TR / 4, T);
+      zero_rows<D>(static_cast<uint16_t*>(key_role ? a.dk : a.dq) + slice + (key_role ? x : a.qb[x]) * a.bstride, fs,
+                   z0, z1, lane);
+      if (key_role) zero_rows<D>(static_cast<uint16_t*>(a.dv) + slice + x * a.bstride, fs, z0, z1, lane);
+      continue;
+    }
+    if (key_role)
+      sweep_role<D, SPLIT, true>(a, sm, x, b, h, f0, len, w, lane);
+    else
+      sweep_role<D, SPLIT, false>(a, sm, x, b, h, f0, len, w, lane);
+    lds_barrier();  // every wave is done with the buffers before the next item's
+  }
+}
+
+template <bool SPLIT>
+hipError_t launch_bwd(BwdDev a, int d, hipStream_t stream) {
+  set_items(a, d, kTileRows);
+  const dim3 grid(a.items < kMaxGrid ? a.items : kMaxGrid), block(kThreads);
+  if (d == 64)
+    hipLaunchKernelGGL((band_bwd_sweep_kernel<64, SPLIT>), grid, block, 0, stream, a);
+  else
+    hipLaunchKernelGGL((band_bwd_sweep_kernel<32, SPLIT>), grid, block, 0, stream, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_sa_backward_sweep(const SaBackwardArgs& x, hipStream_t stream) {
+  return launch_bwd<false>(sa_args(x), x.d, stream);
+}
+
+hipError_t launch_llsa_backward_general(const LlsaBackwardArgs& x, ElemType et, hipStream_t stream) {
+  return et == kF32 ? launch_llsa_backward_f32(x, stream) : launch_bwd<true>(llsa_args(x), x.d, stream);
+}
+
+hipError_t launch_llsa_paper_backward_general(const LlsaPaperBwdArgs& x, ElemType et, hipStream_t stream) {
+  return et == kF32 ? launch_llsa_paper_backward_f32(x, stream) : launch_bwd<true>(paper_args(x), x.d, stream);
+}
+
+}  // namespace sa

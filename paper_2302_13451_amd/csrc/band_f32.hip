@@ -1,7 +1,6 @@
 // Band attention in float32 arithmetic on the matrix cores
 // (v_mfma_f32_16x16x4_f32), any window: the float32 SA and LLSA forward, and
-// the backward of SA, two-branch LLSA and the paper's LLSA for float32 tensors
-// and for the bfloat16 windows that no staged kernel takes.
+// the float32 backward of SA, two-branch LLSA and the paper's LLSA.
 //
 // One wave owns 16 rows (queries, or keys in the backward's key role), one row
 // per lane column of the MFMA's N dimension, and sweeps the rows its window
@@ -15,186 +14,33 @@
 //     loads features F col .. F col + F - 1 (F = D / 16) of row 4g + i for step
 //     i. A score tile comes out as rows 4g + i of column col, which is the
 //     weight operand of step i: weights never leave their registers.
-// Both patterns read whole rows per instruction, the four waves of a workgroup
-// own neighbouring rows and meet in the L1, and a block's loads are issued
-// before the products of the block before it finish, so no LDS and no barrier
-// is needed. What bounds it: the float32 MFMA rate (157 TFLOP/s: a 16 x 16
-// block and 64 features is 512 cycles of one SIMD per product) against the
-// rows' way through the L1; HBM only sees each row about once.
+// The four waves of a workgroup own neighbouring rows and meet in the L1; a
+// block's row loads are issued once the score products of the block before it
+// have taken their operands, its transposed rows before its score products, so
+// neither LDS nor a barrier is needed.
+//
+// What bounds it (B = 8, T = 500, H = 12, d = 64, Lb = 32, La = 8, ragged):
+// backward 54 us, of which the float32 matrix instructions are 14 us (512 cycles
+// of one SIMD per product of a 16 x 16 block and 64 features) and the traffic 14
+// us at the device copy's rate; the rest is the latency of a wave's four to five
+// blocks at two waves per SIMD. One thread per row on the vector ALUs took 441
+// us, loads in the order of use 57 us, and rows staged through LDS by a
+// workgroup 61 us. Forward 16 us (177 us), at the same shape.
 //
 // A matrix product multiplies the rows outside a row's window by a zero
 // weight, and 0 * inf is NaN: a wave that ends with a value that is not finite
 // recomputes its rows one by one over their own windows only (rows_slow), so
 // that an infinity or NaN reaches exactly the rows whose window holds it.
 #include "device_common.h"
+#include "channel_bwd.h"
 #include "kernels.h"
-#include "sa.h"
+#include "rows16.h"
 
 namespace sa {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kRowsPerWave = 16;
-constexpr int kTileRows = 64;          // rows of a workgroup (four waves)
-constexpr int kMaxGrid = 1 << 20;      // workgroups per launch; more items loop
-constexpr int kMaxOut = SA_LLSA_PAPER_MAX_LA + 1;  // outputs and branches of one backward call
-
-__device__ __forceinline__ float lo_bf(uint32_t x) { return __uint_as_float(x << 16); }
-__device__ __forceinline__ float hi_bf(uint32_t x) { return __uint_as_float(x & 0xffff0000u); }
-
-// Row pattern: this lane's D / 4 features of a row, in contraction-step order.
-template <int D>
-__device__ __forceinline__ void row_frag(const float* row, int g, float* x) {
-#pragma unroll
-  for (int j = 0; j < D / 16; ++j) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(row + 16 * j + 4 * g);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) x[4 * j + s] = v[s];
-  }
-}
-template <int D>
-__device__ __forceinline__ void row_frag(const uint16_t* row, int g, float* x) {
-#pragma unroll
-  for (int j = 0; j < D / 32; ++j) {
-    const u32x4 v = ld16(row + 32 * j + 8 * g);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      x[8 * j + 2 * s] = lo_bf(v[s]);
-      x[8 * j + 2 * s + 1] = hi_bf(v[s]);
-    }
-  }
-}
-
-// Features F col .. F col + F - 1 of a row (F = D / 16: 2 or 4).
-template <int D>
-__device__ __forceinline__ void feat_frag(const float* row, int col, float* x) {
-  if constexpr (D == 64) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(row + 4 * col);
-    x[0] = v[0]; x[1] = v[1]; x[2] = v[2]; x[3] = v[3];
-  } else {
-    const f32x2 v = *reinterpret_cast<const f32x2*>(row + 2 * col);
-    x[0] = v[0]; x[1] = v[1];
-  }
-}
-template <int D>
-__device__ __forceinline__ void feat_frag(const uint16_t* row, int col, float* x) {
-  if constexpr (D == 64) {
-    const u32x2 v = *reinterpret_cast<const u32x2*>(row + 4 * col);
-    x[0] = lo_bf(v[0]); x[1] = hi_bf(v[0]); x[2] = lo_bf(v[1]); x[3] = hi_bf(v[1]);
-  } else {
-    const uint32_t v = *reinterpret_cast<const uint32_t*>(row + 2 * col);
-    x[0] = lo_bf(v); x[1] = hi_bf(v);
-  }
-}
-__device__ __forceinline__ void store_feat(float* p, const float* x, int n) {
-  if (n == 4) *reinterpret_cast<f32x4*>(p) = f32x4{x[0], x[1], x[2], x[3]};
-  else *reinterpret_cast<f32x2*>(p) = f32x2{x[0], x[1]};
-}
-__device__ __forceinline__ void store_feat(uint16_t* p, const float* x, int n) {
-  if (n == 4) st8(p, u32x2{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])});
-  else *reinterpret_cast<uint32_t*>(p) = pack_bf16x2(x[0], x[1]);
-}
-
-// A . B over the head dim: 16 rows against the wave's 16 own rows. Two chains,
-// so that a product does not wait for the one before it.
-template <int N>
-__device__ __forceinline__ f32x4 row_product(const float* a, const float* b) {
-  f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
-#pragma unroll
-  for (int n = 0; n < N; n += 2) {
-    s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[n], b[n], s0, 0, 0, 0);
-    s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[n + 1], b[n + 1], s1, 0, 0, 0);
-  }
-  return s0 + s1;
-}
-
-// acc[f] += X^T W over 16 frames: x[i] this lane's features of frame 4g + i,
-// w[i] the weights of that frame.
-template <int F>
-__device__ __forceinline__ void col_product(const float (*x)[F], const float* w, f32x4* acc) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int f = 0; f < F; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i][f], w[i], acc[f], 0, 0, 0);
-}
-
-template <int F>
-__device__ __forceinline__ bool all_finite(const f32x4* acc) {
-  float z = 0.f;
-#pragma unroll
-  for (int f = 0; f < F; ++f)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) z = __builtin_fmaf(acc[f][r], 0.f, z);  // NaN for an infinity or NaN
-  return z == 0.f;
-}
-
-// Stores row col's features, held as acc[f][r] = feature F (4g + r) + f,
-// times mul (zero rows when !valid). The lanes of a row first trade values
-// (the swaps exchange a lane bit with a register index), so that every store
-// instruction writes 64 contiguous bytes (32 of bfloat16) of 16 rows.
-template <int D, typename E>
-__device__ __forceinline__ void store_own_row(E* row, const f32x4* acc, float mul, bool valid, bool write, int g) {
-  constexpr int F = D / 16;
-  float x[4][F];
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int f = 0; f < F; ++f) x[r][f] = valid ? acc[f][r] * mul : 0.f;
-  auto swap32 = [](float& p, float& q) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(q), false, false);
-    p = __uint_as_float(r[0]);
-    q = __uint_as_float(r[1]);
-  };
-  auto swap16 = [](float& p, float& q) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(q), false, false);
-    p = __uint_as_float(r[0]);
-    q = __uint_as_float(r[1]);
-  };
-  if constexpr (D == 64) {
-    // 4 x 4 transpose of the groups and the register rows: register row r then
-    // holds features 16 r + 4 g ..
-#pragma unroll
-    for (int f = 0; f < F; ++f) {
-      swap32(x[0][f], x[2][f]);
-      swap32(x[1][f], x[3][f]);
-      swap16(x[0][f], x[1][f]);
-      swap16(x[2][f], x[3][f]);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (write) store_feat(row + 16 * r + 4 * g, x[r], 4);
-  } else {
-    // features 8g + 2r + f: four of them (r = 0, 1 and r = 2, 3) make a piece;
-    // after exchanging the upper lane bit with the piece index, piece n of lane
-    // (b5, b4) is features 16 n + 8 b4 + 4 b5 ..
-    float p[2][4] = {{x[0][0], x[0][1], x[1][0], x[1][1]}, {x[2][0], x[2][1], x[3][0], x[3][1]}};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) swap32(p[0][j], p[1][j]);
-#pragma unroll
-    for (int n = 0; n < 2; ++n)
-      if (write) store_feat(row + 16 * n + 8 * (g & 1) + 4 * (g >> 1), p[n], 4);
-  }
-}
-
-// The frames one of a wave's columns sees, as a start and a width: frame x is
-// inside iff unsigned(x - start) <= width; an empty range never matches.
-struct Span {
-  int start;
-  unsigned width;
-  __device__ __forceinline__ Span(bool valid, int lo, int hi) {
-    const bool any = valid && hi >= lo;
-    start = any ? lo : 1 << 30;
-    width = any ? static_cast<unsigned>(hi - lo) : 0u;
-  }
-  __device__ __forceinline__ bool has(int x) const { return static_cast<unsigned>(x - start) <= width; }
-};
-
-// Zeros rows r0 .. r1 - 1 of a slice (one wave).
-template <int D, typename E>
-__device__ __forceinline__ void zero_rows(E* dst, int fs, int r0, int r1, int lane) {
-  constexpr int CPR = D * sizeof(E) / 16, EPC = 16 / sizeof(E);
-  for (int e = lane; e < (r1 - r0) * CPR; e += 64) st16(dst + (r0 + e / CPR) * fs + EPC * (e % CPR), kZero16);
-}
+constexpr int kTileRows = 64;  // rows of a workgroup (four waves)
 
 // ---------------------------------------------------------------------------
 // Forward: up to two outputs, each over one or two window segments.
@@ -215,8 +61,9 @@ __device__ void fwd_rows_slow(const FwdDev& a, const BandJob& job, size_t slice,
   for (int it = 0; it < 4; ++it) {
     const int t = r0 + 4 * it + g;
     if (t >= len) continue;
-    float q[F], acc[F];
-    feat_frag<D>(static_cast<const float*>(job.q) + slice + t * fs, col, q);
+    float acc[F];
+    FeatFrag<float, D> q, x;
+    q.load(static_cast<const float*>(job.q) + slice + t * fs, col);
 #pragma unroll
     for (int f = 0; f < F; ++f) acc[f] = 0.f;
     float m = kNegInf, l = 0.f;
@@ -224,15 +71,15 @@ __device__ void fwd_rows_slow(const FwdDev& a, const BandJob& job, size_t slice,
       const BandSegment& sg = job.seg[si];
       const int lo = max(0, t + sg.lo_off), hi = min(len - 1, t + sg.hi_off);
       for (int key = lo; key <= hi; ++key) {
-        float x[F], s = 0.f;
-        feat_frag<D>(static_cast<const float*>(sg.k) + slice + key * fs, col, x);
+        float s = 0.f;
+        x.load(static_cast<const float*>(sg.k) + slice + key * fs, col);
 #pragma unroll
         for (int f = 0; f < F; ++f) s += q[f] * x[f];
         s = group_sum<16>(s) * a.scale_log2;
         const float mn = fmaxf(m, s), alpha = fast_exp2(m - mn), p = fast_exp2(s - mn);
         m = mn;
         l = l * alpha + p;
-        feat_frag<D>(static_cast<const float*>(sg.v) + slice + key * fs, col, x);
+        x.load(static_cast<const float*>(sg.v) + slice + key * fs, col);
 #pragma unroll
         for (int f = 0; f < F; ++f) acc[f] = acc[f] * alpha + p * x[f];
       }
@@ -248,11 +95,12 @@ __device__ void fwd_rows_slow(const FwdDev& a, const BandJob& job, size_t slice,
 // One wave, 16 queries; the window in steps of 32 keys with an online softmax.
 template <int D>
 __global__ __launch_bounds__(kThreads) void band_fwd_f32_kernel(FwdDev a) {
-  constexpr int N = D / 4, F = D / 16;
+  constexpr int F = D / 16;
   const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int T = a.T, H = a.H, fs = H * D;
   const float c2 = a.scale_log2;
+  const BlockRows<D> rows(fs, col, g);
   for (int bid = blockIdx.x; bid < a.items; bid += gridDim.x) {
     int bh, item;
     if (!xcd_slice_item(bid, a.B * H, a.njobs * a.ntiles, bh, item)) continue;
@@ -273,8 +121,8 @@ __global__ __launch_bounds__(kThreads) void band_fwd_f32_kernel(FwdDev a) {
     }
     const bool valid = t < len;
     const int wmax = min(r0 + kRowsPerWave - 1, len - 1);
-    float q[N];
-    row_frag<D>(static_cast<const float*>(job.q) + slice + min(t, len - 1) * fs, g, q);
+    RowFrag<float, D> q;
+    q.load(static_cast<const float*>(job.q) + slice + min(t, len - 1) * fs, g);
     float m = kNegInf, lsum = 0.f;
     f32x4 acc[F];
 #pragma unroll
@@ -287,22 +135,22 @@ __global__ __launch_bounds__(kThreads) void band_fwd_f32_kernel(FwdDev a) {
       if (wlo > whi) continue;
       const Span win(valid, max(0, t + sg.lo_off), min(len - 1, t + sg.hi_off));
       const int last = len - 1;
-      float k[2][N];
+      RowFrag<float, D> k[2];
       auto load_keys = [&](int kb) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) row_frag<D>(kp + min(kb + 16 * u + col, last) * fs, g, k[u]);
+        for (int u = 0; u < 2; ++u) k[u].load(kp + rows.row(kb + 16 * u, last), g);
       };
       load_keys(wlo);
       for (int kb = wlo; kb <= whi; kb += 32) {
-        float v[2][4][F];
+        FeatFrag<float, D> v[2][4];
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) feat_frag<D>(vp + min(kb + 16 * u + 4 * g + i, last) * fs, col, v[u][i]);
+          for (int i = 0; i < 4; ++i) v[u][i].load(vp + rows.frame(kb + 16 * u, i, last), col);
         float z[2][4], zmax = kNegInf;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-          const f32x4 s = row_product<N>(k[u], q);
+          const f32x4 s = row_product(k[u], q);
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             z[u][i] = win.has(kb + 16 * u + 4 * g + i) ? s[i] : kNegInf;
@@ -324,7 +172,7 @@ __global__ __launch_bounds__(kThreads) void band_fwd_f32_kernel(FwdDev a) {
             z[u][i] = fast_exp2(__builtin_fmaf(z[u][i], c2, -ms));
             lsum += z[u][i];
           }
-          col_product<F>(v[u], z[u], acc);
+          col_product(v[u], z[u], acc);
         }
       }
     }
@@ -341,127 +189,18 @@ __global__ __launch_bounds__(kThreads) void band_fwd_f32_kernel(FwdDev a) {
 }
 
 // ---------------------------------------------------------------------------
-// Backward, in the general channel form (Eq. 7-13 per output row; the paper's
-// Eq. 16 prints only the value part of the LLSA gradient). Channels
-// c = 0 .. La, each held by a branch (tensor); output o computes channel c_o
-// with the query of branch qb_o. Query t of output o reads the frames tau in
-// [t + c_o - La - Lb, t + c_o] (clipped to the sequence), frame tau from the
-// branch whose interval [elo, ehi] holds e = t + c_o - tau, so that output o
-// reads from branch i the band t + c_o - ehi_i .. t + c_o - elo_i. SA is one
-// output and one branch. With P the attention weights of a row,
-// dP_tau = dout . v_tau, D = dout . out and dS = P (dP - D):
-//   dq[qb_o]_t  += (1/sqrt d) sum_tau dS_(t,tau) k[i]_tau
-//   dk[i]_tau   += (1/sqrt d) sum over the (o, t) that read tau from i of dS_(t,tau) q[qb_o]_t
-//   dv[i]_tau   += sum over the same (o, t) of P_(t,tau) dout[o]_t
-// A query role per (output, 16 frames) gathers dq over its bands, a key role
-// per (branch, 16 frames) gathers dk and dv over the outputs' queries that
-// read it. Each output's query branch is distinct, so every gradient row has
-// one writer: no atomics, no workspace, deterministic.
-struct BwdDev {
-  const void *q, *k, *v, *out, *dout;
-  const float* lse;
-  void *dq, *dk, *dv;
-  int B, T, H, ntiles, items;
-  int nout, nbranch;
-  int c[kMaxOut];    // channel of output o
-  int qb[kMaxOut];   // branch of output o's query
-  int elo[kMaxOut];  // e-interval of branch i (empty: elo > ehi)
-  int ehi[kMaxOut];
-  size_t bstride;  // elements of one branch (or output) tensor
-  size_t lstride;  // floats of one output's lse
-  const int32_t* lengths;
-  float scale, scale_log2;
-};
-
-template <typename E, int D>
-__device__ __forceinline__ float feat_dot(const float* x, const E* row, int col) {
-  constexpr int F = D / 16;
-  float y[F], s = 0.f;
-  feat_frag<D>(row, col, y);
-#pragma unroll
-  for (int f = 0; f < F; ++f) s += x[f] * y[f];
-  return group_sum<16>(s);
-}
-
-// The wave's gradient rows one by one (as fwd_rows_slow): the query role of
-// output x, or the key role of branch x.
-template <typename E, int D>
-__device__ void bwd_rows_slow(const BwdDev& a, bool key_role, int x, int b, int h, int r0, int len, int lane) {
-  constexpr int F = D / 16;
-  const int col = lane & 15, g = lane >> 4;
-  const int T = a.T, fs = a.H * D;
-  const size_t slice = row_index(b, 0, h, T, a.H, D);
-  const E *q = static_cast<const E*>(a.q) + slice, *k = static_cast<const E*>(a.k) + slice;
-  const E *v = static_cast<const E*>(a.v) + slice, *o = static_cast<const E*>(a.out) + slice;
-  const E* dout = static_cast<const E*>(a.dout) + slice;
-  const float* lse = a.lse + (static_cast<size_t>(b) * a.H + h) * T;
-  for (int it = 0; it < 4; ++it) {
-    const int t = r0 + 4 * it + g;
-    if (t >= len) continue;
-    float acc0[F], acc1[F], x0[F], x1[F], y[F];
-#pragma unroll
-    for (int f = 0; f < F; ++f) acc0[f] = acc1[f] = 0.f;
-    if (!key_role) {
-      const size_t qo = a.qb[x] * a.bstride, oo = x * a.bstride;
-      feat_frag<D>(q + qo + t * fs, col, x0);
-      feat_frag<D>(dout + oo + t * fs, col, x1);
-      const float dn = feat_dot<E, D>(x1, o + oo + t * fs, col);
-      const float lse2 = lse[x * a.lstride + t] * kLog2e;
-      for (int i = 0; i < a.nbranch; ++i) {
-        const size_t ko = i * a.bstride;
-        const int lo = max(0, t + a.c[x] - a.ehi[i]), hi = min(len - 1, t + a.c[x] - a.elo[i]);
-        for (int tau = lo; tau <= hi; ++tau) {
-          const float p = fast_exp2(feat_dot<E, D>(x0, k + ko + tau * fs, col) * a.scale_log2 - lse2);
-          const float ds = p * (feat_dot<E, D>(x1, v + ko + tau * fs, col) - dn);
-          feat_frag<D>(k + ko + tau * fs, col, y);
-#pragma unroll
-          for (int f = 0; f < F; ++f) acc0[f] += ds * y[f];
-        }
-      }
-#pragma unroll
-      for (int f = 0; f < F; ++f) acc0[f] *= a.scale;
-      store_feat(static_cast<E*>(a.dq) + slice + qo + t * fs + F * col, acc0, F);
-      continue;
-    }
-    const size_t ko = x * a.bstride;
-    feat_frag<D>(k + ko + t * fs, col, x0);
-    feat_frag<D>(v + ko + t * fs, col, x1);
-    for (int oi = 0; oi < a.nout; ++oi) {
-      const size_t qo = a.qb[oi] * a.bstride, oo = oi * a.bstride;
-      const int lo = max(0, t - a.c[oi] + a.elo[x]), hi = min(len - 1, t - a.c[oi] + a.ehi[x]);
-      for (int n = lo; n <= hi; ++n) {
-        float dr[F];
-        feat_frag<D>(dout + oo + n * fs, col, dr);
-        feat_frag<D>(q + qo + n * fs, col, y);
-        const float dn = feat_dot<E, D>(dr, o + oo + n * fs, col);
-        float s = 0.f, dp = 0.f;
-#pragma unroll
-        for (int f = 0; f < F; ++f) {
-          s += x0[f] * y[f];
-          dp += x1[f] * dr[f];
-        }
-        const float p = fast_exp2(group_sum<16>(s) * a.scale_log2 - lse[oi * a.lstride + n] * kLog2e);
-        const float ds = p * (group_sum<16>(dp) - dn);
-#pragma unroll
-        for (int f = 0; f < F; ++f) {
-          acc0[f] += ds * y[f];
-          acc1[f] += p * dr[f];
-        }
-      }
-    }
-#pragma unroll
-    for (int f = 0; f < F; ++f) acc0[f] *= a.scale;
-    store_feat(static_cast<E*>(a.dk) + slice + ko + t * fs + F * col, acc0, F);
-    store_feat(static_cast<E*>(a.dv) + slice + ko + t * fs + F * col, acc1, F);
-  }
-}
-
-template <typename E, int D>
+// Backward (the channel form of channel_bwd.h): a query role per (output, 16
+// frames) gathers dq over its bands, a key role per (branch, 16 frames) gathers
+// dk and dv over the outputs' queries that read it. Every gradient row has one
+// writer: no atomics, no workspace, deterministic.
+template <int D>
 __global__ __launch_bounds__(kThreads) void band_bwd_f32_kernel(BwdDev a) {
+  typedef float E;
   constexpr int N = D / 4, F = D / 16;
   const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int T = a.T, H = a.H, fs = H * D;
+  const BlockRows<D> rows(fs, col, g);
   const int nroles = a.nbranch + a.nout;
   const float c2 = a.scale_log2;
   for (int bid = blockIdx.x; bid < a.items; bid += gridDim.x) {
@@ -496,9 +235,12 @@ __global__ __launch_bounds__(kThreads) void band_bwd_f32_kernel(BwdDev a) {
 #pragma unroll
     for (int f = 0; f < F; ++f) acc0[f] = acc1[f] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (key_role) {
-      float kf[N], vf[N];
-      row_frag<D>(k + x * a.bstride + own, g, kf);
-      row_frag<D>(v + x * a.bstride + own, g, vf);
+      RowFrag<E, D> kf, vf;
+      kf.load(k + x * a.bstride + own, g);
+      vf.load(v + x * a.bstride + own, g);
+      // the own rows are in before the loops: a wait for them inside would also
+      // wait for the loads issued there
+      __builtin_amdgcn_s_waitcnt(0x0f70);
       for (int oi = 0; oi < a.nout; ++oi) {
         const int lo = a.c[oi] - a.ehi[x], hi = a.c[oi] - a.elo[x];
         const int wlo = max(0, r0 - hi), whi = min(last, wmax - lo);
@@ -506,74 +248,91 @@ __global__ __launch_bounds__(kThreads) void band_bwd_f32_kernel(BwdDev a) {
         const Span see(valid, max(0, me - hi), min(last, me - lo));  // queries that see this lane's key
         const E *qp = q + a.qb[oi] * a.bstride, *dp = dout + oi * a.bstride, *op = o + oi * a.bstride;
         const float* lp = lse + oi * a.lstride;
+        // a block's rows are loaded while the dk and dv products of the block
+        // before run, its transposed rows while its score products run
+        RowFrag<E, D> qr, dr, orow;
+        float lv;
+        auto load_rows = [&](int qb) {
+          const size_t rr = rows.row(qb, last);
+          qr.load(qp + rr, g);
+          dr.load(dp + rr, g);
+          orow.load(op + rr, g);
+          lv = lp[min(qb + col, last)];
+        };
+        load_rows(wlo);
         for (int qb = wlo; qb <= whi; qb += 16) {
-          float qr[N], dr[N], orow[N], qt[4][F], dt[4][F], l2[4];
-          const int rr = min(qb + col, last) * fs;
-          row_frag<D>(qp + rr, g, qr);
-          row_frag<D>(dp + rr, g, dr);
-          row_frag<D>(op + rr, g, orow);
+          FeatFrag<E, D> qt[4], dt[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int n = min(qb + 4 * g + i, last);
-            l2[i] = lp[n];
-            feat_frag<D>(dp + n * fs, col, dt[i]);
-            feat_frag<D>(qp + n * fs, col, qt[i]);
+            const size_t rt = rows.frame(qb, i, last);
+            dt[i].load(dp + rt, col);
+            qt[i].load(qp + rt, col);
           }
-          const f32x4 s = row_product<N>(qr, kf), dpv = row_product<N>(dr, vf);
-          // D of query col in every lane of the column, then of the queries
-          // 4g + i whose scores this lane holds
+          const f32x4 s = row_product(qr, kf), dpv = row_product(dr, vf);
+          // D and lse of query col in every lane of the column, then of the
+          // queries 4g + i whose scores this lane holds
           float dn = 0.f;
 #pragma unroll
           for (int n = 0; n < N; ++n) dn += dr[n] * orow[n];
           dn = sum_over_column(dn);
+          const float l2 = lv * kLog2e;
+          if (qb + 16 <= whi) load_rows(qb + 16);
           float p[4], ds[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const float di =
-                __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (4 * g + i), __float_as_int(dn)));
+            const int src = 4 * (4 * g + i);
+            const float di = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(dn)));
+            const float li = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(l2)));
             const bool in = see.has(qb + 4 * g + i);
-            const float pw = fast_exp2(__builtin_fmaf(s[i], c2, -l2[i] * kLog2e));
+            const float pw = fast_exp2(__builtin_fmaf(s[i], c2, -li));
             p[i] = in ? pw : 0.f;
             ds[i] = in ? pw * (dpv[i] - di) : 0.f;
           }
-          col_product<F>(dt, p, acc1);
-          col_product<F>(qt, ds, acc0);
+          col_product(dt, p, acc1);
+          col_product(qt, ds, acc0);
         }
       }
     } else {
       const size_t oo = x * a.bstride;
-      float qf[N], df[N], dn = 0.f;
-      row_frag<D>(q + a.qb[x] * a.bstride + own, g, qf);
-      row_frag<D>(dout + oo + own, g, df);
+      RowFrag<E, D> qf, df;
+      float dn = 0.f;
+      qf.load(q + a.qb[x] * a.bstride + own, g);
+      df.load(dout + oo + own, g);
       {
-        float of[N];
-        row_frag<D>(o + oo + own, g, of);
+        RowFrag<E, D> of;
+        of.load(o + oo + own, g);
 #pragma unroll
         for (int n = 0; n < N; ++n) dn += df[n] * of[n];
         dn = sum_over_column(dn);
       }
       const float l2 = lse[x * a.lstride + min(me, last)] * kLog2e;
+      __builtin_amdgcn_s_waitcnt(0x0f70);
       for (int i = 0; i < a.nbranch; ++i) {
         const int lo = a.c[x] - a.ehi[i], hi = a.c[x] - a.elo[i];
         const int wlo = max(0, r0 + lo), whi = min(last, wmax + hi);
         if (lo > hi || wlo > whi) continue;
         const Span win(valid, max(0, me + lo), min(last, me + hi));
         const E *kp = k + i * a.bstride, *vp = v + i * a.bstride;
+        RowFrag<E, D> kr, vr;
+        auto load_rows = [&](int kb) {
+          const size_t rr = rows.row(kb, last);
+          kr.load(kp + rr, g);
+          vr.load(vp + rr, g);
+        };
+        load_rows(wlo);
         for (int kb = wlo; kb <= whi; kb += 16) {
-          float kr[N], vr[N], kt[4][F];
-          const int rr = min(kb + col, last) * fs;
-          row_frag<D>(kp + rr, g, kr);
-          row_frag<D>(vp + rr, g, vr);
+          FeatFrag<E, D> kt[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) feat_frag<D>(kp + min(kb + 4 * g + u, last) * fs, col, kt[u]);
-          const f32x4 s = row_product<N>(kr, qf), dpv = row_product<N>(vr, df);
+          for (int u = 0; u < 4; ++u) kt[u].load(kp + rows.frame(kb, u, last), col);
+          const f32x4 s = row_product(kr, qf), dpv = row_product(vr, df);
+          if (kb + 16 <= whi) load_rows(kb + 16);
           float ds[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const float pw = fast_exp2(__builtin_fmaf(s[u], c2, -l2));
             ds[u] = win.has(kb + 4 * g + u) ? pw * (dpv[u] - dn) : 0.f;
           }
-          col_product<F>(kt, ds, acc0);
+          col_product(kt, ds, acc0);
         }
       }
     }
@@ -590,43 +349,14 @@ __global__ __launch_bounds__(kThreads) void band_bwd_f32_kernel(BwdDev a) {
   }
 }
 
-template <typename E>
-hipError_t launch_bwd(BwdDev& a, int d, hipStream_t stream) {
-  a.ntiles = (a.T + kTileRows - 1) / kTileRows;
-  a.items = xcd_slice_grid(a.B * a.H, (a.nbranch + a.nout) * a.ntiles);
-  a.scale = 1.f / sqrtf(static_cast<float>(d));
-  a.scale_log2 = kLog2e * a.scale;
+hipError_t launch_bwd(BwdDev a, int d, hipStream_t stream) {
+  set_items(a, d, kTileRows);
   const dim3 grid(a.items < kMaxGrid ? a.items : kMaxGrid), block(kThreads);
   if (d == 64)
-    hipLaunchKernelGGL((band_bwd_f32_kernel<E, 64>), grid, block, 0, stream, a);
+    hipLaunchKernelGGL(band_bwd_f32_kernel<64>, grid, block, 0, stream, a);
   else
-    hipLaunchKernelGGL((band_bwd_f32_kernel<E, 32>), grid, block, 0, stream, a);
+    hipLaunchKernelGGL(band_bwd_f32_kernel<32>, grid, block, 0, stream, a);
   return hipGetLastError();
-}
-
-template <typename Args>
-BwdDev common(const Args& x) {
-  BwdDev a{};
-  a.q = x.q;
-  a.k = x.k;
-  a.v = x.v;
-  a.out = x.out;
-  a.dout = x.dout;
-  a.lse = x.lse;
-  a.dq = x.dq;
-  a.dk = x.dk;
-  a.dv = x.dv;
-  a.B = x.B;
-  a.T = x.T;
-  a.H = x.H;
-  a.lengths = x.lengths;
-  a.bstride = static_cast<size_t>(x.B) * x.T * x.H * x.d;
-  a.lstride = static_cast<size_t>(x.B) * x.H * x.T;
-  return a;
-}
-
-hipError_t launch_bwd_typed(BwdDev& a, int d, ElemType et, hipStream_t stream) {
-  return et == kBF16 ? launch_bwd<uint16_t>(a, d, stream) : launch_bwd<float>(a, d, stream);
 }
 
 }  // namespace
@@ -652,39 +382,15 @@ hipError_t launch_band_forward_f32(const BandForwardArgs& x, hipStream_t stream)
 }
 
 hipError_t launch_sa_backward_f32(const SaBackwardArgs& x, hipStream_t stream) {
-  BwdDev a = common(x);
-  a.nout = a.nbranch = 1;
-  a.c[0] = x.La;
-  a.ehi[0] = x.La + x.Lb;
-  return launch_bwd<float>(a, x.d, stream);
+  return launch_bwd(sa_args(x), x.d, stream);
 }
 
-hipError_t launch_llsa_backward_general(const LlsaBackwardArgs& x, ElemType et, hipStream_t stream) {
-  BwdDev a = common(x);
-  // branch 0 (causal) holds channels 0 .. La-1, branch 1 (look-ahead) channel La;
-  // output 0 is channel 0 with branch 0's query, output 1 channel La with branch 1's
-  a.nout = 2;
-  a.nbranch = 2;
-  a.c[1] = x.La;
-  a.qb[1] = 1;
-  a.ehi[0] = x.La - 1;  // empty when La = 0
-  a.elo[1] = x.La;
-  a.ehi[1] = x.La + x.Lb;
-  return launch_bwd_typed(a, x.d, et, stream);
+hipError_t launch_llsa_backward_f32(const LlsaBackwardArgs& x, hipStream_t stream) {
+  return launch_bwd(llsa_args(x), x.d, stream);
 }
 
-hipError_t launch_llsa_paper_backward_general(const LlsaPaperBwdArgs& x, ElemType et, hipStream_t stream) {
-  BwdDev a = common(x);
-  // every channel a branch of its own, computed with its own query
-  a.nout = x.La + 1;
-  a.nbranch = x.La + 1;
-  for (int c = 0; c <= x.La; ++c) {
-    a.c[c] = c;
-    a.qb[c] = c;
-    a.elo[c] = c;
-    a.ehi[c] = c < x.La ? c : x.La + x.Lb;
-  }
-  return launch_bwd_typed(a, x.d, et, stream);
+hipError_t launch_llsa_paper_backward_f32(const LlsaPaperBwdArgs& x, hipStream_t stream) {
+  return launch_bwd(paper_args(x), x.d, stream);
 }
 
 }  // namespace sa

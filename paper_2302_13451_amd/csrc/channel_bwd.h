@@ -1,0 +1,202 @@
+// The LLSA backward in its general channel form, shared by the kernels that run
+// it for any window (band_f32.hip: float32 tensors, band_bwd_sweep.hip:
+// bfloat16).
+#pragma once
+
+#include "device_common.h"
+#include "kernels.h"
+#include "rows16.h"
+#include "sa.h"
+
+namespace sa {
+namespace {
+
+constexpr int kRowsPerWave = 16;
+constexpr int kMaxGrid = 1 << 20;                  // workgroups per launch; more items loop
+constexpr int kMaxOut = SA_LLSA_PAPER_MAX_LA + 1;  // outputs and branches of one call
+
+// The backward per output row is Eq. 7-13 (the paper's Eq. 16 prints only the
+// value part of the LLSA gradient). Channels
+// c = 0 .. La, each held by a branch (tensor); output o computes channel c_o
+// with the query of branch qb_o. Query t of output o reads the frames tau in
+// [t + c_o - La - Lb, t + c_o] (clipped to the sequence), frame tau from the
+// branch whose interval [elo, ehi] holds e = t + c_o - tau, so that output o
+// reads from branch i the band t + c_o - ehi_i .. t + c_o - elo_i. SA is one
+// output and one branch. With P the attention weights of a row,
+// dP_tau = dout . v_tau, D = dout . out and dS = P (dP - D):
+//   dq[qb_o]_t  += (1/sqrt d) sum_tau dS_(t,tau) k[i]_tau
+//   dk[i]_tau   += (1/sqrt d) sum over the (o, t) that read tau from i of dS_(t,tau) q[qb_o]_t
+//   dv[i]_tau   += sum over the same (o, t) of P_(t,tau) dout[o]_t
+// A query role per (output, 16 frames) gathers dq over its bands, a key role
+// per (branch, 16 frames) gathers dk and dv over the outputs' queries that
+// read it. Each output's query branch is distinct, so every gradient row has
+// one writer: no atomics, no workspace, deterministic.
+struct BwdDev {
+  const void *q, *k, *v, *out, *dout;
+  const float* lse;
+  void *dq, *dk, *dv;
+  int B, T, H, ntiles, items;
+  int nout, nbranch;
+  int c[kMaxOut];    // channel of output o
+  int qb[kMaxOut];   // branch of output o's query
+  int elo[kMaxOut];  // e-interval of branch i (empty: elo > ehi)
+  int ehi[kMaxOut];
+  size_t bstride;  // elements of one branch (or output) tensor
+  size_t lstride;  // floats of one output's lse
+  const int32_t* lengths;
+  float scale, scale_log2;
+};
+
+template <typename E, int D>
+__device__ __forceinline__ float feat_dot(const FeatFrag<E, D>& x, const E* row, int col) {
+  FeatFrag<E, D> y;
+  y.load(row, col);
+  float s = 0.f;
+#pragma unroll
+  for (int f = 0; f < D / 16; ++f) s += x[f] * y[f];
+  return group_sum<16>(s);
+}
+
+// The wave's gradient rows one by one (as fwd_rows_slow): the query role of
+// output x, or the key role of branch x.
+template <typename E, int D>
+__device__ void bwd_rows_slow(const BwdDev& a, bool key_role, int x, int b, int h, int r0, int len, int lane) {
+  constexpr int F = D / 16;
+  const int col = lane & 15, g = lane >> 4;
+  const int T = a.T, fs = a.H * D;
+  const size_t slice = row_index(b, 0, h, T, a.H, D);
+  const E *q = static_cast<const E*>(a.q) + slice, *k = static_cast<const E*>(a.k) + slice;
+  const E *v = static_cast<const E*>(a.v) + slice, *o = static_cast<const E*>(a.out) + slice;
+  const E* dout = static_cast<const E*>(a.dout) + slice;
+  const float* lse = a.lse + (static_cast<size_t>(b) * a.H + h) * T;
+  for (int it = 0; it < 4; ++it) {
+    const int t = r0 + 4 * it + g;
+    if (t >= len) continue;
+    float acc0[F], acc1[F];
+    FeatFrag<E, D> x0, x1, y;
+#pragma unroll
+    for (int f = 0; f < F; ++f) acc0[f] = acc1[f] = 0.f;
+    if (!key_role) {
+      const size_t qo = a.qb[x] * a.bstride, oo = x * a.bstride;
+      x0.load(q + qo + t * fs, col);
+      x1.load(dout + oo + t * fs, col);
+      const float dn = feat_dot<E, D>(x1, o + oo + t * fs, col);
+      const float lse2 = lse[x * a.lstride + t] * kLog2e;
+      for (int i = 0; i < a.nbranch; ++i) {
+        const size_t ko = i * a.bstride;
+        const int lo = max(0, t + a.c[x] - a.ehi[i]), hi = min(len - 1, t + a.c[x] - a.elo[i]);
+        for (int tau = lo; tau <= hi; ++tau) {
+          const float p = fast_exp2(feat_dot<E, D>(x0, k + ko + tau * fs, col) * a.scale_log2 - lse2);
+          const float ds = p * (feat_dot<E, D>(x1, v + ko + tau * fs, col) - dn);
+          y.load(k + ko + tau * fs, col);
+#pragma unroll
+          for (int f = 0; f < F; ++f) acc0[f] += ds * y[f];
+        }
+      }
+#pragma unroll
+      for (int f = 0; f < F; ++f) acc0[f] *= a.scale;
+      store_feat(static_cast<E*>(a.dq) + slice + qo + t * fs + F * col, acc0, F);
+      continue;
+    }
+    const size_t ko = x * a.bstride;
+    x0.load(k + ko + t * fs, col);
+    x1.load(v + ko + t * fs, col);
+    for (int oi = 0; oi < a.nout; ++oi) {
+      const size_t qo = a.qb[oi] * a.bstride, oo = oi * a.bstride;
+      const int lo = max(0, t - a.c[oi] + a.elo[x]), hi = min(len - 1, t - a.c[oi] + a.ehi[x]);
+      for (int n = lo; n <= hi; ++n) {
+        FeatFrag<E, D> dr;
+        dr.load(dout + oo + n * fs, col);
+        y.load(q + qo + n * fs, col);
+        const float dn = feat_dot<E, D>(dr, o + oo + n * fs, col);
+        float s = 0.f, dp = 0.f;
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+          s += x0[f] * y[f];
+          dp += x1[f] * dr[f];
+        }
+        const float p = fast_exp2(group_sum<16>(s) * a.scale_log2 - lse[oi * a.lstride + n] * kLog2e);
+        const float ds = p * (group_sum<16>(dp) - dn);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+          acc0[f] += ds * y[f];
+          acc1[f] += p * dr[f];
+        }
+      }
+    }
+#pragma unroll
+    for (int f = 0; f < F; ++f) acc0[f] *= a.scale;
+    store_feat(static_cast<E*>(a.dk) + slice + ko + t * fs + F * col, acc0, F);
+    store_feat(static_cast<E*>(a.dv) + slice + ko + t * fs + F * col, acc1, F);
+  }
+}
+
+template <typename Args>
+BwdDev common(const Args& x) {
+  BwdDev a{};
+  a.q = x.q;
+  a.k = x.k;
+  a.v = x.v;
+  a.out = x.out;
+  a.dout = x.dout;
+  a.lse = x.lse;
+  a.dq = x.dq;
+  a.dk = x.dk;
+  a.dv = x.dv;
+  a.B = x.B;
+  a.T = x.T;
+  a.H = x.H;
+  a.lengths = x.lengths;
+  a.bstride = static_cast<size_t>(x.B) * x.T * x.H * x.d;
+  a.lstride = static_cast<size_t>(x.B) * x.H * x.T;
+  return a;
+}
+
+// SA: one output and one branch.
+inline BwdDev sa_args(const SaBackwardArgs& x) {
+  BwdDev a = common(x);
+  a.nout = a.nbranch = 1;
+  a.c[0] = x.La;
+  a.ehi[0] = x.La + x.Lb;
+  return a;
+}
+
+// Two branches: branch 0 (causal) holds channels 0 .. La-1, branch 1
+// (look-ahead) channel La; output 0 is channel 0 with branch 0's query, output 1
+// channel La with branch 1's.
+inline BwdDev llsa_args(const LlsaBackwardArgs& x) {
+  BwdDev a = common(x);
+  a.nout = 2;
+  a.nbranch = 2;
+  a.c[1] = x.La;
+  a.qb[1] = 1;
+  a.ehi[0] = x.La - 1;  // empty when La = 0
+  a.elo[1] = x.La;
+  a.ehi[1] = x.La + x.Lb;
+  return a;
+}
+
+// The paper's form: every channel a branch of its own, computed with its own query.
+inline BwdDev paper_args(const LlsaPaperBwdArgs& x) {
+  BwdDev a = common(x);
+  a.nout = x.La + 1;
+  a.nbranch = x.La + 1;
+  for (int c = 0; c <= x.La; ++c) {
+    a.c[c] = c;
+    a.qb[c] = c;
+    a.elo[c] = c;
+    a.ehi[c] = c < x.La ? c : x.La + x.Lb;
+  }
+  return a;
+}
+
+// Tiles, items and scales of a launch; the items run on at most kMaxGrid workgroups.
+inline void set_items(BwdDev& a, int d, int tile_rows) {
+  a.ntiles = (a.T + tile_rows - 1) / tile_rows;
+  a.items = xcd_slice_grid(a.B * a.H, (a.nbranch + a.nout) * a.ntiles);
+  a.scale = 1.f / sqrtf(static_cast<float>(d));
+  a.scale_log2 = kLog2e * a.scale;
+}
+
+}  // namespace
+}  // namespace sa

@@ -72,8 +72,9 @@ hipError_t launch_llsa_paper_backward_band(const LlsaPaperBwdArgs& a, hipStream_
 bool llsa_paper_backward_fits(int d, int Lb, int La);
 // The whole backward: the band part, then the diagonal frames' part.
 hipError_t launch_llsa_paper_backward(const LlsaPaperBwdArgs& a, ElemType et, hipStream_t stream);
-// Any window and either element type, in float32 arithmetic on MFMA (band_f32.hip).
+// Any window and either element type (band_bwd_sweep.hip, float32: band_f32.hip).
 hipError_t launch_llsa_paper_backward_general(const LlsaPaperBwdArgs& a, ElemType et, hipStream_t stream);
+hipError_t launch_llsa_paper_backward_f32(const LlsaPaperBwdArgs& a, hipStream_t stream);
 
 struct SaBackwardArgs {
   const void *q, *k, *v, *out, *dout;
@@ -86,6 +87,8 @@ struct SaBackwardArgs {
 hipError_t launch_sa_backward(const SaBackwardArgs& a, ElemType et, hipStream_t stream);
 // float32 tensors, any window (band_f32.hip).
 hipError_t launch_sa_backward_f32(const SaBackwardArgs& a, hipStream_t stream);
+// bfloat16 tensors, any window (band_bwd_sweep.hip).
+hipError_t launch_sa_backward_sweep(const SaBackwardArgs& a, hipStream_t stream);
 
 // Two-branch LLSA backward; every tensor but lse is [2][B][T][H][d] (index 0:
 // causal branch, 1: look-ahead branch), lse is [2][B][H][T]. bfloat16 only.
@@ -98,8 +101,9 @@ struct LlsaBackwardArgs {
 };
 
 hipError_t launch_llsa_backward(const LlsaBackwardArgs& a, ElemType et, hipStream_t stream);
-// Any window and either element type, in float32 arithmetic on MFMA (band_f32.hip).
+// Any window and either element type (band_bwd_sweep.hip, float32: band_f32.hip).
 hipError_t launch_llsa_backward_general(const LlsaBackwardArgs& a, ElemType et, hipStream_t stream);
+hipError_t launch_llsa_backward_f32(const LlsaBackwardArgs& a, hipStream_t stream);
 
 // Whether the window's bands fit one staged segment of the tile kernel (the
 // bfloat16 MFMA path of launch_llsa_backward outside the persistent kernel's

@@ -1,0 +1,179 @@
+// Pieces shared by the kernels that work 16 rows per wave on
+// v_mfma_f32_16x16x4_f32 (band_f32.hip, band_bwd_sweep.hip): operand fragments,
+// products and output rows of one wave. A wave's 16 own rows (queries, or keys)
+// are the MFMA's N dimension, one per lane column col = lane % 16; g = lane / 16.
+#pragma once
+
+#include "device_common.h"
+
+namespace sa {
+namespace {
+
+__device__ __forceinline__ float lo_bf(uint32_t x) { return __uint_as_float(x << 16); }
+__device__ __forceinline__ float hi_bf(uint32_t x) { return __uint_as_float(x & 0xffff0000u); }
+
+// Row pattern: this lane's D / 4 features of a row, in contraction-step order,
+// as loaded (bfloat16 is widened where a product takes it, so that a load in
+// flight is waited for only there).
+template <typename E, int D>
+struct RowFrag {
+  static constexpr int N = D / 4, NR = N * sizeof(E) / 16, EPC = 16 / sizeof(E);
+  u32x4 r[NR];
+  __device__ __forceinline__ void load(const E* row, int g) {
+#pragma unroll
+    for (int j = 0; j < NR; ++j) r[j] = ld16(row + 4 * EPC * j + EPC * g);
+  }
+  __device__ __forceinline__ float operator[](int n) const {
+    if constexpr (sizeof(E) == 4) return __uint_as_float(r[n >> 2][n & 3]);
+    else return (n & 1) ? hi_bf(r[n >> 3][(n & 7) >> 1]) : lo_bf(r[n >> 3][(n & 7) >> 1]);
+  }
+};
+
+// Features F col .. F col + F - 1 of a row (F = D / 16: 2 or 4).
+template <typename E, int D>
+struct FeatFrag {
+  static constexpr int F = D / 16, NW = F * sizeof(E) / 4;
+  typedef uint32_t words __attribute__((ext_vector_type(NW == 1 ? 2 : NW)));
+  words r;
+  __device__ __forceinline__ void load(const E* row, int col) {
+    if constexpr (NW == 1) r[0] = *reinterpret_cast<const uint32_t*>(row + F * col);
+    else r = *reinterpret_cast<const words*>(row + F * col);
+  }
+  __device__ __forceinline__ float operator[](int f) const {
+    if constexpr (sizeof(E) == 4) return __uint_as_float(r[f]);
+    else return (f & 1) ? hi_bf(r[f >> 1]) : lo_bf(r[f >> 1]);
+  }
+};
+__device__ __forceinline__ void store_feat(float* p, const float* x, int n) {
+  if (n == 4) *reinterpret_cast<f32x4*>(p) = f32x4{x[0], x[1], x[2], x[3]};
+  else *reinterpret_cast<f32x2*>(p) = f32x2{x[0], x[1]};
+}
+__device__ __forceinline__ void store_feat(uint16_t* p, const float* x, int n) {
+  if (n == 4) st8(p, u32x2{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])});
+  else *reinterpret_cast<uint32_t*>(p) = pack_bf16x2(x[0], x[1]);
+}
+
+// A . B over the head dim: 16 rows against the wave's 16 own rows. Two chains,
+// so that a product does not wait for the one before it.
+template <typename E, int D>
+__device__ __forceinline__ f32x4 row_product(const RowFrag<E, D>& a, const RowFrag<E, D>& b) {
+  f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+  for (int n = 0; n < RowFrag<E, D>::N; n += 2) {
+    s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[n], b[n], s0, 0, 0, 0);
+    s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[n + 1], b[n + 1], s1, 0, 0, 0);
+  }
+  return s0 + s1;
+}
+
+// acc[f] += X^T W over 16 frames: x[i] this lane's features of frame 4g + i,
+// w[i] the weights of that frame.
+template <typename E, int D>
+__device__ __forceinline__ void col_product(const FeatFrag<E, D>* x, const float* w, f32x4* acc) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int f = 0; f < D / 16; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i][f], w[i], acc[f], 0, 0, 0);
+}
+
+template <int F>
+__device__ __forceinline__ bool all_finite(const f32x4* acc) {
+  float z = 0.f;
+#pragma unroll
+  for (int f = 0; f < F; ++f)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) z = __builtin_fmaf(acc[f][r], 0.f, z);  // NaN for an infinity or NaN
+  return z == 0.f;
+}
+
+// Stores row col's features, held as acc[f][r] = feature F (4g + r) + f,
+// times mul (zero rows when !valid). The lanes of a row first trade values
+// (the swaps exchange a lane bit with a register index), so that every store
+// instruction writes 64 contiguous bytes (32 of bfloat16) of 16 rows.
+template <int D, typename E>
+__device__ __forceinline__ void store_own_row(E* row, const f32x4* acc, float mul, bool valid, bool write, int g) {
+  constexpr int F = D / 16;
+  float x[4][F];
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int f = 0; f < F; ++f) x[r][f] = valid ? acc[f][r] * mul : 0.f;
+  auto swap32 = [](float& p, float& q) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+    p = __uint_as_float(r[0]);
+    q = __uint_as_float(r[1]);
+  };
+  auto swap16 = [](float& p, float& q) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+    p = __uint_as_float(r[0]);
+    q = __uint_as_float(r[1]);
+  };
+  if constexpr (D == 64) {
+    // 4 x 4 transpose of the groups and the register rows: register row r then
+    // holds features 16 r + 4 g ..
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+      swap32(x[0][f], x[2][f]);
+      swap32(x[1][f], x[3][f]);
+      swap16(x[0][f], x[1][f]);
+      swap16(x[2][f], x[3][f]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (write) store_feat(row + 16 * r + 4 * g, x[r], 4);
+  } else {
+    // features 8g + 2r + f: four of them (r = 0, 1 and r = 2, 3) make a piece;
+    // after exchanging the upper lane bit with the piece index, piece n of lane
+    // (b5, b4) is features 16 n + 8 b4 + 4 b5 ..
+    float p[2][4] = {{x[0][0], x[0][1], x[1][0], x[1][1]}, {x[2][0], x[2][1], x[3][0], x[3][1]}};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) swap32(p[0][j], p[1][j]);
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+      if (write) store_feat(row + 16 * n + 8 * (g & 1) + 4 * (g >> 1), p[n], 4);
+  }
+}
+
+// The frames one of a wave's columns sees, as a start and a width: frame x is
+// inside iff unsigned(x - start) <= width; an empty range never matches.
+struct Span {
+  int start;
+  unsigned width;
+  __device__ __forceinline__ Span(bool valid, int lo, int hi) {
+    const bool any = valid && hi >= lo;
+    start = any ? lo : 1 << 30;
+    width = any ? static_cast<unsigned>(hi - lo) : 0u;
+  }
+  __device__ __forceinline__ bool has(int x) const { return static_cast<unsigned>(x - start) <= width; }
+};
+
+// Element offsets of a lane's rows in the block of 16 frames that starts at
+// frame fb, frames past `last` replaced by it (their weights are zero): row col
+// (row pattern) and frame 4g + i (transposed rows). The products with the frame
+// stride are taken once; a block adds its uniform start.
+template <int D>
+struct BlockRows {
+  int fs;
+  unsigned rc, rt;  // offsets of row col and of row 4g
+  __device__ __forceinline__ BlockRows(int fs_, int col, int g)
+      : fs(fs_), rc(static_cast<unsigned>(col * fs_)), rt(static_cast<unsigned>(4 * g * fs_)) {}
+  __device__ __forceinline__ size_t at(int fb, unsigned off, int last) const {
+    const int start = min(fb, last);
+    const unsigned most = static_cast<unsigned>(min(last - start, 15) * fs);
+    return static_cast<size_t>(start) * fs + min(off, most);
+  }
+  __device__ __forceinline__ size_t row(int fb, int last) const { return at(fb, rc, last); }
+  __device__ __forceinline__ size_t frame(int fb, int i, int last) const {
+    return at(fb, rt + static_cast<unsigned>(i * fs), last);
+  }
+};
+
+// Zeros rows r0 .. r1 - 1 of a slice (one wave).
+template <int D, typename E>
+__device__ __forceinline__ void zero_rows(E* dst, int fs, int r0, int r1, int lane) {
+  constexpr int CPR = D * sizeof(E) / 16, EPC = 16 / sizeof(E);
+  for (int e = lane; e < (r1 - r0) * CPR; e += 64) st16(dst + (r0 + e / CPR) * fs + EPC * (e % CPR), kZero16);
+}
+
+}  // namespace
+}  // namespace sa

@@ -1,5 +1,6 @@
-"""The float32-arithmetic matrix-core kernels (16 rows per wave, blocks of 16
-frames from the window's first row) at the sizes where they can go wrong:
+"""The matrix-core kernels that take any window (float32: 16 rows per wave,
+blocks of 16 frames from the window's first row; bfloat16 backward: chunks of
+64 or 128 rows swept in blocks of 32) at the sizes where they can go wrong:
 windows around one and two blocks, last rows of a wave and a tile, more
 sequences than compute units, against the fp64 oracle; and infinities and NaN,
 which must reach exactly the rows whose window holds them.
@@ -127,6 +128,34 @@ def test_llsa_backward_float32_arithmetic(oracle_mod, dtype, B, T, H, d, Lb, La,
         assert_slices_close(f64(g), r, dtype, L, n, zero_atol=zero, row_scale=dtype == "bf16")
 
 
+# bfloat16 SA windows wider than the staged kernels take (Lb + La > 80 at d = 64,
+# > 208 at d = 32), from the oracle's rounded output: the smallest such window,
+# chunks with one row more, tiles and sequences shorter than a chunk, more
+# sequences than the staged kernels' 64
+@pytest.mark.parametrize("B,T,H,d,Lb,La,lengths", [
+    (2, 129, 2, 64, 73, 8, (64, 129)),
+    (1, 193, 1, 64, 0, 128, "full"),
+    (2, 321, 1, 32, 200, 9, (130, 321)),
+    (1, 257, 2, 64, 191, 0, "full"),
+    (3, 60, 1, 64, 481, 8, (1, 60)),
+    (67, 70, 1, 64, 90, 3, (0, 70)),
+])
+def test_sa_backward_bfloat16_wide(oracle_mod, B, T, H, d, Lb, La, lengths):
+    print("bf16 wide backward B=%d T=%d H=%d d=%d Lb=%d La=%d" % (B, T, H, d, Lb, La), flush=True)
+    x = sa_inputs(B, T, H, d, 67, scale="unit", lengths=lengths, pad_value=float("nan"))
+    names = ("q", "k", "v", "dout")
+    q, k, v, do = (to_gpu(x[n], "bf16") for n in names)
+    ln, L = x["lengths"].cuda(), x["lengths"].numpy()
+    clean = [np.nan_to_num(f64(x[n])) for n in names]
+    y, lse = oracle_mod.sa_forward(*clean[:3], Lb, La, L)
+    out = torch.from_numpy(y).to(q.dtype).cuda()
+    got = bd.sa_backward(q, k, v, out, torch.from_numpy(lse).float().cuda(), do, Lb, La, ln)
+    ref = oracle_mod.sa_backward(*clean, Lb, La, L, y=f64(out))
+    zero = 1e-5 * float(np.max(np.abs(ref[2])))
+    for n, g, r in zip(("dq", "dk", "dv"), got, ref):
+        assert_slices_close(f64(g), r, "bf16", L, n, zero_atol=zero, row_scale=True)
+
+
 @pytest.mark.parametrize("where", ["q", "k", "v", "dout"])
 def test_backward_nonfinite_frames_stay_in_their_windows(where):
     B, T, H, d, Lb, La, at = 1, 90, 2, 64, 7, 3, 41
@@ -146,3 +175,32 @@ def test_backward_nonfinite_frames_stay_in_their_windows(where):
         assert torch.equal(a[0, :, 1], c[0, :, 1]), n
         torch.testing.assert_close(a[0, ~r, 0], c[0, ~r, 0], rtol=1e-5, atol=1e-5, msg=n)
     assert not torch.isfinite(got[0][0, reads[0], 0]).all()
+
+
+@pytest.mark.parametrize("where", ["q", "k", "v", "dout"])
+def test_wide_llsa_backward_nonfinite_frames_stay_in_their_windows(where):
+    B, T, H, d, Lb, La, at = 1, 300, 1, 64, 100, 5, 151
+    x = llsa_inputs(B, T, H, d, 68, scale="unit", with_dout=True)
+    g = {n: to_gpu(x[n], "bf16") for n in ("q", "k", "v", "dout")}
+    out, lse = bd.llsa_forward(g["q"], g["k"], g["v"], Lb, La)
+
+    def run():
+        return [t.float().cpu()[:, 0, :, 0] for t in
+                bd.llsa_backward(g["q"], g["k"], g["v"], out, lse, g["dout"], Lb, La)]
+
+    clean = run()
+    g[where][1, 0, at, 0, 5] = float("inf")  # branch L, or the look-ahead output
+    got = run()
+    t = torch.arange(T)
+    none = torch.zeros(T, dtype=torch.bool)
+    if where in ("k", "v"):  # queries of both outputs that read frame `at` from branch L
+        hit_q = [(t - La - Lb <= at) & (at <= t - La), (t - Lb <= at) & (at <= t)]
+        hit_k = [none, t == at]
+    else:  # keys that the look-ahead query of frame `at` reads from each branch
+        hit_q = [none, t == at]
+        hit_k = [(at + 1 <= t) & (t <= at + La), (at - Lb <= t) & (t <= at)]
+    for n, a, c, hit in zip(("dq", "dk", "dv"), got, clean, (hit_q, hit_k, hit_k)):
+        for br in (0, 1):
+            torch.testing.assert_close(a[br, ~hit[br]], c[br, ~hit[br]], rtol=2 ** -7, atol=1e-4,
+                                       msg="%s branch %d" % (n, br))
+    assert not torch.isfinite(got[0][1, hit_q[1]]).all()
