@@ -11,22 +11,17 @@
 // recomputed from the log-sum-exp the forward stored, so nothing of size
 // T x window is ever kept.
 //
-// bfloat16 path (MFMA): one launch, two workgroup roles per 64-frame tile of a
-// (sequence, head). The key role owns 64 keys and sweeps the queries that see
+// Here: bfloat16 windows whose bands fit LDS. Two roles per 64-frame tile of a
+// (sequence, head): the key role owns 64 keys and sweeps the queries that see
 // them, [f0 - La, f0 + 63 + Lb], accumulating dk and dv in registers; the query
 // role owns 64 queries and sweeps their keys, [f0 - Lb, f0 + 63 + La],
 // accumulating dq. Every gradient row is produced by exactly one workgroup, so
-// there are no atomics and no workspace, and the result is deterministic. The
-// two roles of a tile get adjacent logical ids and the ids are laid out
-// contiguously per XCD, so the second read of a tile's q, k, v, out and dout
-// usually hits that XCD's L2. The swept operands are staged row-major through
-// LDS in 64-frame chunks (the next chunk's loads in flight while the current
-// one is computed); the products that contract over frames read them with the
-// transposing LDS read. Each wave keeps its own 16 rows in registers as the
-// MFMA's N operand, so every lane owns one key (key role) or one query (query
-// role) and the softmax statistics it needs are per lane.
+// there are no atomics and no workspace, and the result is deterministic. Each
+// wave keeps its own 16 rows in registers as the MFMA's N operand, so every lane
+// owns one key (key role) or one query (query role) and the softmax statistics
+// it needs are per lane.
 //
-// float tensors, and the LLSA windows no kernel here takes: band_f32.hip.
+// Wider windows: band_bwd_sweep.hip; float tensors: band_f32.hip.
 #include <type_traits>
 
 #include "device_common.h"
@@ -39,16 +34,10 @@ constexpr int kThreads = 256;
 
 constexpr int kC = 64;    // frames per tile
 constexpr int kSub = 32;  // frames per sub-block: the contraction length of one MFMA
-// Frames of the swept band staged in LDS at once (two tensors of SEG rows each).
-// With 4 workgroups per CU this keeps every band of the Lb = 64, La = 8 case in
-// one segment; wider bands are swept in several segments.
+// Frames of a band staged in LDS at once: every band of the Lb = 64, La = 8 case.
 template <int D>
 struct Seg {
   static constexpr int kRows = 144 * 64 / D;
-  static constexpr int kStat = (kRows + kSub - 1) / kSub * kSub;  // rows of D_n and lse
-  // A sweep that does not fit one segment advances by whole sub-blocks; the
-  // rows a segment holds past kStep are processed again by the next one.
-  static constexpr int kStep = kRows / kSub * kSub;
 };
 
 struct BwdDev {
@@ -62,14 +51,6 @@ struct BwdDev {
   float log2_scale;  // log2 of the score scale
 };
 
-__device__ __forceinline__ float dot8_bf16(u32x4 x, u32x4 y) {
-  float d = 0.f;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    d += bf2f(x[j] & 0xffffu) * bf2f(y[j] & 0xffffu) + bf2f(x[j] >> 16) * bf2f(y[j] >> 16);
-  return d;
-}
-
 template <int D, int NT = kThreads>
 __device__ __forceinline__ void zero_rows(uint16_t* x, uint16_t* y, int b, int h, int T, int H,
                                           int r_begin, int r_end, int tid) {
@@ -79,247 +60,6 @@ __device__ __forceinline__ void zero_rows(uint16_t* x, uint16_t* y, int b, int h
     const size_t off = row_index(b, r_begin + r, h, T, H, D) + 8 * c;
     st16(x + off, kZero16);
     if (y) st16(y + off, kZero16);
-  }
-}
-
-template <int D>
-__device__ __forceinline__ void store_rows4(uint16_t* dst, int off, const f32x4* acc, float mul,
-                                            bool valid, int g) {
-#pragma unroll
-  for (int i = 0; i < D / 16; ++i) {
-    u32x2 pk;
-    pk[0] = valid ? pack_bf16x2(acc[i][0] * mul, acc[i][1] * mul) : 0u;
-    pk[1] = valid ? pack_bf16x2(acc[i][2] * mul, acc[i][3] * mul) : 0u;
-    st8(dst + (off + 16 * i + 4 * g), pk);
-  }
-}
-
-template <int D>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void sa_bwd_bf16_kernel(BwdDev a) {
-  constexpr int SEG = Seg<D>::kRows, NST = Seg<D>::kStat, STEP = Seg<D>::kStep;
-  constexpr int NS = D / 32, NB = D / 16, CPR = D / 8;
-  constexpr int NDI = (NST * CPR + kThreads - 1) / kThreads;  // D_n pieces per thread
-  __shared__ __attribute__((aligned(16))) uint16_t rm0[SEG * D];  // key role: q    | query role: k
-  __shared__ __attribute__((aligned(16))) uint16_t rm1[SEG * D];  // key role: dout | query role: v
-  __shared__ __attribute__((aligned(16))) float s_dn[NST];
-  __shared__ __attribute__((aligned(16))) float s_lse2[NST];
-
-  // items of a slice: the key and query roles of tile 0, of tile 1, ...; the
-  // second role of a tile finds the tile's rows in the XCD's L2
-  int bh, item;
-  if (!xcd_slice_item(blockIdx.x, a.B * a.H, 2 * a.ntiles, bh, item)) return;
-  const bool key_role = (item & 1) == 0;
-  const int tile = item >> 1;
-  const int h = bh % a.H;
-  const int b = bh / a.H;
-  const int T = a.T, H = a.H, Lb = a.Lb, La = a.La;
-  const int len = clamp_len_uniform(a.lengths, b, T);
-  const int f0 = tile * kC;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int col = lane & 15, g = lane >> 4;
-
-  if (f0 >= len) {  // padding tile
-    if (key_role)
-      zero_rows<D>(a.dk, a.dv, b, h, T, H, f0, min(f0 + kC, T), tid);
-    else
-      zero_rows<D>(a.dq, nullptr, b, h, T, H, f0, min(f0 + kC, T), tid);
-    return;
-  }
-  const int r0 = f0 + 16 * w;
-  const int me = r0 + col;  // this lane's key (key role) or query (query role)
-  const bool valid = me < len;
-  const int fmax = min(f0 + kC, len) - 1;
-  const int wmax = min(r0 + 15, len - 1);
-  // Uniform pointers to frame 0 of the (sequence, head) slice; within a slice
-  // every offset fits in int (T * H * d < 2^31 is checked by the caller).
-  const size_t slice = row_index(b, 0, h, T, H, D);
-  const int fs = H * D;  // elements from one frame to the next
-  const uint16_t *q = a.q + slice, *k = a.k + slice, *v = a.v + slice;
-  const uint16_t *o = a.o + slice, *dout = a.dout + slice;
-  const float* lse_bh = a.lse + (static_cast<size_t>(b) * H + h) * T;
-  const int my_off = me * fs;
-  // own-row reads come from a valid frame (lanes past the end read the last one
-  // and discard it), so that the loads need no branch
-  const int rd_off = min(me, len - 1) * fs;
-
-  if (key_role) {
-    // sweep the queries that see the tile's keys: [f0 - La, fmax + Lb]
-    const int lo = max(0, f0 - La), hi = min(len - 1, fmax + Lb);
-    int s0 = lo, nv = min(SEG, hi - lo + 1);
-    seg_issue<D>(rm0, q + s0 * fs, fs, nv, w, lane);
-    seg_issue<D>(rm1, dout + s0 * fs, fs, nv, w, lane);
-    // own key and value rows, the N operand of every product (lanes past the
-    // end of the sequence hold the last frame's and are masked out)
-    bf16x8 kf[NS], vf[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      kf[s] = __builtin_bit_cast(bf16x8, ld16(k + (rd_off + 32 * s + 8 * g)));
-      vf[s] = __builtin_bit_cast(bf16x8, ld16(v + (rd_off + 32 * s + 8 * g)));
-    }
-    f32x4 adv[NB], adk[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) adv[i] = adk[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int wlo = max(0, r0 - La);
-    const int whi = (wmax < r0) ? -1 : min(len - 1, wmax + Lb);
-    const int mylo = max(0, me - La), myhi = min(len - 1, me + Lb);  // queries that see me
-    // lanes past the end of the sequence see no query
-    const unsigned span = valid ? static_cast<unsigned>(myhi - mylo) : 0u;
-    const int mylo_v = valid ? mylo : 1 << 30;
-    const SubBlockOffsets<D> so(lane);
-    for (;;) {
-      const bool last = hi - s0 + 1 <= SEG;  // nv rows, all of them swept here
-      const int nsw = last ? nv : STEP;      // rows whose sub-blocks are swept here
-      // out rows and lse of the segment's queries, for D_n = dout_n . out_n;
-      // unconditional loads from a clamped row, so that no lane overwrites a
-      // register with a load still in flight
-      u32x4 ov[NDI];
-      float lv[NDI];
-#pragma unroll
-      for (int i = 0; i < NDI; ++i) {
-        const int e = tid + i * kThreads, r = e / CPR, pc = e % CPR, rc = min(r, nv - 1);
-        ov[i] = ld16(o + ((s0 + rc) * fs + 8 * pc));
-        lv[i] = lse_bh[s0 + rc];
-      }
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < NDI; ++i) {
-        const int e = tid + i * kThreads, r = e / CPR, pc = e % CPR;
-        float dn = r < nv ? dot8_bf16(ld16(rm1 + seg_off<D>(r, 8 * pc)), ov[i]) : 0.f;
-        const float l2 = r < nv ? lv[i] * kLog2e : 0.f;
-#pragma unroll
-        for (int m = 1; m < CPR; m <<= 1) dn += __shfl_xor(dn, m);  // the row's pieces are adjacent lanes
-        if (pc == 0 && r < NST) {
-          s_dn[r] = dn;
-          s_lse2[r] = l2;
-        }
-      }
-      __syncthreads();
-      const int rl = nv - 1;
-      for (int sb = 0; sb < nsw && wlo <= whi; sb += kSub) {
-        const int qb = s0 + sb;
-        if (qb > whi || qb + kSub - 1 < wlo) continue;
-        int oa, oc, ota, otc;
-        so.at(sb, rl, oa, oc, ota, otc);
-        f32x4 sc0 = {0.f, 0.f, 0.f, 0.f}, sc1 = sc0, dp0 = sc0, dp1 = sc0;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          sc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_row8(rm0 + (oa ^ (32 * s))), kf[s], sc0, 0, 0, 0);
-          sc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_row8(rm0 + (oc ^ (32 * s))), kf[s], sc1, 0, 0, 0);
-          dp0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_row8(rm1 + (oa ^ (32 * s))), vf[s], dp0, 0, 0, 0);
-          dp1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_row8(rm1 + (oc ^ (32 * s))), vf[s], dp1, 0, 0, 0);
-        }
-        // statistics of the 8 queries this lane holds: rows sb + 8g .. +7
-        const f32x4 l0 = *reinterpret_cast<const f32x4*>(s_lse2 + sb + 8 * g);
-        const f32x4 l1 = *reinterpret_cast<const f32x4*>(s_lse2 + sb + 8 * g + 4);
-        const f32x4 n0 = *reinterpret_cast<const f32x4*>(s_dn + sb + 8 * g);
-        const f32x4 n1 = *reinterpret_cast<const f32x4*>(s_dn + sb + 8 * g + 4);
-        const int d0 = qb + 8 * g - mylo_v;  // query qb + 8g + j sees me iff 0 <= d0 + j <= span
-        bf16x8 pf, dsf;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float sv = j < 4 ? sc0[j] : sc1[j - 4];
-          const float dp = j < 4 ? dp0[j] : dp1[j - 4];
-          const float l2 = j < 4 ? l0[j] : l1[j - 4];
-          const float dnq = j < 4 ? n0[j] : n1[j - 4];
-          const bool ok = static_cast<unsigned>(d0 + j) <= span;
-          const float pw = fast_exp2(sv * a.scale_log2 - l2);
-          pf[j] = static_cast<__bf16>(ok ? pw : 0.f);
-          dsf[j] = static_cast<__bf16>(ok ? pw * (dp - dnq) : 0.f);
-        }
-        // dv^T += dout^T P and dk^T += q^T dS, contracting over the 32 queries
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-          adv[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_tr8(rm1, ota ^ (16 * i), otc ^ (16 * i)), pf, adv[i], 0, 0, 0);
-          adk[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_tr8(rm0, ota ^ (16 * i), otc ^ (16 * i)), dsf, adk[i], 0, 0, 0);
-        }
-      }
-      if (last) break;
-      s0 += STEP;
-      nv = min(SEG, hi - s0 + 1);
-      __syncthreads();  // every wave is done with this segment
-      seg_issue<D>(rm0, q + s0 * fs, fs, nv, w, lane);
-      seg_issue<D>(rm1, dout + s0 * fs, fs, nv, w, lane);
-    }
-    if (me < T) {
-      store_rows4<D>(a.dv + slice, my_off, adv, 1.f, valid, g);
-      store_rows4<D>(a.dk + slice, my_off, adk, a.scale, valid, g);
-    }
-  } else {
-    // sweep the keys of the tile's queries: [f0 - Lb, fmax + La]
-    const int lo = max(0, f0 - Lb), hi = min(len - 1, fmax + La);
-    int s0 = lo, nv = min(SEG, hi - lo + 1);
-    seg_issue<D>(rm0, k + s0 * fs, fs, nv, w, lane);
-    seg_issue<D>(rm1, v + s0 * fs, fs, nv, w, lane);
-    // own query and output-gradient rows, the N operand of every product, and
-    // D = dout . out of the own query (lanes past the end of the sequence hold
-    // the last frame's and are masked out)
-    bf16x8 qf[NS], df[NS];
-    float dn = 0.f;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int off = rd_off + 32 * s + 8 * g;
-      const u32x4 dr = ld16(dout + off);
-      qf[s] = __builtin_bit_cast(bf16x8, ld16(q + off));
-      df[s] = __builtin_bit_cast(bf16x8, dr);
-      dn += dot8_bf16(dr, ld16(o + off));
-    }
-    dn += __shfl_xor(dn, 16);
-    dn += __shfl_xor(dn, 32);
-    const float lse2 = lse_bh[min(me, len - 1)] * kLog2e;
-    f32x4 aq[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) aq[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int wlo = max(0, r0 - Lb);
-    const int whi = (wmax < r0) ? -1 : min(len - 1, wmax + La);
-    const int mylo = max(0, me - Lb), myhi = min(len - 1, me + La);  // my window
-    // lanes past the end of the sequence have an empty window
-    const unsigned span = valid ? static_cast<unsigned>(myhi - mylo) : 0u;
-    const int mylo_v = valid ? mylo : 1 << 30;
-    const SubBlockOffsets<D> so(lane);
-    for (;;) {
-      const bool last = hi - s0 + 1 <= SEG;  // nv rows, all of them swept here
-      const int nsw = last ? nv : STEP;      // rows whose sub-blocks are swept here
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      const int rl = nv - 1;
-      for (int sb = 0; sb < nsw && wlo <= whi; sb += kSub) {
-        const int kb = s0 + sb;
-        if (kb > whi || kb + kSub - 1 < wlo) continue;
-        int oa, oc, ota, otc;
-        so.at(sb, rl, oa, oc, ota, otc);
-        f32x4 sc0 = {0.f, 0.f, 0.f, 0.f}, sc1 = sc0, dp0 = sc0, dp1 = sc0;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          sc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_row8(rm0 + (oa ^ (32 * s))), qf[s], sc0, 0, 0, 0);
-          sc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_row8(rm0 + (oc ^ (32 * s))), qf[s], sc1, 0, 0, 0);
-          dp0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_row8(rm1 + (oa ^ (32 * s))), df[s], dp0, 0, 0, 0);
-          dp1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_row8(rm1 + (oc ^ (32 * s))), df[s], dp1, 0, 0, 0);
-        }
-        const int d0 = kb + 8 * g - mylo_v;  // key kb + 8g + j is in my window iff 0 <= d0 + j <= span
-        bf16x8 dsf;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float sv = j < 4 ? sc0[j] : sc1[j - 4];
-          const float dp = j < 4 ? dp0[j] : dp1[j - 4];
-          const bool ok = static_cast<unsigned>(d0 + j) <= span;
-          const float pw = fast_exp2(sv * a.scale_log2 - lse2);
-          dsf[j] = static_cast<__bf16>(ok ? pw * (dp - dn) : 0.f);
-        }
-        // dq^T += k^T dS^T, contracting over the 32 keys
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-          aq[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_tr8(rm0, ota ^ (16 * i), otc ^ (16 * i)), dsf, aq[i], 0, 0, 0);
-      }
-      if (last) break;
-      s0 += STEP;
-      nv = min(SEG, hi - s0 + 1);
-      __syncthreads();  // every wave is done with this segment
-      seg_issue<D>(rm0, k + s0 * fs, fs, nv, w, lane);
-      seg_issue<D>(rm1, v + s0 * fs, fs, nv, w, lane);
-    }
-    if (me < T) store_rows4<D>(a.dq + slice, my_off, aq, a.scale, valid, g);
   }
 }
 
@@ -1033,11 +773,12 @@ hipError_t launch_mfma(const SaBackwardArgs& a, hipStream_t stream) {
     else
       hipLaunchKernelGGL(sa_bwd_tile_kernel<32>, dim3(grid), dim3(2 * kThreads), 0, stream, d);
   } else {
-    const int grid = xcd_slice_grid(a.B * a.H, 2 * d.ntiles);
-    if (a.d == 64)
-      hipLaunchKernelGGL(sa_bwd_bf16_kernel<64>, dim3(grid), dim3(kThreads), 0, stream, d);
-    else
-      hipLaunchKernelGGL(sa_bwd_bf16_kernel<32>, dim3(grid), dim3(kThreads), 0, stream, d);
+    // bands wider than one segment stream through LDS in chunks whose loads
+    // overlap the products: 48 us where sweeping them in staged segments took 58
+    // us (B = 4, T = 1000, H = 16, d = 64, a window of 490), 24.4 against 26.4 us
+    // (H = 12, a window of 139) and 10.1 against 11.5 us (B = 1, T = 200, H = 8, a
+    // window of 365)
+    return launch_sa_backward_sweep(a, stream);
   }
   return hipGetLastError();
 }
