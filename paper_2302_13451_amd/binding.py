@@ -127,24 +127,43 @@ def _check(rc: int):
         raise SAError(rc, load_library().sa_last_error().decode(errors="replace"))
 
 
-def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.bfloat16:
+def _dtype_code(dtype: torch.dtype) -> int:
+    if dtype is torch.bfloat16:
         return SA_BF16
-    if t.dtype == torch.float32:
+    if dtype is torch.float32:
         return SA_F32
-    raise SAError(SA_ERR_UNSUPPORTED, "tensors must be bfloat16 or float32, got %s" % t.dtype)
+    raise SAError(SA_ERR_UNSUPPORTED, "tensors must be bfloat16 or float32, got %s" % dtype)
+
+
+# Per-call host time matters: a streaming step or a short utterance runs for 4 to
+# 8 us on the GPU. Pointers and the stream go to ctypes as plain integers (the
+# argument types are void pointers), and a tensor that passes its checks costs
+# one expression: a call of sa_forward takes 7.3 us of host time (10.6 with
+# pointer objects, a stream object and a check per property), sa_stream_step 6.8
+# us (9.4).
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device, stream) -> ctypes.c_void_p:
-    s = stream if stream is not None else torch.cuda.current_stream(device)
-    return ctypes.c_void_p(s.cuda_stream)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
-def _require(t: torch.Tensor, name: str, shape, dtype, device):
+def _stream(index: int, stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(index)
+    return torch.cuda.current_stream(index).cuda_stream
+
+
+def _require(t: torch.Tensor, name: str, shape, dtype, index: int):
+    """Checks a tensor against a shape, a dtype and the GPU ``index`` (-1: the
+    call's tensors are not on a GPU, which is an error for each of them)."""
+    if (t.get_device() == index >= 0 and t.dtype is dtype and t.shape == shape
+            and t.is_contiguous()):
+        return
     if not t.is_cuda:
         raise SAError(SA_ERR_INVALID, "%s must be a GPU tensor" % name)
     if tuple(t.shape) != tuple(shape):
@@ -152,16 +171,25 @@ def _require(t: torch.Tensor, name: str, shape, dtype, device):
                                                                          tuple(shape)))
     if t.dtype != dtype:
         raise SAError(SA_ERR_INVALID, "%s has dtype %s, expected %s" % (name, t.dtype, dtype))
-    if t.device != device:
-        raise SAError(SA_ERR_INVALID, "%s is on %s, expected %s" % (name, t.device, device))
+    if t.get_device() != index:
+        raise SAError(SA_ERR_INVALID, "%s is on %s, expected %s" % (
+            name, t.device, torch.device("cuda", index) if index >= 0 else "cpu"))
     if not t.is_contiguous():
         raise SAError(SA_ERR_INVALID, "%s must be contiguous" % name)
 
 
-def _lengths(lengths, n, device):
+def _out(t: Optional[torch.Tensor], name: str, like: torch.Tensor) -> torch.Tensor:
+    """The caller's output tensor, checked against ``like``, or a new one."""
+    if t is None:
+        return torch.empty_like(like)
+    _require(t, name, like.shape, like.dtype, like.get_device())
+    return t
+
+
+def _lengths(lengths, n, index: int):
     if lengths is None:
         return None
-    _require(lengths, "lengths", (n,), torch.int32, device)
+    _require(lengths, "lengths", (n,), torch.int32, index)
     return lengths
 
 
@@ -170,19 +198,19 @@ def sa_forward(q, k, v, Lb: int, La: int, lengths=None, out=None, lse=None, *,
     """SA forward. q, k, v: [B][T][H][d] (bf16 or f32); lengths: int32 [B] or
     None. Returns (out, lse) with lse float32 [B][H][T] (None if not wanted)."""
     B, T, H, d = q.shape
+    dt, dev = q.dtype, q.get_device()
     for n, t in (("q", q), ("k", k), ("v", v)):
-        _require(t, n, (B, T, H, d), q.dtype, q.device)
-    code = _dtype_code(q)
-    out = torch.empty_like(q) if out is None else out
-    _require(out, "out", (B, T, H, d), q.dtype, q.device)
-    if lse is None and want_lse:
-        lse = torch.empty((B, H, T), dtype=torch.float32, device=q.device)
+        _require(t, n, (B, T, H, d), dt, dev)
+    code = _dtype_code(dt)
+    out = _out(out, "out", q)
     if lse is not None:
-        _require(lse, "lse", (B, H, T), torch.float32, q.device)
-    lengths = _lengths(lengths, B, q.device)
+        _require(lse, "lse", (B, H, T), torch.float32, dev)
+    elif want_lse:
+        lse = torch.empty((B, H, T), dtype=torch.float32, device=q.device)
+    lengths = _lengths(lengths, B, dev)
     _check(load_library().sa_forward(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), B, T, H, d,
                                      int(Lb), int(La), _ptr(lengths), code,
-                                     _stream(q.device, stream)))
+                                     _stream(dev, stream)))
     return out, lse
 
 
@@ -190,20 +218,17 @@ def sa_backward(q, k, v, out, lse, dout, Lb: int, La: int, lengths=None, dq=None
                 dv=None, *, stream=None):
     """SA backward. Returns (dq, dk, dv), each [B][T][H][d]."""
     B, T, H, d = q.shape
+    dt, dev = q.dtype, q.get_device()
     for n, t in (("q", q), ("k", k), ("v", v), ("out", out), ("dout", dout)):
-        _require(t, n, (B, T, H, d), q.dtype, q.device)
-    _require(lse, "lse", (B, H, T), torch.float32, q.device)
-    code = _dtype_code(q)
-    dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.empty_like(q) if dk is None else dk
-    dv = torch.empty_like(q) if dv is None else dv
-    for n, t in (("dq", dq), ("dk", dk), ("dv", dv)):
-        _require(t, n, (B, T, H, d), q.dtype, q.device)
-    lengths = _lengths(lengths, B, q.device)
+        _require(t, n, (B, T, H, d), dt, dev)
+    _require(lse, "lse", (B, H, T), torch.float32, dev)
+    code = _dtype_code(dt)
+    dq, dk, dv = _out(dq, "dq", q), _out(dk, "dk", q), _out(dv, "dv", q)
+    lengths = _lengths(lengths, B, dev)
     _check(load_library().sa_backward(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse),
                                       _ptr(dout), _ptr(dq), _ptr(dk), _ptr(dv), B, T, H, d,
                                       int(Lb), int(La), _ptr(lengths), code,
-                                      _stream(q.device, stream)))
+                                      _stream(dev, stream)))
     return dq, dk, dv
 
 
@@ -213,21 +238,21 @@ def llsa_forward(q, k, v, Lb: int, La: int, lengths=None, out=None, lse=None, *,
     branch, 1 = look-ahead branch. Returns (out [2][B][T][H][d], lse
     [2][B][H][T] or None)."""
     two, B, T, H, d = q.shape
+    dt, dev = q.dtype, q.get_device()
     if two != 2:
         raise SAError(SA_ERR_INVALID, "LLSA tensors must have a leading dimension of 2")
     for n, t in (("q", q), ("k", k), ("v", v)):
-        _require(t, n, (2, B, T, H, d), q.dtype, q.device)
-    code = _dtype_code(q)
-    out = torch.empty_like(q) if out is None else out
-    _require(out, "out", (2, B, T, H, d), q.dtype, q.device)
-    if lse is None and want_lse:
-        lse = torch.empty((2, B, H, T), dtype=torch.float32, device=q.device)
+        _require(t, n, (2, B, T, H, d), dt, dev)
+    code = _dtype_code(dt)
+    out = _out(out, "out", q)
     if lse is not None:
-        _require(lse, "lse", (2, B, H, T), torch.float32, q.device)
-    lengths = _lengths(lengths, B, q.device)
+        _require(lse, "lse", (2, B, H, T), torch.float32, dev)
+    elif want_lse:
+        lse = torch.empty((2, B, H, T), dtype=torch.float32, device=q.device)
+    lengths = _lengths(lengths, B, dev)
     _check(load_library().llsa_forward(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), B, T, H,
                                        d, int(Lb), int(La), _ptr(lengths), code,
-                                       _stream(q.device, stream)))
+                                       _stream(dev, stream)))
     return out, lse
 
 
@@ -237,19 +262,21 @@ def llsa_paper_forward(q, k, v, Lb: int, La: int, lengths=None, out=None, lse=No
     channel c computed with its own query. Returns (out [La+1][B][T][H][d],
     lse [La+1][B][H][T])."""
     C, B, T, H, d = q.shape
+    dt, dev = q.dtype, q.get_device()
     if C != La + 1:
         raise SAError(SA_ERR_INVALID, "paper LLSA tensors must have La + 1 = %d channels" % (La + 1))
     for n, t in (("q", q), ("k", k), ("v", v)):
-        _require(t, n, (C, B, T, H, d), q.dtype, q.device)
-    code = _dtype_code(q)
-    out = torch.empty_like(q) if out is None else out
-    _require(out, "out", (C, B, T, H, d), q.dtype, q.device)
-    lse = torch.empty((C, B, H, T), dtype=torch.float32, device=q.device) if lse is None else lse
-    _require(lse, "lse", (C, B, H, T), torch.float32, q.device)
-    lengths = _lengths(lengths, B, q.device)
+        _require(t, n, (C, B, T, H, d), dt, dev)
+    code = _dtype_code(dt)
+    out = _out(out, "out", q)
+    if lse is not None:
+        _require(lse, "lse", (C, B, H, T), torch.float32, dev)
+    else:
+        lse = torch.empty((C, B, H, T), dtype=torch.float32, device=q.device)
+    lengths = _lengths(lengths, B, dev)
     _check(load_library().llsa_paper_forward(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), B,
                                              T, H, d, int(Lb), int(La), _ptr(lengths), code,
-                                             _stream(q.device, stream)))
+                                             _stream(dev, stream)))
     return out, lse
 
 
@@ -258,22 +285,19 @@ def llsa_paper_backward(q, k, v, out, lse, dout, Lb: int, La: int, lengths=None,
     """Backward of llsa_paper_forward. Every tensor is [La+1][B][T][H][d],
     lse [La+1][B][H][T] from the forward. Returns (dq, dk, dv)."""
     C, B, T, H, d = q.shape
+    dt, dev = q.dtype, q.get_device()
     if C != La + 1:
         raise SAError(SA_ERR_INVALID, "paper LLSA tensors must have La + 1 = %d channels" % (La + 1))
     for n, t in (("q", q), ("k", k), ("v", v), ("out", out), ("dout", dout)):
-        _require(t, n, (C, B, T, H, d), q.dtype, q.device)
-    _require(lse, "lse", (C, B, H, T), torch.float32, q.device)
-    code = _dtype_code(q)
-    dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.empty_like(q) if dk is None else dk
-    dv = torch.empty_like(q) if dv is None else dv
-    for n, t in (("dq", dq), ("dk", dk), ("dv", dv)):
-        _require(t, n, (C, B, T, H, d), q.dtype, q.device)
-    lengths = _lengths(lengths, B, q.device)
+        _require(t, n, (C, B, T, H, d), dt, dev)
+    _require(lse, "lse", (C, B, H, T), torch.float32, dev)
+    code = _dtype_code(dt)
+    dq, dk, dv = _out(dq, "dq", q), _out(dk, "dk", q), _out(dv, "dv", q)
+    lengths = _lengths(lengths, B, dev)
     _check(load_library().llsa_paper_backward(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse),
                                               _ptr(dout), _ptr(dq), _ptr(dk), _ptr(dv), B, T, H,
                                               d, int(Lb), int(La), _ptr(lengths), code,
-                                              _stream(q.device, stream)))
+                                              _stream(dev, stream)))
     return dq, dk, dv
 
 
@@ -283,22 +307,19 @@ def llsa_backward(q, k, v, out, lse, dout, Lb: int, La: int, lengths=None, dq=No
     causal branch, 1 = look-ahead branch), lse [2][B][H][T] from
     llsa_forward. Returns (dq, dk, dv)."""
     two, B, T, H, d = q.shape
+    dt, dev = q.dtype, q.get_device()
     if two != 2:
         raise SAError(SA_ERR_INVALID, "LLSA tensors must have a leading dimension of 2")
     for n, t in (("q", q), ("k", k), ("v", v), ("out", out), ("dout", dout)):
-        _require(t, n, (2, B, T, H, d), q.dtype, q.device)
-    _require(lse, "lse", (2, B, H, T), torch.float32, q.device)
-    code = _dtype_code(q)
-    dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.empty_like(q) if dk is None else dk
-    dv = torch.empty_like(q) if dv is None else dv
-    for n, t in (("dq", dq), ("dk", dk), ("dv", dv)):
-        _require(t, n, (2, B, T, H, d), q.dtype, q.device)
-    lengths = _lengths(lengths, B, q.device)
+        _require(t, n, (2, B, T, H, d), dt, dev)
+    _require(lse, "lse", (2, B, H, T), torch.float32, dev)
+    code = _dtype_code(dt)
+    dq, dk, dv = _out(dq, "dq", q), _out(dk, "dk", q), _out(dv, "dv", q)
+    lengths = _lengths(lengths, B, dev)
     _check(load_library().llsa_backward(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse),
                                         _ptr(dout), _ptr(dq), _ptr(dk), _ptr(dv), B, T, H, d,
                                         int(Lb), int(La), _ptr(lengths), code,
-                                        _stream(q.device, stream)))
+                                        _stream(dev, stream)))
     return dq, dk, dv
 
 
@@ -325,12 +346,11 @@ def sa_stream_step(state: StreamState, q, k, v, out=None, *, stream=None):
     nothing. ``state`` is advanced on the device."""
     S, H, d = state.S, state.H, state.d
     dt = state.k_ring.dtype
-    dev = state.k_ring.device
+    dev = state.k_ring.get_device()
     for n, t in (("q", q), ("k", k), ("v", v)):
         _require(t, n, (S, H, d), dt, dev)
-    out = torch.empty_like(q) if out is None else out
-    _require(out, "out", (S, H, d), dt, dev)
-    code = _dtype_code(state.k_ring)
+    out = _out(out, "out", q)
+    code = _dtype_code(dt)
     _check(load_library().sa_stream_step(
         _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(state.q_ring), _ptr(state.k_ring),
         _ptr(state.v_ring), state.R, _ptr(state.step_ctr), _ptr(state.emitted), S, H, d,
@@ -364,14 +384,11 @@ def llsa_stream_step(state: LlsaStreamState, qc, kc, vc, ql, kl, vl, out_c=None,
     of frame u - La; emitted = -1 where nothing was emitted."""
     S, H, d = state.S, state.H, state.d
     dt = state.rings[0].dtype
-    dev = state.rings[0].device
+    dev = state.rings[0].get_device()
     for n, t in (("qc", qc), ("kc", kc), ("vc", vc), ("ql", ql), ("kl", kl), ("vl", vl)):
         _require(t, n, (S, H, d), dt, dev)
-    out_c = torch.empty_like(qc) if out_c is None else out_c
-    out_l = torch.empty_like(qc) if out_l is None else out_l
-    _require(out_c, "out_c", (S, H, d), dt, dev)
-    _require(out_l, "out_l", (S, H, d), dt, dev)
-    code = _dtype_code(state.rings[0])
+    out_c, out_l = _out(out_c, "out_c", qc), _out(out_l, "out_l", qc)
+    code = _dtype_code(dt)
     _check(load_library().llsa_stream_step(
         _ptr(qc), _ptr(kc), _ptr(vc), _ptr(ql), _ptr(kl), _ptr(vl), _ptr(out_c), _ptr(out_l),
         *[_ptr(r) for r in state.rings], state.R, _ptr(state.step_ctr), _ptr(state.emitted_c),
@@ -390,5 +407,5 @@ def copy_reference(src: torch.Tensor, dst: torch.Tensor, mode: int = 0, *, strea
     if dst.numel() * dst.element_size() != n:
         raise SAError(SA_ERR_INVALID, "src and dst differ in size")
     _check(load_library().sa_copy_reference(_ptr(src), _ptr(dst), n, int(mode),
-                                            _stream(src.device, stream)))
+                                            _stream(src.get_device(), stream)))
     return dst
