@@ -13,6 +13,8 @@
 //      lane, so every load is coalesced; the scores stay in registers.
 // The just-arrived frame u is taken from the input rather than from the ring
 // slot written in this same launch, so the kernel never reads its own stores.
+#include <type_traits>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -24,11 +26,20 @@ namespace {
 // waves of the SA and LLSA steps (one head each, more in turn; their state
 // allows three per SIMD)
 constexpr int kMaxWaves = 12;
-// row groups per block of attend_rows: the SA step takes windows of up to 10
-// (80 frames at d = 64 in bfloat16, 160 at d = 32) in one block; the LLSA
-// step, with two queries' scores in registers, blocks of 5
-constexpr int kRowGroups = 10;
-constexpr int kRowGroups2 = 5;
+// Row groups (rows that one load instruction reads: 8 at d = 64 in bfloat16) per
+// block of attend_rows: 3, 5, 7 or 10, the smallest that takes the window in the
+// fewest blocks. A block's rows are all loaded before any arithmetic, so a second
+// block costs another round trip to the rings (LLSA, 64 streams, a window of 73:
+// 10.3 us a step in one block of 10, 11.2 us in two of 5), and a group past the
+// window costs its arithmetic (LLSA, 250 streams, a window of 49: 10.6 us with 7
+// groups, 11.4 us with 10). 10 groups of keys and values and two queries' scores
+// are what 168 registers (three waves per SIMD, 12 heads) hold.
+constexpr int kMaxRowGroups = 10;
+inline int row_groups(int W, int d, size_t elem) {
+  const int rows = 64 * 16 / (d * static_cast<int>(elem)), groups = (W + rows - 1) / rows;
+  const int blocks = (groups + kMaxRowGroups - 1) / kMaxRowGroups, n = (groups + blocks - 1) / blocks;
+  return n <= 3 ? 3 : n <= 5 ? 5 : n <= 7 ? 7 : 10;
+}
 
 template <typename E>
 __device__ __forceinline__ void unpack16(const uint4& x, float* f);
@@ -77,8 +88,7 @@ struct DevStream {
 // (kg, dc) takes 16-byte chunk dc of key and value rows kg, kg + NKG, ..., so
 // each load instruction reads NKG whole rows. The window is taken in blocks of
 // NV row groups (one block for windows up to NV * NKG frames); per block the
-// key (and, with one query, value) chunks are loaded before any arithmetic,
-// the score of row j is summed over the CH lanes of its group and stays in
+// key and value chunks are loaded before any arithmetic, the score of row j is summed over the CH lanes of its group and stays in
 // them, and those lanes weight their value chunks with it: no score goes
 // through LDS. Across blocks the softmax runs online (running maximum, sum and
 // weighted sum rescaled when the maximum grows). qs[n] is query n's row (null
@@ -108,16 +118,14 @@ __device__ __forceinline__ void attend_rows(const E* const* qs, KRow krow, VRow 
     for (int e = 0; e < EPC; ++e) acc[n][e] = 0.f;
   }
   for (int j0 = 0; j0 < W; j0 += NV * NKG) {
-    // key chunks, and with one query the value chunks too, before any
-    // arithmetic (two queries need the registers for their scores: their
-    // value chunks follow the scores)
+    // key and value chunks before any arithmetic
     uint4 kc[NV], vc[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int j = j0 + kg + NKG * i;
       const bool in = j < W;
       kc[i] = in ? chunk(krow(lo + j), dc) : make_uint4(0, 0, 0, 0);
-      if constexpr (NQ == 1) vc[i] = in ? chunk(vrow(lo + j), dc) : make_uint4(0, 0, 0, 0);
+      vc[i] = in ? chunk(vrow(lo + j), dc) : make_uint4(0, 0, 0, 0);
     }
     float z[NQ][NV], bm[NQ];
 #pragma unroll
@@ -135,13 +143,6 @@ __device__ __forceinline__ void attend_rows(const E* const* qs, KRow krow, VRow 
         p = group_sum<CH>(p);  // the row's CH chunks
         z[n][i] = in ? p * scale_log2 : kNegInf;
         bm[n] = fmaxf(bm[n], z[n][i]);
-      }
-    }
-    if constexpr (NQ > 1) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int j = j0 + kg + NKG * i;
-        vc[i] = j < W ? chunk(vrow(lo + j), dc) : make_uint4(0, 0, 0, 0);
       }
     }
 #pragma unroll
@@ -180,7 +181,7 @@ __device__ __forceinline__ void attend_rows(const E* const* qs, KRow krow, VRow 
   }
 }
 
-template <typename E, int D>
+template <typename E, int D, int NV>
 __global__ __launch_bounds__(64 * kMaxWaves) void stream_step_kernel(DevStream a) {
   constexpr int EPC = 16 / sizeof(E);   // elements per 16-byte chunk
   constexpr int CH = D / EPC;           // chunks per row
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stream_step_kernel(DevStream a
     const E* qrow = (La == 0 ? qin : qring + static_cast<size_t>(t % QR) * HD) + ho;
     const E* qs[1] = {qrow};
     E* os[1] = {out + ho};
-    attend_rows<E, D, kRowGroups, 1>(qs, krow, vrow, lo, W, a.scale_log2, os, lane);
+    attend_rows<E, D, NV, 1>(qs, krow, vrow, lo, W, a.scale_log2, os, lane);
   }
   if (threadIdx.x == 0 && a.emitted) a.emitted[s] = emit ? t : -1;
   __syncthreads();  // every wave has read step[s]
@@ -247,7 +248,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stream_step_kernel(DevStream a
 // tau taken from branch L when tau <= t and from branch C otherwise (Eq. 14/15
 // with channels 0 .. La-1 held by C and channel La by L), so the two outputs
 // differ only in their query. Layout and work split as in stream_step_kernel;
-// per head one pass over the window computes both outputs (attend_wave2).
+// per head one pass over the window computes both outputs.
 struct DevLlsaStream {
   const void *qc, *kc, *vc, *ql, *kl, *vl;
   void *out_c, *out_l;
@@ -260,7 +261,7 @@ struct DevLlsaStream {
   float scale_log2;
 };
 
-template <typename E, int D>
+template <typename E, int D, int NV>
 __global__ __launch_bounds__(64 * kMaxWaves) void llsa_stream_step_kernel(DevLlsaStream a) {
   constexpr int EPC = 16 / sizeof(E);
   constexpr int CH = D / EPC;
@@ -324,7 +325,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void llsa_stream_step_kernel(DevLls
     }
     const E* qq[2] = {got_c ? qc + ho : nullptr, got_l ? ql + ho : nullptr};
     E* oo[2] = {out_c + ho, out_l + ho};
-    attend_rows<E, D, kRowGroups2, 2>(qq, krow, vrow, lo, hi - lo + 1, a.scale_log2, oo, lane);
+    attend_rows<E, D, NV, 2>(qq, krow, vrow, lo, hi - lo + 1, a.scale_log2, oo, lane);
   }
   if (threadIdx.x == 0) {
     if (a.emitted_c) a.emitted_c[s] = got_c ? u : -1;
@@ -332,6 +333,25 @@ __global__ __launch_bounds__(64 * kMaxWaves) void llsa_stream_step_kernel(DevLls
   }
   __syncthreads();  // every wave has read step[s]
   if (threadIdx.x == 0) a.step[s] = u + 1;
+}
+
+// Calls f(element, head dim, row groups) with the step's compile-time shape.
+template <typename F>
+void with_step_shape(ElemType et, int d, int W, F f) {
+  auto groups = [&](auto e, auto dim) {
+    switch (row_groups(W, dim, sizeof(e))) {
+      case 3: f(e, dim, std::integral_constant<int, 3>{}); break;
+      case 5: f(e, dim, std::integral_constant<int, 5>{}); break;
+      case 7: f(e, dim, std::integral_constant<int, 7>{}); break;
+      default: f(e, dim, std::integral_constant<int, kMaxRowGroups>{}); break;
+    }
+  };
+  auto dims = [&](auto e) {
+    if (d == 64) groups(e, std::integral_constant<int, 64>{});
+    else groups(e, std::integral_constant<int, 32>{});
+  };
+  if (et == kBF16) dims(uint16_t{});
+  else dims(float{});
 }
 
 }  // namespace
@@ -361,18 +381,9 @@ hipError_t launch_llsa_stream_step(const LlsaStreamStepArgs& a, ElemType et, hip
   d.lengths = a.lengths;
   d.scale_log2 = kLog2e / sqrtf(static_cast<float>(a.d));
   const int nw = a.H < kMaxWaves ? a.H : kMaxWaves;
-  const dim3 grid(a.S), block(64 * nw);
-  if (et == kBF16) {
-    if (a.d == 64)
-      hipLaunchKernelGGL((llsa_stream_step_kernel<uint16_t, 64>), grid, block, 0, stream, d);
-    else
-      hipLaunchKernelGGL((llsa_stream_step_kernel<uint16_t, 32>), grid, block, 0, stream, d);
-  } else {
-    if (a.d == 64)
-      hipLaunchKernelGGL((llsa_stream_step_kernel<float, 64>), grid, block, 0, stream, d);
-    else
-      hipLaunchKernelGGL((llsa_stream_step_kernel<float, 32>), grid, block, 0, stream, d);
-  }
+  with_step_shape(et, a.d, a.Lb + a.La + 1, [&](auto e, auto dim, auto nv) {
+    hipLaunchKernelGGL((llsa_stream_step_kernel<decltype(e), dim, nv>), dim3(a.S), dim3(64 * nw), 0, stream, d);
+  });
   return hipGetLastError();
 }
 
@@ -395,18 +406,9 @@ hipError_t launch_stream_step(const StreamStepArgs& a, ElemType et, hipStream_t 
   d.lengths = a.lengths;
   d.scale_log2 = kLog2e / sqrtf(static_cast<float>(a.d));
   const int nw = a.H < kMaxWaves ? a.H : kMaxWaves;
-  const dim3 grid(a.S), block(64 * nw);
-  if (et == kBF16) {
-    if (a.d == 64)
-      hipLaunchKernelGGL((stream_step_kernel<uint16_t, 64>), grid, block, 0, stream, d);
-    else
-      hipLaunchKernelGGL((stream_step_kernel<uint16_t, 32>), grid, block, 0, stream, d);
-  } else {
-    if (a.d == 64)
-      hipLaunchKernelGGL((stream_step_kernel<float, 64>), grid, block, 0, stream, d);
-    else
-      hipLaunchKernelGGL((stream_step_kernel<float, 32>), grid, block, 0, stream, d);
-  }
+  with_step_shape(et, a.d, a.Lb + a.La + 1, [&](auto e, auto dim, auto nv) {
+    hipLaunchKernelGGL((stream_step_kernel<decltype(e), dim, nv>), dim3(a.S), dim3(64 * nw), 0, stream, d);
+  });
   return hipGetLastError();
 }
 
