@@ -83,6 +83,17 @@ struct DevStream {
   float scale_log2;
 };
 
+// Ring slots of the frames lo, lo + 1, ... (lo >= 0) of a window of at most R
+// frames: one remainder, then a wrap per frame.
+struct RingSlots {
+  int first, R;
+  __device__ __forceinline__ RingSlots(int lo, int R_) : first(lo % R_), R(R_) {}
+  __device__ __forceinline__ size_t at(int j) const {
+    const int x = first + j;
+    return static_cast<size_t>(x >= R ? x - R : x);
+  }
+};
+
 // Attention of NQ query rows (one head, NQ = 1 or 2) over the same W frames
 // lo .. lo + W - 1 by one wave, with every memory access coalesced: lane
 // (kg, dc) takes 16-byte chunk dc of key and value rows kg, kg + NKG, ..., so
@@ -93,9 +104,10 @@ struct DevStream {
 // through LDS. Across blocks the softmax runs online (running maximum, sum and
 // weighted sum rescaled when the maximum grows). qs[n] is query n's row (null
 // when it is not due), o[n] its output row (zero when not due).
+// krow(j) and vrow(j) give the rows of the window's frame j.
 template <typename E, int D, int NV, int NQ, typename KRow, typename VRow>
-__device__ __forceinline__ void attend_rows(const E* const* qs, KRow krow, VRow vrow, int lo, int W,
-                                            float scale_log2, E* const* o, int lane) {
+__device__ __forceinline__ void attend_rows(const E* const* qs, KRow krow, VRow vrow, int W, float scale_log2,
+                                            E* const* o, int lane) {
   constexpr int EPC = 16 / sizeof(E);
   constexpr int CH = D / EPC;     // chunks per row: lanes per row group
   constexpr int NKG = 64 / CH;    // row groups per wave
@@ -122,10 +134,11 @@ __device__ __forceinline__ void attend_rows(const E* const* qs, KRow krow, VRow 
     uint4 kc[NV], vc[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      const int j = j0 + kg + NKG * i;
-      const bool in = j < W;
-      kc[i] = in ? chunk(krow(lo + j), dc) : make_uint4(0, 0, 0, 0);
-      vc[i] = in ? chunk(vrow(lo + j), dc) : make_uint4(0, 0, 0, 0);
+      // rows past the window: its last row again, so that every load goes out
+      // without a branch (masked below)
+      const int j = min(j0 + kg + NKG * i, W - 1);
+      kc[i] = chunk(krow(j), dc);
+      vc[i] = chunk(vrow(j), dc);
     }
     float z[NQ][NV], bm[NQ];
 #pragma unroll
@@ -157,6 +170,7 @@ __device__ __forceinline__ void attend_rows(const E* const* qs, KRow krow, VRow 
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       float vf[EPC];
+      if (j0 + kg + NKG * i >= W) vc[i] = make_uint4(0, 0, 0, 0);
       unpack16<E>(vc[i], vf);
 #pragma unroll
       for (int n = 0; n < NQ; ++n) {
@@ -194,9 +208,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stream_step_kernel(DevStream a
   const int QR = La + 1;
   const size_t HD = static_cast<size_t>(H) * D;
 
-  const int u = a.step[s];
-  int len = a.lengths ? a.lengths[s] : 0x7fffffff;
-  len = len < 0 ? 0 : len;
+  const int u = __builtin_amdgcn_readfirstlane(a.step[s]);
+  const int len = clamp_len_uniform(a.lengths, s, 0x7fffffff);
   const bool append = u >= 0 && u < len;
   const long long tl = static_cast<long long>(u) - La;
   const bool emit = tl >= 0 && tl < len;
@@ -227,13 +240,15 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stream_step_kernel(DevStream a
     const int lo = max(0, t - a.Lb);
     const int hi = min(len - 1, u);
     const int W = hi - lo + 1;
-    // frame tau's row: the just-arrived frame u is still in the input
-    auto krow = [&](int tau) { return (tau == u ? kin : kring + static_cast<size_t>(tau % R) * HD) + ho; };
-    auto vrow = [&](int tau) { return (tau == u ? vin : vring + static_cast<size_t>(tau % R) * HD) + ho; };
+    // frame lo + j's row: the just-arrived frame u is still in the input
+    const RingSlots slots(lo, R);
+    const int ju = u - lo;
+    auto krow = [&](int j) { return (j == ju ? kin : kring + slots.at(j) * HD) + ho; };
+    auto vrow = [&](int j) { return (j == ju ? vin : vring + slots.at(j) * HD) + ho; };
     const E* qrow = (La == 0 ? qin : qring + static_cast<size_t>(t % QR) * HD) + ho;
     const E* qs[1] = {qrow};
     E* os[1] = {out + ho};
-    attend_rows<E, D, NV, 1>(qs, krow, vrow, lo, W, a.scale_log2, os, lane);
+    attend_rows<E, D, NV, 1>(qs, krow, vrow, W, a.scale_log2, os, lane);
   }
   if (threadIdx.x == 0 && a.emitted) a.emitted[s] = emit ? t : -1;
   __syncthreads();  // every wave has read step[s]
@@ -273,9 +288,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void llsa_stream_step_kernel(DevLls
   const int H = a.H, La = a.La, R = a.R;
   const size_t HD = static_cast<size_t>(H) * D;
 
-  const int u = a.step[s];
-  int len = a.lengths ? a.lengths[s] : 0x7fffffff;
-  len = len < 0 ? 0 : len;
+  const int u = __builtin_amdgcn_readfirstlane(a.step[s]);
+  const int len = clamp_len_uniform(a.lengths, s, 0x7fffffff);
   const bool got_c = u >= 0 && u < len;  // branch C's frame u arrives; its causal output is due
   const long long tl = static_cast<long long>(u) - La;
   const bool got_l = tl >= 0 && tl < len;  // branch L's frame t arrives; its look-ahead output is due
@@ -307,14 +321,14 @@ __global__ __launch_bounds__(64 * kMaxWaves) void llsa_stream_step_kernel(DevLls
         *reinterpret_cast<uint4*>(dst + ho + c * EPC) = chunk(src + ho, c);
       }
     }
-    // frame tau's rows; the frames that arrived in this step are still in the inputs
-    auto krow = [&](int tau) {
-      return (tau <= split ? (tau == t ? kl : klr + static_cast<size_t>(tau % R) * HD)
-                           : (tau == u ? kc : kcr + static_cast<size_t>(tau % R) * HD)) + ho;
+    // frame lo + j's rows; the frames that arrived in this step are still in the inputs
+    const RingSlots slots(lo, R);
+    const int js = static_cast<int>(split - lo), jt = got_l ? t - lo : -1, ju = u - lo;
+    auto krow = [&](int j) {
+      return (j <= js ? (j == jt ? kl : klr + slots.at(j) * HD) : (j == ju ? kc : kcr + slots.at(j) * HD)) + ho;
     };
-    auto vrow = [&](int tau) {
-      return (tau <= split ? (tau == t ? vl : vlr + static_cast<size_t>(tau % R) * HD)
-                           : (tau == u ? vc : vcr + static_cast<size_t>(tau % R) * HD)) + ho;
+    auto vrow = [&](int j) {
+      return (j <= js ? (j == jt ? vl : vlr + slots.at(j) * HD) : (j == ju ? vc : vcr + slots.at(j) * HD)) + ho;
     };
     if (!got_c && !got_l) {
       if (lane < CH) {
@@ -325,7 +339,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void llsa_stream_step_kernel(DevLls
     }
     const E* qq[2] = {got_c ? qc + ho : nullptr, got_l ? ql + ho : nullptr};
     E* oo[2] = {out_c + ho, out_l + ho};
-    attend_rows<E, D, NV, 2>(qq, krow, vrow, lo, hi - lo + 1, a.scale_log2, oo, lane);
+    attend_rows<E, D, NV, 2>(qq, krow, vrow, hi - lo + 1, a.scale_log2, oo, lane);
   }
   if (threadIdx.x == 0) {
     if (a.emitted_c) a.emitted_c[s] = got_c ? u : -1;
