@@ -268,7 +268,8 @@ __global__ __launch_bounds__(kThreads) void band_fwd_bf16_kernel(DevArgs a) {
 // output, 4 waves; LLSA: both outputs, 8 waves, waves 4j .. 4j + 3 for output
 // j). Each band (a pair of key and value tensors) is staged once, in one go,
 // with direct global->LDS copies: band b holds the frames f0 + base_b ..
-// f0 + base_b + rows_b - 1 (frames outside the sequence zero-filled). The 16
+// f0 + base_b + rows_b - 1 (frames outside the sequence clamped to its ends and
+// masked). The 16
 // queries of wave w of an output sweep band b in 32-key sub-blocks starting at
 // row 16 (w % 4) + shift, so all four waves of an output see their window at
 // the same offset inside their sub-blocks and a window of 16 + hi - lo frames
@@ -283,6 +284,7 @@ struct TileBand {
   const void* k;
   const void* v;
   int base;  // frame of band row 0, relative to the tile's first query
+  int rows;  // band rows some wave reads, in whole copies
 };
 struct TileSeg {
   int lo, hi;   // the window's frames t + lo .. t + hi come from this band
@@ -447,10 +449,8 @@ __global__ __launch_bounds__(256 * NJOB) void band_fwd_tile_kernel(TileArgs a) {
   constexpr int NS = D / 32, NB = D / 16;
   constexpr int CPR = D / 8;
   __shared__ __attribute__((aligned(128))) uint16_t s_kv[2 * (SEG0 + SEG1) * D];
-  static_assert(NW * stage_elems<D>() <= 2 * (SEG0 + SEG1) * D, "staging must fit in the bands");
   uint16_t* const bk[2] = {s_kv, s_kv + 2 * SEG0 * D};
   uint16_t* const bv[2] = {s_kv + SEG0 * D, s_kv + (2 * SEG0 + SEG1) * D};
-  constexpr int brows[2] = {SEG0, SEG1};
   static_assert(SEG0 * D * 2 % 128 == 0 && SEG1 * D * 2 % 128 == 0, "band arrays must stay 128-byte aligned");
 
   int bh, tile;
@@ -481,18 +481,15 @@ __global__ __launch_bounds__(256 * NJOB) void band_fwd_tile_kernel(TileArgs a) {
     return;
   }
 
-  // stage the bands; rows outside the sequence are zero-filled below
-  int blo[2], bhi[2];
-  bool edge = false;
+  // stage the bands (frames outside the sequence clamped to its ends, and masked)
 #pragma unroll
   for (int bi = 0; bi < 2; ++bi) {
     if (bi >= a.nband) break;
     const int bbase = f0 + a.band[bi].base;
-    blo[bi] = max(0, -bbase);
-    bhi[bi] = min(brows[bi], len - bbase);
-    edge |= blo[bi] > 0 || bhi[bi] < brows[bi];
-    seg_issue_rows<D, NW>(bk[bi], static_cast<const uint16_t*>(a.band[bi].k) + slice, fs, bbase, blo[bi], bhi[bi], w, lane);
-    seg_issue_rows<D, NW>(bv[bi], static_cast<const uint16_t*>(a.band[bi].v) + slice, fs, bbase, blo[bi], bhi[bi], w, lane);
+    seg_issue_clamped<D, NW>(bk[bi], static_cast<const uint16_t*>(a.band[bi].k) + slice, fs, bbase, a.band[bi].rows,
+                             len - 1, w, lane);
+    seg_issue_clamped<D, NW>(bv[bi], static_cast<const uint16_t*>(a.band[bi].v) + slice, fs, bbase, a.band[bi].rows,
+                             len - 1, w, lane);
   }
   const int jb = NJOB > 1 ? (w >> 2) : 0;
   const TileJob& job = a.job[jb];
@@ -511,17 +508,6 @@ __global__ __launch_bounds__(256 * NJOB) void band_fwd_tile_kernel(TileArgs a) {
   }
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (edge) {  // the tile touches an end of the sequence
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi) {
-      if (bi >= a.nband) break;
-      seg_zero_rows<D, NT>(bk[bi], 0, blo[bi], tid);
-      seg_zero_rows<D, NT>(bk[bi], bhi[bi], brows[bi], tid);
-      seg_zero_rows<D, NT>(bv[bi], 0, blo[bi], tid);
-      seg_zero_rows<D, NT>(bv[bi], bhi[bi], brows[bi], tid);
-    }
-    __syncthreads();
-  }
 
   const float c2 = a.scale_log2;
   float lsum = 0.f;
@@ -972,34 +958,36 @@ DevJob to_dev(const BandJob& j) {
 }
 
 
-// Rows staged per band by the tile kernel (for d = 64; twice as many for
-// d = 32, whose rows are half as long).
-constexpr int kSaRows = 144;                     // SA: 48 + 32 * 3 (Lb + La <= 80)
+// Rows staged per band by the SA tile kernel whose waves take n sub-blocks (up
+// to kMaxBlocks0: Lb + La <= 80). Rows past a window's last sub-block are not
+// staged (a window of 73 at d = 32, B = 96, T = 131, H = 8: 11.4 us with 288 rows
+// staged and zero-filled at the ends, 9.5 us with 144 clamped ones).
+constexpr int sa_rows(int n) { return 48 + kSub * n; }
+// LLSA: rows per band for d = 64; twice as many for d = 32, whose rows are half
+// as long.
 constexpr int kLlsaRows0 = 152, kLlsaRows1 = 88;  // LLSA: both outputs, Lb = 64, La = 8 and smaller
 // Sub-blocks a wave holds in registers per band (the window of one band).
 constexpr int kMaxBlocks0 = 3, kMaxBlocks1 = 1;
 
-// The persistent kernel holds the sequence lengths in the lanes of a wave;
-// past this many sequences the tile kernel is used instead.
-constexpr int kPersistMaxB = 64;
-
 // Lays the jobs' window segments onto tile-kernel bands (segment i of every job
-// reads band i). Returns false when a band would need more than its rows.
-bool plan_tile(const BandForwardArgs& a, int rows0, int rows1, TileArgs& d) {
+// reads band i). Every wave computes all of a kernel instance's sub-blocks of a
+// band: blocks[i], on entry the most it may take, comes back as what the windows
+// need (at least one). Returns false when a band would need more sub-blocks or
+// rows.
+bool plan_tile(const BandForwardArgs& a, const int* rows, int* blocks, TileArgs& d) {
   const int nseg = a.job[0].nseg;
   for (int j = 1; j < a.njobs; ++j)
     if (a.job[j].nseg != nseg) return false;
   d.nband = nseg;
   for (int i = 0; i < nseg; ++i) {
-    const int rows = i == 0 ? rows0 : rows1;
-    int base = 1 << 30;
+    int base = 1 << 30, most = 1;
     for (int j = 0; j < a.njobs; ++j) {
       const BandSegment& sg = a.job[j].seg[i];
       if (sg.k != a.job[0].seg[i].k || sg.v != a.job[0].seg[i].v) return false;
       if (sg.lo_off <= sg.hi_off) base = base < sg.lo_off ? base : sg.lo_off;
     }
     if (base == (1 << 30)) base = 0;  // every job's segment is empty
-    d.band[i] = TileBand{a.job[0].seg[i].k, a.job[0].seg[i].v, base};
+    long long shift = 0;
     for (int j = 0; j < a.njobs; ++j) {
       const BandSegment& sg = a.job[j].seg[i];
       TileSeg& ts = d.job[j].seg[i];
@@ -1008,11 +996,16 @@ bool plan_tile(const BandForwardArgs& a, int rows0, int rows1, TileArgs& d) {
       ts.shift = sg.lo_off - base;
       // the waves' sub-blocks start up to 15 rows before their windows
       ts.nblk = sg.lo_off <= sg.hi_off ? (16 + sg.hi_off - sg.lo_off + (ts.shift & 15) + kSub - 1) / kSub : 0;
-      // every wave computes all of the kernel's sub-blocks of a band, the
-      // last of them starting at row shift + 48 + 32 (blocks - 1)
-      const int blocks = i == 0 ? kMaxBlocks0 : kMaxBlocks1;
-      if (ts.nblk > blocks || static_cast<long long>(ts.shift) + 48 + kSub * blocks > rows) return false;
+      most = most > ts.nblk ? most : ts.nblk;
+      shift = shift > ts.shift ? shift : ts.shift;
     }
+    // the last sub-block starts at row shift + 48 + 32 (blocks - 1)
+    const long long need = shift + 48 + kSub * static_cast<long long>(most);
+    if (most > blocks[i] || need > rows[i]) return false;
+    blocks[i] = most;
+    const int rpc = 512 / a.d;  // rows of a copy (rows[i] is a multiple)
+    d.band[i] = TileBand{a.job[0].seg[i].k, a.job[0].seg[i].v, base,
+                         static_cast<int>((need + rpc - 1) / rpc * rpc)};
   }
   for (int j = 0; j < a.njobs; ++j) {
     d.job[j].q = a.job[j].q;
@@ -1061,21 +1054,34 @@ bool launch_llsa_ring(const BandForwardArgs& a, int ntiles, float scale_log2, hi
     r.out[j] = a.job[j].out;
     r.lse[j] = a.job[j].lse;
   }
-  r.B = a.B;
   r.T = a.T;
   r.H = a.H;
   r.ntiles = ntiles;
-  r.lengths = a.lengths;
   r.scale_log2 = scale_log2;
+  if (nb[0] > 3) return false;
   const dim3 grid(compute_units()), block(1024);
-  if (nb[0] <= 1)
-    hipLaunchKernelGGL((llsa_fwd_ring_kernel<D, 1, 1>), grid, block, 0, stream, r);
-  else if (nb[0] == 2)
-    hipLaunchKernelGGL((llsa_fwd_ring_kernel<D, 2, 1>), grid, block, 0, stream, r);
-  else if (nb[0] == 3)
-    hipLaunchKernelGGL((llsa_fwd_ring_kernel<D, 3, 1>), grid, block, 0, stream, r);
-  else
-    return false;
+  const int parts = (a.B + 63) / 64;  // the kernel holds the lengths of up to 64 sequences
+  for (int i = 0; i < parts; ++i) {
+    const int b0 = static_cast<int>(static_cast<long long>(a.B) * i / parts);
+    const size_t e = static_cast<size_t>(b0) * a.T * a.H * D;
+    LlsaRingArgs x = r;
+    for (int j = 0; j < 2; ++j) {
+      auto at = [e](const void* p) { return static_cast<const void*>(static_cast<const uint16_t*>(p) + e); };
+      x.q[j] = at(r.q[j]);
+      x.k[j] = at(r.k[j]);
+      x.v[j] = at(r.v[j]);
+      x.out[j] = static_cast<uint16_t*>(r.out[j]) + e;
+      x.lse[j] = r.lse[j] ? r.lse[j] + static_cast<size_t>(b0) * a.H * a.T : nullptr;
+    }
+    x.lengths = a.lengths ? a.lengths + b0 : nullptr;
+    x.B = static_cast<int>(static_cast<long long>(a.B) * (i + 1) / parts) - b0;
+    if (nb[0] <= 1)
+      hipLaunchKernelGGL((llsa_fwd_ring_kernel<D, 1, 1>), grid, block, 0, stream, x);
+    else if (nb[0] == 2)
+      hipLaunchKernelGGL((llsa_fwd_ring_kernel<D, 2, 1>), grid, block, 0, stream, x);
+    else
+      hipLaunchKernelGGL((llsa_fwd_ring_kernel<D, 3, 1>), grid, block, 0, stream, x);
+  }
   return true;
 }
 
@@ -1091,41 +1097,76 @@ bool launch_tile(const BandForwardArgs& a, hipStream_t stream) {
   constexpr int X = 64 / D;
   const int grid = xcd_slice_grid(a.B * a.H, d.ntiles);
   if (a.njobs == 1 && a.job[0].nseg == 1) {
-    if (!plan_tile(a, X * kSaRows, 0, d)) return false;
-    if (a.B <= kPersistMaxB) {
-      PairFwdArgs p;
-      p.q = a.job[0].q;
-      p.k = a.job[0].seg[0].k;
-      p.v = a.job[0].seg[0].v;
-      p.out = a.job[0].out;
-      p.lse = a.job[0].lse;
-      p.lo = a.job[0].seg[0].lo_off;
-      p.hi = a.job[0].seg[0].hi_off;
-      p.B = a.B;
-      p.T = a.T;
-      p.H = a.H;
-      p.ntiles = d.ntiles;
-      p.lengths = a.lengths;
-      p.scale_log2 = d.scale_log2;
-      // sub-blocks of a wave's window (an empty window still reads one)
-      const int nblk = p.lo <= p.hi ? (16 + p.hi - p.lo + kSub - 1) / kSub : 1;
-      const dim3 grid(compute_units()), block(64 * (8 + kFwdLoaders));
-      if (nblk <= 1)
-        hipLaunchKernelGGL((band_fwd_pair_kernel<D, 1>), grid, block, 0, stream, p);
-      else if (nblk == 2)
-        hipLaunchKernelGGL((band_fwd_pair_kernel<D, 2>), grid, block, 0, stream, p);
-      else
-        hipLaunchKernelGGL((band_fwd_pair_kernel<D, 3>), grid, block, 0, stream, p);
-      return true;
+    const int rows[2] = {sa_rows(kMaxBlocks0), 0};
+    int blocks[2] = {kMaxBlocks0, 0};
+    if (!plan_tile(a, rows, blocks, d)) return false;
+    const int nblk = blocks[0];
+    // Many tiles per compute unit at d = 64: the persistent kernel, whose loaders
+    // run ahead of the compute waves. With 16 tiles per compute unit it is ahead
+    // by itself (26.5 / 30.5 us, B = 32, T = 500, H = 16, a window of 73), with 8
+    // to 14 the tile kernel is (13.5 / 14.5 us at 8), but a training pass, forward
+    // then backward, is not (44.9 / 43.3 us); below, and at d = 32, the tile kernel
+    // is ahead in both (B = 8, T = 500, H = 12, a window of 41: 7.5 / 8.3 us and
+    // 19.8 / 20.9 us; B = 64, T = 800, H = 12, d = 32: 38.2 / 41.2 us and 114.5 /
+    // 119.2 us).
+    if constexpr (D == 64) {
+      if (a.B <= 64 && static_cast<long long>(a.B) * a.H * d.ntiles >= 8LL * compute_units()) {
+        PairFwdArgs p;
+        p.q = a.job[0].q;
+        p.k = a.job[0].seg[0].k;
+        p.v = a.job[0].seg[0].v;
+        p.out = a.job[0].out;
+        p.lse = a.job[0].lse;
+        p.lo = a.job[0].seg[0].lo_off;
+        p.hi = a.job[0].seg[0].hi_off;
+        p.B = a.B;
+        p.T = a.T;
+        p.H = a.H;
+        p.ntiles = d.ntiles;
+        p.lengths = a.lengths;
+        p.scale_log2 = d.scale_log2;
+        const dim3 g(compute_units()), block(64 * (8 + kFwdLoaders));
+        if (nblk <= 1)
+          hipLaunchKernelGGL((band_fwd_pair_kernel<D, 1>), g, block, 0, stream, p);
+        else if (nblk == 2)
+          hipLaunchKernelGGL((band_fwd_pair_kernel<D, 2>), g, block, 0, stream, p);
+        else
+          hipLaunchKernelGGL((band_fwd_pair_kernel<D, 3>), g, block, 0, stream, p);
+        return true;
+      }
     }
-    hipLaunchKernelGGL((band_fwd_tile_kernel<D, 1, X * kSaRows, 0, 3, 0>), dim3(grid), dim3(256), 0, stream, d);
+    if (nblk <= 1)
+      hipLaunchKernelGGL((band_fwd_tile_kernel<D, 1, sa_rows(1), 0, 1, 0>), dim3(grid), dim3(256), 0, stream, d);
+    else if (nblk == 2)
+      hipLaunchKernelGGL((band_fwd_tile_kernel<D, 1, sa_rows(2), 0, 2, 0>), dim3(grid), dim3(256), 0, stream, d);
+    else
+      hipLaunchKernelGGL((band_fwd_tile_kernel<D, 1, sa_rows(3), 0, 3, 0>), dim3(grid), dim3(256), 0, stream, d);
     return true;
   }
   if (a.njobs == 2 && a.job[0].nseg == 2) {
-    if (a.B <= kPersistMaxB && launch_llsa_ring<D>(a, d.ntiles, d.scale_log2, stream)) return true;
-    if (!plan_tile(a, X * kLlsaRows0, X * kLlsaRows1, d)) return false;
-    hipLaunchKernelGGL((band_fwd_tile_kernel<D, 2, X * kLlsaRows0, X * kLlsaRows1, 3, 1>), dim3(grid), dim3(512), 0,
-                       stream, d);
+    // The ring kernel (at most 64 sequences per launch) overlaps copies and
+    // compute but fills its pipeline anew in every workgroup: with six tiles per
+    // compute unit and launch the two meet (22.5 us each at B = 32, T = 256, H =
+    // 12, Lb = 64, La = 8), with ten the tile kernel is behind (37.2 / 32.5 us at B
+    // = 16, T = 800), with three ahead (12.4 / 12.8 us at B = 8, T = 500, Lb = 32;
+    // 8.5 / 10.4 us at B = 2, T = 1500, H = 8, Lb = 16, La = 4). The tile kernel's
+    // bands hold La up to 8 at Lb = 64; windows only the rings hold run there at
+    // any size.
+    const int parts = (a.B + 63) / 64;
+    const bool many = static_cast<long long>(a.B) * a.H * d.ntiles >= 6LL * parts * compute_units();
+    if (many && launch_llsa_ring<D>(a, d.ntiles, d.scale_log2, stream)) return true;
+    const int rows[2] = {X * kLlsaRows0, X * kLlsaRows1};
+    int blocks[2] = {kMaxBlocks0, kMaxBlocks1};
+    if (!plan_tile(a, rows, blocks, d)) return !many && launch_llsa_ring<D>(a, d.ntiles, d.scale_log2, stream);
+    if (blocks[0] == 1)
+      hipLaunchKernelGGL((band_fwd_tile_kernel<D, 2, X * kLlsaRows0, X * kLlsaRows1, 1, 1>), dim3(grid), dim3(512), 0,
+                         stream, d);
+    else if (blocks[0] == 2)
+      hipLaunchKernelGGL((band_fwd_tile_kernel<D, 2, X * kLlsaRows0, X * kLlsaRows1, 2, 1>), dim3(grid), dim3(512), 0,
+                         stream, d);
+    else
+      hipLaunchKernelGGL((band_fwd_tile_kernel<D, 2, X * kLlsaRows0, X * kLlsaRows1, 3, 1>), dim3(grid), dim3(512), 0,
+                         stream, d);
     return true;
   }
   return false;

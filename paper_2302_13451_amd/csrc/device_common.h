@@ -156,6 +156,25 @@ __device__ __forceinline__ void seg_zero_rows(uint16_t* X, int lo, int hi, int t
   for (int e = lo * CPR + tid; e < hi * CPR; e += NT) st16(X + 8 * e, kZero16);
 }
 
+// Issue the direct copies that fill segment rows [0, nrows) of X with frames
+// base .. base + nrows - 1 of src, frames outside [0, last] replaced by the first
+// or last one: every row then holds a frame of the sequence, and the rows whose
+// frame is outside it are masked where they are used. Copy I
+// fills rows RPI I .. RPI I + RPI - 1; wave w (uniform) of NW issues copies w,
+// w + NW, ... nrows is a multiple of RPI. The caller waits (vmcnt) and barriers
+// before reading X.
+template <int D, int NW>
+__device__ __forceinline__ void seg_issue_clamped(uint16_t* X, const uint16_t* src, int rstride, int base, int nrows,
+                                                  int last, int w, int lane) {
+  constexpr int CPR = D / 8, RPI = 64 / CPR;
+  const int rl = lane / CPR, pp = lane % CPR;
+  for (int I = w; I * RPI < nrows; I += NW) {
+    const int r = I * RPI + rl;
+    const int off = min(max(base + r, 0), last) * rstride + 8 * (pp ^ seg_swizzle<D>(r));
+    __builtin_amdgcn_global_load_lds(src + off, X + I * 512, 16, 0, 0);
+  }
+}
+
 // Number of elements a wave's staging area for one 16-row output tile takes
 // (rows of D elements padded to D + 8, so every row starts 16-byte aligned).
 template <int D>

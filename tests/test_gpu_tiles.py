@@ -1,0 +1,108 @@
+"""Kernels chosen by the window and the size of a call: the SA tile kernels stage
+the rows that one, two, three (or, backward at d = 32, up to seven) sub-blocks of
+32 read, and calls of more than 64 long sequences run as several launches of the
+persistent kernels. Windows on both sides of every line, against the fp64 oracle;
+a call in several launches bit for bit against its parts.
+
+Tolerance: parity.TOL["bf16"], the bar of the SA and LLSA parity tests."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2302_13451_amd import binding as bd
+from paper_2302_13451_amd.inputs import llsa_inputs, sa_inputs
+from parity import assert_lse_close, assert_slices_close, f64, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+# 16 + Lb + La frames per wave: 32, 33, 64, 65, 96, 97 at both head dims, and at
+# d = 32 the widest staged backward (224) and one more; T on both sides of one
+# tile, of the shortest sequences the persistent kernel takes (four tiles), and a
+# last tile of one row
+@pytest.mark.parametrize("d,Lb,La,T", [
+    (64, 11, 5, 65), (64, 12, 5, 64), (64, 40, 8, 129), (64, 0, 49, 130), (64, 72, 8, 193),
+    (64, 81, 0, 190), (32, 16, 0, 63), (32, 9, 8, 129), (32, 41, 7, 128), (32, 40, 9, 200),
+    (32, 70, 10, 193), (32, 73, 8, 192), (32, 200, 8, 257), (32, 201, 8, 257),
+])
+@pytest.mark.parametrize("H", [2, 131])  # few tiles; more than two per compute unit
+def test_sa_windows_at_the_lines_between_kernels(oracle_mod, d, Lb, La, T, H):
+    print("SA d=%d Lb=%d La=%d T=%d H=%d" % (d, Lb, La, T, H), flush=True)
+    x = sa_inputs(2, T, H, d, 71, scale="unit", lengths=[T, max(1, T - 70)], pad_value=float("nan"))
+    names = ("q", "k", "v", "dout")
+    q, k, v, do = (to_gpu(x[n], "bf16") for n in names)
+    ln, L = x["lengths"].cuda(), x["lengths"].numpy()
+    clean = [np.nan_to_num(f64(x[n])) for n in names]
+    y, lse = oracle_mod.sa_forward(*clean[:3], Lb, La, L)
+    out, lg = bd.sa_forward(q, k, v, Lb, La, ln)
+    assert_slices_close(f64(out), y, "bf16", L, "out")
+    assert_lse_close(lg.cpu().numpy(), lse, "bf16")
+    yb = torch.from_numpy(y).to(torch.bfloat16).cuda()
+    got = bd.sa_backward(q, k, v, yb, torch.from_numpy(lse).float().cuda(), do, Lb, La, ln)
+    ref = oracle_mod.sa_backward(*clean, Lb, La, L, y=f64(yb))
+    zero = 1e-5 * float(np.max(np.abs(ref[2])))
+    for n, g, r in zip(("dq", "dk", "dv"), got, ref):
+        assert_slices_close(f64(g), r, "bf16", L, n, zero_atol=zero, row_scale=True)
+
+
+@pytest.mark.parametrize("with_lengths", [True, False])
+@pytest.mark.parametrize("kind,B,T,H,d,Lb,La", [
+    ("sa", 67, 260, 12, 64, 30, 4),
+    ("sa", 131, 200, 12, 32, 20, 3),
+    ("llsa", 67, 260, 12, 64, 30, 4),
+    ("llsa", 65, 250, 12, 64, 20, 16),
+])
+def test_many_sequences_equal_their_parts(kind, B, T, H, d, Lb, La, with_lengths):
+    print("parts %s B=%d T=%d H=%d d=%d Lb=%d La=%d" % (kind, B, T, H, d, Lb, La), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(72)
+    lead = (2,) if kind == "llsa" else ()
+    q, k, v, do = (torch.randn(lead + (B, T, H, d), generator=g, device="cuda").to(torch.bfloat16)
+                   for _ in range(4))
+    ln = None
+    if with_lengths:
+        ln = torch.randint(0, T + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+        ln[0], ln[B - 1] = T, T
+    fwd, bwd = (bd.sa_forward, bd.sa_backward) if kind == "sa" else (bd.llsa_forward, bd.llsa_backward)
+    out, lse = fwd(q, k, v, Lb, La, ln)
+    grads = bwd(q, k, v, out, lse, do, Lb, La, ln)
+    parts = (B + 63) // 64
+    dim = len(lead)
+
+    def part(t, a, b):
+        return t.narrow(dim, a, b - a).contiguous()
+
+    for i in range(parts):
+        a, b = B * i // parts, B * (i + 1) // parts
+        x = [part(t, a, b) for t in (q, k, v, do)]
+        l = None if ln is None else ln[a:b].clone()
+        o, e = fwd(x[0], x[1], x[2], Lb, La, l)
+        gr = bwd(x[0], x[1], x[2], o, e, x[3], Lb, La, l)
+        for n, whole, p in zip(("out", "lse", "dq", "dk", "dv"), (out, lse) + tuple(grads), (o, e) + tuple(gr)):
+            assert torch.equal(part(whole, a, b), p), (n, i)
+
+
+@pytest.mark.parametrize("d,Lb,La,T", [
+    (64, 10, 1, 65), (64, 20, 8, 70), (64, 64, 8, 129), (64, 72, 0, 63), (32, 30, 8, 100),
+    (32, 64, 15, 130), (32, 5, 0, 64), (32, 15, 3, 257),
+])
+@pytest.mark.parametrize("B", [2, 66])
+def test_llsa_windows_of_the_tile_kernels(oracle_mod, d, Lb, La, T, B):
+    H = 1
+    print("LLSA d=%d Lb=%d La=%d T=%d B=%d" % (d, Lb, La, T, B), flush=True)
+    lengths = [T, max(1, T - 66)] + [(7 * i) % (T + 1) for i in range(B - 2)]
+    x = llsa_inputs(B, T, H, d, 73, scale="unit", lengths=lengths, pad_value=float("nan"), with_dout=True)
+    names = ("q", "k", "v", "dout")
+    q, k, v, do = (to_gpu(x[n], "bf16") for n in names)
+    ln, L = x["lengths"].cuda(), x["lengths"].numpy()
+    clean = [np.nan_to_num(f64(x[n])) for n in names]
+    y, lse = oracle_mod.llsa_two_branch(*clean[:3], Lb, La, L)
+    out, lg = bd.llsa_forward(q, k, v, Lb, La, ln)
+    assert_slices_close(f64(out), y, "bf16", L, "out")
+    assert_lse_close(lg.cpu().numpy(), lse, "bf16")
+    yb = torch.from_numpy(y).to(torch.bfloat16).cuda()
+    got = bd.llsa_backward(q, k, v, yb, torch.from_numpy(lse).float().cuda(), do, Lb, La, ln)
+    ref = oracle_mod.llsa_two_branch_backward(*clean, Lb, La, L, y=f64(yb))
+    zero = 1e-5 * float(np.max(np.abs(ref[2])))
+    for n, g, r in zip(("dq", "dk", "dv"), got, ref):
+        assert_slices_close(f64(g), r, "bf16", L, n, zero_atol=zero, row_scale=True)
