@@ -297,7 +297,7 @@ __device__ __forceinline__ void bwd_query_role(const BwdBands<D, RR>& bd, const 
 // with 48 + 32 ceil((16 + Lb + La) / 32) <= Seg<D>::kRows: waves 0-3 take the
 // key role and waves 4-7 the query role. The query band of q and dout starts
 // at frame f0 - La and the key band of k and v at f0 - Lb; each band stages
-// Seg<D>::kRows frames (frames outside the sequence are zero-filled), and each
+// SEG frames, and each
 // role finds its own rows inside the other role's band. The 16 keys (queries)
 // of wave w sweep the band rows 16 (w % 4) + 32 m, m = 0, 1, ...: every
 // sub-block of a wave starts at the same offset from the wave's window, so a
@@ -310,19 +310,15 @@ __device__ __forceinline__ void bwd_query_role(const BwdBands<D, RR>& bd, const 
 // the sequence get lse = +inf, so their weights are exactly zero without a
 // window test; the window test is only made in sub-blocks that cross a window
 // edge or the sequence's ends.
-template <int D>
+template <int D, int SEG>
 __global__ __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void sa_bwd_tile_kernel(BwdDev a) {
   constexpr int NT = 2 * kThreads;
-  constexpr int SEG = Seg<D>::kRows;
   constexpr int NS = D / 32, NB = D / 16;
   constexpr int NB16 = SEG / 16;           // 16-row blocks of the D product
   constexpr int BPW = (NB16 + 7) / 8;      // ... per wave
   static_assert(SEG % 16 == 0, "the D product covers the band in 16-row blocks");
-  // the four bands; once every wave is done with them, the first part holds
-  // each wave's output rows on their way to memory
   __shared__ __attribute__((aligned(128))) uint16_t s_band[4 * SEG * D];
-  static_assert(8 * 2 * stage_elems<D>() <= 4 * SEG * D, "staging must fit in the bands");
   uint16_t* const s_q = s_band;
   uint16_t* const s_do = s_band + SEG * D;
   uint16_t* const s_k = s_band + 2 * SEG * D;
@@ -347,48 +343,32 @@ void sa_bwd_tile_kernel(BwdDev a) {
     return;
   }
   const int qbase = f0 - La, kbase = f0 - Lb;  // frames of band row 0 (may be negative)
-  // band rows that hold frames of the sequence; the others are zero-filled
-  const int qlo = max(0, -qbase), qhi = min(SEG, len - qbase);
-  const int klo = max(0, -kbase), khi = min(SEG, len - kbase);
+  const int last = len - 1;
   const size_t slice = row_index(b, 0, h, T, H, D);
   const int fs = H * D;  // elements from one frame to the next
   const uint16_t *q = a.q + slice, *k = a.k + slice, *v = a.v + slice;
   const uint16_t *o = a.o + slice, *dout = a.dout + slice;
   const float* lse_bh = a.lse + (static_cast<size_t>(b) * H + h) * T;
 
-  seg_issue_rows<D, 8>(s_q, q, fs, qbase, qlo, qhi, w, lane);
-  seg_issue_rows<D, 8>(s_do, dout, fs, qbase, qlo, qhi, w, lane);
-  seg_issue_rows<D, 8>(s_k, k, fs, kbase, klo, khi, w, lane);
-  seg_issue_rows<D, 8>(s_v, v, fs, kbase, klo, khi, w, lane);
-  // out rows of the query band as the B operand of the D product (zero outside
-  // the sequence): wave w takes the 16-row blocks w, w + 8, ...
+  // (frames outside the sequence are clamped to its ends: their query rows weigh
+  // zero through lse = +inf, their key rows are masked)
+  seg_issue_clamped<D, 8>(s_q, q, fs, qbase, SEG, last, w, lane);
+  seg_issue_clamped<D, 8>(s_do, dout, fs, qbase, SEG, last, w, lane);
+  seg_issue_clamped<D, 8>(s_k, k, fs, kbase, SEG, last, w, lane);
+  seg_issue_clamped<D, 8>(s_v, v, fs, kbase, SEG, last, w, lane);
+  // out rows of the query band as the B operand of the D product: wave w takes
+  // the 16-row blocks w, w + 8, ...
   bf16x8 of[BPW][NS];
 #pragma unroll
   for (int j = 0; j < BPW; ++j) {
-    const int fr = qbase + 16 * (w + 8 * j) + col;
-    const bool in = w + 8 * j < NB16 && fr >= 0 && fr < len;
+    const int fr = min(max(qbase + 16 * (w + 8 * j) + col, 0), last);
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      of[j][s] = bf16x8{};
-      if (in) of[j][s] = __builtin_bit_cast(bf16x8, ld16(o + (fr * fs + 32 * s + 8 * g)));
-    }
+    for (int s = 0; s < NS; ++s) of[j][s] = __builtin_bit_cast(bf16x8, ld16(o + (fr * fs + 32 * s + 8 * g)));
   }
-  float lsev = 0.f;
   const int lfr = qbase + tid;
-  if (tid < SEG && lfr >= 0 && lfr < len) lsev = lse_bh[lfr];
+  const float lsev = lse_bh[min(max(lfr, 0), last)];
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (qlo > 0 || qhi < SEG || klo > 0 || khi < SEG) {  // the tile touches an end of the sequence
-    seg_zero_rows<D, NT>(s_q, 0, qlo, tid);
-    seg_zero_rows<D, NT>(s_q, qhi, SEG, tid);
-    seg_zero_rows<D, NT>(s_do, 0, qlo, tid);
-    seg_zero_rows<D, NT>(s_do, qhi, SEG, tid);
-    seg_zero_rows<D, NT>(s_k, 0, klo, tid);
-    seg_zero_rows<D, NT>(s_k, khi, SEG, tid);
-    seg_zero_rows<D, NT>(s_v, 0, klo, tid);
-    seg_zero_rows<D, NT>(s_v, khi, SEG, tid);
-    __syncthreads();
-  }
   if (tid < SEG) s_lse2[tid] = (lfr >= 0 && lfr < len) ? lsev * kLog2e : __builtin_huge_valf();
 #pragma unroll
   for (int j = 0; j < BPW; ++j) {
@@ -420,16 +400,13 @@ void sa_bwd_tile_kernel(BwdDev a) {
   if (w < 4) {
     f32x4 adv[NB], adk[NB];
     bwd_key_role<D, SEG, false>(bands, sa, own, r0, w & 3, len, Lb, La, nblk, a.scale_log2, lane, adv, adk);
-    __syncthreads();  // every wave is done with the bands
-    uint16_t* stage = s_band + w * 2 * stage_elems<D>();
-    store_tile_rows<D>(stage, a.dv + slice, fs, r0, nrows, adv, 1.f, valid, lane);
-    store_tile_rows<D>(stage + stage_elems<D>(), a.dk + slice, fs, r0, nrows, adk, a.scale, valid, lane);
+    store_rows_direct<D>(a.dv + slice, fs, r0, nrows, adv, 1.f, valid, lane);
+    store_rows_direct<D>(a.dk + slice, fs, r0, nrows, adk, a.scale, valid, lane);
   } else {
     f32x4 aq[NB];
     bwd_query_role<D, SEG, false>(bands, sa, own, c_own, r0, w & 3, len, Lb, La, nblk, a.scale_log2, a.log2_scale,
                                   lane, aq);
-    __syncthreads();  // every wave is done with the bands
-    store_tile_rows<D>(s_band + w * 2 * stage_elems<D>(), a.dq + slice, fs, r0, nrows, aq, 1.f, valid, lane);
+    store_rows_direct<D>(a.dq + slice, fs, r0, nrows, aq, 1.f, valid, lane);
   }
 }
 
@@ -448,7 +425,6 @@ void sa_bwd_tile_kernel(BwdDev a) {
 // Band rows outside the sequence hold copies of its first or last frame
 // (finite data) and are masked: query rows by lse = +inf, key rows by the
 // window test.
-constexpr int kPersistMaxB = 64;
 
 template <int D, int ROWS>
 struct RingRegs {
@@ -737,6 +713,43 @@ __global__ __launch_bounds__(768) void sa_bwd_persist_kernel(BwdDev a) {
   }
 }
 
+// One workgroup per compute unit (persist) or per tile, with bands of the rows
+// that windows of nblk sub-blocks read (a window of 73 at d = 32 by tiles, B = 96, T =
+// 131, H = 8: 21.2 us with 288 rows staged and zero-filled at the ends, 15.9 us with
+// 144 clamped ones; at d = 64, B = 32, T = 131, H = 12: 16.1 / 14.9 us).
+template <int D, int SEG>
+void launch_sa_staged(const BwdDev& a, bool persist, hipStream_t stream) {
+  if (persist)
+    hipLaunchKernelGGL((sa_bwd_persist_kernel<D, SEG>), dim3(compute_units()), dim3(768), 0, stream, a);
+  else
+    hipLaunchKernelGGL((sa_bwd_tile_kernel<D, SEG>), dim3(xcd_slice_grid(a.B * a.H, a.ntiles)), dim3(2 * kThreads), 0,
+                       stream, a);
+}
+template <int D>
+void launch_sa_staged(const BwdDev& a, int nblk, bool persist, hipStream_t stream) {
+  if (nblk <= 1) launch_sa_staged<D, 48 + kSub>(a, persist, stream);
+  else if (nblk == 2) launch_sa_staged<D, 48 + 2 * kSub>(a, persist, stream);
+  else if (nblk == 3) launch_sa_staged<D, 48 + 3 * kSub>(a, persist, stream);
+  else launch_sa_staged<D, Seg<D>::kRows>(a, persist, stream);
+}
+
+// Sequences b0 .. b0 + n - 1 of a call.
+BwdDev batch_slice(BwdDev a, int D, int b0, int n) {
+  const size_t e = static_cast<size_t>(b0) * a.T * a.H * D;
+  a.q += e;
+  a.k += e;
+  a.v += e;
+  a.o += e;
+  a.dout += e;
+  a.dq += e;
+  a.dk += e;
+  a.dv += e;
+  a.lse += static_cast<size_t>(b0) * a.H * a.T;
+  if (a.lengths) a.lengths += b0;
+  a.B = n;
+  return a;
+}
+
 hipError_t launch_mfma(const SaBackwardArgs& a, hipStream_t stream) {
   BwdDev d;
   d.q = static_cast<const uint16_t*>(a.q);
@@ -761,17 +774,18 @@ hipError_t launch_mfma(const SaBackwardArgs& a, hipStream_t stream) {
   const int seg_rows = a.d == 64 ? Seg<64>::kRows : Seg<32>::kRows;
   const long long nblk = (16LL + a.Lb + a.La + kSub - 1) / kSub;
   if (48 + kSub * nblk <= seg_rows) {
-    // both sweeps fit one segment: one workgroup per tile
-    const int grid = xcd_slice_grid(a.B * a.H, d.ntiles);
-    if (a.B <= kPersistMaxB) {
-      if (a.d == 64)
-        hipLaunchKernelGGL((sa_bwd_persist_kernel<64, Seg<64>::kRows>), dim3(compute_units()), dim3(768), 0, stream, d);
-      else
-        hipLaunchKernelGGL((sa_bwd_persist_kernel<32, Seg<32>::kRows>), dim3(compute_units()), dim3(768), 0, stream, d);
-    } else if (a.d == 64)
-      hipLaunchKernelGGL(sa_bwd_tile_kernel<64>, dim3(grid), dim3(2 * kThreads), 0, stream, d);
-    else
-      hipLaunchKernelGGL(sa_bwd_tile_kernel<32>, dim3(grid), dim3(2 * kThreads), 0, stream, d);
+    // both sweeps fit one segment
+    const int parts = persist_launches(a.B, a.H, d.ntiles);
+    if (parts == 0) {
+      if (a.d == 64) launch_sa_staged<64>(d, static_cast<int>(nblk), false, stream);
+      else launch_sa_staged<32>(d, static_cast<int>(nblk), false, stream);
+    }
+    for (int i = 0; i < parts; ++i) {
+      const int b0 = static_cast<int>(static_cast<long long>(a.B) * i / parts);
+      const BwdDev x = batch_slice(d, a.d, b0, static_cast<int>(static_cast<long long>(a.B) * (i + 1) / parts) - b0);
+      if (a.d == 64) launch_sa_staged<64>(x, static_cast<int>(nblk), true, stream);
+      else launch_sa_staged<32>(x, static_cast<int>(nblk), true, stream);
+    }
   } else {
     // bands wider than one segment stream through LDS in chunks whose loads
     // overlap the products: 48 us where sweeping them in staged segments took 58
@@ -812,13 +826,14 @@ struct LlsaBwdDev {
   int lo[2][2], hi[2][2];  // segment (output j, branch i); lo > hi: empty
   int qoff[2];             // frame of query band j's row 0, relative to the tile's first frame
   int koff[2];             // frame of key band i's row 0, relative to the tile's first frame
-  int krows[2];            // rows of key band i that some wave reads (<= the band's SEG rows)
+  int qrows[2];            // rows of query band j that some wave reads, in whole 16-row blocks (<= SEG)
+  int krows[2];            // the same of key band i
   int bq[2], bk[2];        // persistent kernel: rows of query band j and key band i per 32-frame step
 };
 
 // One workgroup of 16 waves per (sequence, head, 64-frame tile). LDS holds
 // the key and value bands of both branches and the query and dout bands of
-// both outputs (SEG rows each, frames outside the sequence zero-filled), and
+// both outputs (SEG rows each, filled as far as some wave reads), and
 // -D and lse log2(e) of both query bands. Waves 0-3 / 4-7 take the query role
 // of output 0 / 1 (both segments). Branch L's key role (two long segments) is
 // split by output: waves 8-11 take branch C's key role (both outputs) and then
@@ -863,35 +878,33 @@ __global__ __launch_bounds__(1024) void llsa_bwd_tile_kernel(LlsaBwdDev a) {
   }
   const size_t slice = row_index(b, 0, h, T, H, D);
   const int fs = H * D;
-  int qbase[2], kbase[2], blo[4], bhi[4];
+  // the rows of each band that some wave reads, frames outside the sequence
+  // clamped to its ends (query rows there weigh zero through lse = +inf, key rows
+  // are masked)
+  int qbase[2], kbase[2];
+  const int last = len - 1;
   for (int j = 0; j < 2; ++j) {
     qbase[j] = f0 + a.qoff[j];
     kbase[j] = f0 + a.koff[j];
-    blo[j] = max(0, -qbase[j]);
-    bhi[j] = min(SEG, len - qbase[j]);
-    blo[2 + j] = max(0, -kbase[j]);
-    bhi[2 + j] = min(a.krows[j], len - kbase[j]);
+    seg_issue_clamped<D, 16>(s_qb(j), a.q[j] + slice, fs, qbase[j], a.qrows[j], last, w, lane);
+    seg_issue_clamped<D, 16>(s_db(j), a.dout[j] + slice, fs, qbase[j], a.qrows[j], last, w, lane);
+    seg_issue_clamped<D, 16>(s_kb(j), a.k[j] + slice, fs, kbase[j], a.krows[j], last, w, lane);
+    seg_issue_clamped<D, 16>(s_vb(j), a.v[j] + slice, fs, kbase[j], a.krows[j], last, w, lane);
   }
-  for (int j = 0; j < 2; ++j) {
-    seg_issue_rows<D, 16>(s_qb(j), a.q[j] + slice, fs, qbase[j], blo[j], bhi[j], w, lane);
-    seg_issue_rows<D, 16>(s_db(j), a.dout[j] + slice, fs, qbase[j], blo[j], bhi[j], w, lane);
-    seg_issue_rows<D, 16>(s_kb(j), a.k[j] + slice, fs, kbase[j], blo[2 + j], bhi[2 + j], w, lane);
-    seg_issue_rows<D, 16>(s_vb(j), a.v[j] + slice, fs, kbase[j], blo[2 + j], bhi[2 + j], w, lane);
-  }
-  // out rows of both query bands as the B operand of the D products (zero
-  // outside the sequence): wave w takes the 16-row blocks w, w + 16, ... of
+  // out rows of both query bands as the B operand of the D products: wave w takes
+  // the 16-row blocks w, w + 16, ... of
   // the 2 NB16 blocks (band j = blk / NB16)
   bf16x8 of[BPW][NS];
 #pragma unroll
   for (int i = 0; i < BPW; ++i) {
     const int blk = w + 16 * i;
     const int jb = blk >= NB16 ? 1 : 0, rb = blk - jb * NB16;
-    const int fr = qbase[jb] + 16 * rb + col;
-    const bool in = blk < 2 * NB16 && fr >= 0 && fr < len;
+    const int fr = min(max(qbase[jb] + 16 * rb + col, 0), last);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       of[i][s] = bf16x8{};
-      if (in) of[i][s] = __builtin_bit_cast(bf16x8, ld16(a.o[jb] + slice + (fr * fs + 32 * s + 8 * g)));
+      if (blk < 2 * NB16 && 16 * rb < a.qrows[jb])
+        of[i][s] = __builtin_bit_cast(bf16x8, ld16(a.o[jb] + slice + (fr * fs + 32 * s + 8 * g)));
     }
   }
   // lse of both query bands: thread j SEG + r holds row r of band j
@@ -902,20 +915,12 @@ __global__ __launch_bounds__(1024) void llsa_bwd_tile_kernel(LlsaBwdDev a) {
   if (lin) lsev = a.lse[lj][(static_cast<size_t>(b) * H + h) * T + lfr];
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-#pragma unroll
-  for (int x = 0; x < 8; ++x) {
-    const int bi = x < 4 ? x / 2 : 2 + (x - 4) / 2;  // its row range: query band j or key band 2 + i
-    const int rows = x < 4 ? SEG : a.krows[bi - 2];  // the rows any wave reads
-    if (blo[bi] > 0) seg_zero_rows<D, NT>(band(x), 0, min(blo[bi], rows), tid);
-    if (bhi[bi] < rows) seg_zero_rows<D, NT>(band(x), max(bhi[bi], 0), rows, tid);
-  }
-  __syncthreads();
   if (tid < 2 * SEG) s_stat[2 * SEG * lj + SEG + lr] = lin ? lsev * kLog2e : __builtin_huge_valf();
 #pragma unroll
   for (int i = 0; i < BPW; ++i) {
     const int blk = w + 16 * i;
-    if (blk < 2 * NB16) {
-      const int jb = blk >= NB16 ? 1 : 0, rb = blk - jb * NB16;
+    const int jb = blk >= NB16 ? 1 : 0, rb = blk - jb * NB16;
+    if (blk < 2 * NB16 && 16 * rb < a.qrows[jb]) {
       f32x4 dd = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < NS; ++s)
@@ -1434,19 +1439,26 @@ bool llsa_bwd_geometry(int d, int Lb, int La, LlsaBwdDev& a) {
     }
   for (int i = 0; i < 2; ++i)
     if (64 - a.koff[i] > seg_rows || 64 - a.qoff[i] > seg_rows) return false;
-  // the rows of each key band that some wave reads: its own 64 and the
-  // query roles' sub-blocks (branch C's short segments need about half the
-  // band, so only those rows are staged)
-  for (int i = 0; i < 2; ++i) {
-    int rows = 64 - a.koff[i];
-    for (int j = 0; j < 2; ++j) {
-      if (a.lo[j][i] > a.hi[j][i]) continue;
-      const int rel = a.lo[j][i] - a.koff[i];
-      const int nb = (16 + a.hi[j][i] - a.lo[j][i] + (rel & 15) + kSub - 1) / kSub;
-      const int r = 48 + (rel & ~15) + kSub * nb;
-      rows = rows > r ? rows : r;
+  // the rows of each band that some wave reads: its own 64 and the other roles'
+  // sub-blocks (branch C's short segments need about half the band, short windows
+  // less of every band)
+  auto need = [](int rel, int lo, int hi) {
+    return 48 + (rel & ~15) + kSub * ((16 + hi - lo + (rel & 15) + kSub - 1) / kSub);
+  };
+  for (int x = 0; x < 2; ++x) {
+    int kr = 64 - a.koff[x], qr = 64 - a.qoff[x];
+    for (int y = 0; y < 2; ++y) {
+      if (a.lo[y][x] <= a.hi[y][x]) {
+        const int r = need(a.lo[y][x] - a.koff[x], a.lo[y][x], a.hi[y][x]);
+        kr = kr > r ? kr : r;
+      }
+      if (a.lo[x][y] <= a.hi[x][y]) {
+        const int r = need(-a.hi[x][y] - a.qoff[x], a.lo[x][y], a.hi[x][y]);
+        qr = qr > r ? qr : r;
+      }
     }
-    a.krows[i] = rows;
+    a.krows[x] = (kr + 15) & ~15;
+    a.qrows[x] = (qr + 15) & ~15;
   }
   return true;
 }
@@ -1737,12 +1749,14 @@ bool llsa_backward_fits(int d, int Lb, int La) {
 
 hipError_t launch_llsa_backward(const LlsaBackwardArgs& x, ElemType et, hipStream_t stream) {
   LlsaBwdDev a{};
-  // bfloat16 windows whose bands fit the persistent kernel's rings (up to 64
-  // sequences, d = 64) or one staged segment run on bfloat16 MFMA, the rest in
+  // bfloat16 windows whose bands fit the persistent kernel's rings (d = 64; up to
+  // 64 sequences, or more in several launches that are each large) or one staged segment run on bfloat16 MFMA, the rest in
   // float32 arithmetic (the segments and origins are set whether or not the
   // staged segment fits)
   const bool staged = llsa_bwd_geometry(x.d, x.Lb, x.La, a);
-  const bool ring = et == kBF16 && x.d == 64 && x.B <= kPersistMaxB && llsa_bwd_ring_geometry(a);
+  const int ntiles = (x.T + kC - 1) / kC;
+  const int parts = x.B <= 64 ? 1 : persist_launches(x.B, x.H, ntiles);
+  const bool ring = et == kBF16 && x.d == 64 && parts > 0 && llsa_bwd_ring_geometry(a);
   if (!ring && (et != kBF16 || !staged)) return launch_llsa_backward_general(x, et, stream);
   const size_t branch = static_cast<size_t>(x.B) * x.T * x.H * x.d;
   for (int j = 0; j < 2; ++j) {
@@ -1759,13 +1773,31 @@ hipError_t launch_llsa_backward(const LlsaBackwardArgs& x, ElemType et, hipStrea
   a.B = x.B;
   a.T = x.T;
   a.H = x.H;
-  a.ntiles = (x.T + kC - 1) / kC;
+  a.ntiles = ntiles;
   a.lengths = x.lengths;
   a.scale = 1.f / sqrtf(static_cast<float>(x.d));
   a.scale_log2 = kLog2e * a.scale;
   a.log2_scale = -0.5f * log2f(static_cast<float>(x.d));
   if (ring) {
-    hipLaunchKernelGGL(llsa_bwd_ring_kernel<64>, dim3(compute_units()), dim3(768), 0, stream, a);
+    for (int i = 0; i < parts; ++i) {
+      const int b0 = static_cast<int>(static_cast<long long>(x.B) * i / parts);
+      LlsaBwdDev y = a;
+      const size_t e = static_cast<size_t>(b0) * x.T * x.H * x.d;
+      for (int j = 0; j < 2; ++j) {
+        y.q[j] += e;
+        y.o[j] += e;
+        y.dout[j] += e;
+        y.k[j] += e;
+        y.v[j] += e;
+        y.lse[j] += static_cast<size_t>(b0) * x.H * x.T;
+        y.dq[j] += e;
+        y.dk[j] += e;
+        y.dv[j] += e;
+      }
+      if (y.lengths) y.lengths += b0;
+      y.B = static_cast<int>(static_cast<long long>(x.B) * (i + 1) / parts) - b0;
+      hipLaunchKernelGGL(llsa_bwd_ring_kernel<64>, dim3(compute_units()), dim3(768), 0, stream, y);
+    }
     return hipGetLastError();
   }
   const int grid = xcd_slice_grid(x.B * x.H, a.ntiles);

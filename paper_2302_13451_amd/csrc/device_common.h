@@ -128,34 +128,6 @@ __device__ __forceinline__ int seg_tr_off(int r, int L) {
   return r * D + (((((L >> 1) & 1) ^ seg_swizzle<D>(r)) << 3) | ((L & 1) << 2));
 }
 
-// Issue the direct copies that fill segment rows [lo, hi) of X with frames
-// base + lo .. base + hi - 1 of src (src: the (sequence, head) slice at frame
-// 0, row stride rstride elements; base may be negative, frames base + r for
-// r in [lo, hi) must exist). Copy I fills rows RPI I .. RPI I + RPI - 1; lanes of
-// rows outside [lo, hi) are inactive and leave their bytes untouched. Wave w
-// (uniform) of NW issues copies w, w + NW, ... The caller waits (vmcnt) and
-// barriers before reading X.
-template <int D, int NW>
-__device__ __forceinline__ void seg_issue_rows(uint16_t* X, const uint16_t* src, int rstride, int base, int lo,
-                                               int hi, int w, int lane) {
-  constexpr int CPR = D / 8, RPI = 64 / CPR;
-  const int rl = lane / CPR, pp = lane % CPR;
-  for (int I = lo / RPI + w; I * RPI < hi; I += NW) {
-    const int r = I * RPI + rl;
-    if (r >= lo && r < hi) {
-      const int p = pp ^ seg_swizzle<D>(r);
-      __builtin_amdgcn_global_load_lds(src + ((base + r) * rstride + 8 * p), X + I * 512, 16, 0, 0);
-    }
-  }
-}
-
-// Zero segment rows [lo, hi) of X (NT threads, thread tid).
-template <int D, int NT>
-__device__ __forceinline__ void seg_zero_rows(uint16_t* X, int lo, int hi, int tid) {
-  constexpr int CPR = D / 8;
-  for (int e = lo * CPR + tid; e < hi * CPR; e += NT) st16(X + 8 * e, kZero16);
-}
-
 // Issue the direct copies that fill segment rows [0, nrows) of X with frames
 // base .. base + nrows - 1 of src, frames outside [0, last] replaced by the first
 // or last one: every row then holds a frame of the sequence, and the rows whose
