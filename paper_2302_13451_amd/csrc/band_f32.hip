@@ -5,27 +5,33 @@
 // One wave owns 16 rows (queries, or keys in the backward's key role), one row
 // per lane column of the MFMA's N dimension, and sweeps the rows its window
 // reads in blocks of 16 that start exactly at the window's first row. Operands
-// go from memory straight into the operand registers, in two patterns:
-//   * rows (products that contract over the head dim): lane (g, col) loads
+// come in two patterns:
+//   * rows (products that contract over the head dim): lane (g, col) holds
 //     row col's pieces g. Which feature a contraction step takes does not
 //     matter as long as both operands agree, so a lane's 16-byte load serves
 //     several steps;
 //   * transposed rows (products that contract over frames): lane (g, col)
-//     loads features F col .. F col + F - 1 (F = D / 16) of row 4g + i for step
+//     holds features F col .. F col + F - 1 (F = D / 16) of row 4g + i for step
 //     i. A score tile comes out as rows 4g + i of column col, which is the
 //     weight operand of step i: weights never leave their registers.
-// The four waves of a workgroup own neighbouring rows and meet in the L1; a
-// block's row loads are issued once the score products of the block before it
-// have taken their operands, its transposed rows before its score products, so
-// neither LDS nor a barrier is needed.
 //
-// What bounds it (B = 8, T = 500, H = 12, d = 64, Lb = 32, La = 8, ragged):
-// backward 54 us, of which the float32 matrix instructions are 14 us (512 cycles
-// of one SIMD per product of a 16 x 16 block and 64 features) and the traffic 14
-// us at the device copy's rate; the rest is the latency of a wave's four to five
-// blocks at two waves per SIMD. One thread per row on the vector ALUs took 441
-// us, loads in the order of use 57 us, and rows staged through LDS by a
-// workgroup 61 us. Forward 16 us (177 us), at the same shape.
+// The forward loads both straight into the operand registers: the four waves of
+// a workgroup own neighbouring rows and meet in the L1, and a step's key loads
+// are issued behind the products of the step before. 16 us at B = 8, T = 500,
+// H = 12, d = 64, Lb = 32, La = 8 (ragged), 177 us with one thread per row; its
+// matrix instructions are 4 us and its traffic 7 us of that.
+//
+// The backward reads every row in both patterns, and a row-pattern load touches
+// 16 lines per 16 lanes (measured straight from memory: 49 L1 accesses per
+// instruction, 31 us of accesses alone). A workgroup therefore stages the rows a
+// tile reads in LDS, 112 (d = 64) at once, two workgroups per compute unit
+// overlapping each other's staging: 47 us at the same shape, of which the matrix
+// instructions are 14 us (512 cycles of one SIMD per product of a 16 x 16 block
+// and 64 features); the rest is the latency of staging and of a wave's four to
+// five blocks at two waves per SIMD. Straight from memory 54 us, in stages of 32
+// rows with two buffers 61 us (waves of a workgroup start their windows 16 rows
+// apart, and short stages make them wait for each other), 96 rows and three
+// workgroups 48 to 51 us (spilling), one thread per row 441 us.
 //
 // A matrix product multiplies the rows outside a row's window by a zero
 // weight, and 0 * inf is NaN: a wave that ends with a value that is not finite
@@ -41,6 +47,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kTileRows = 64;  // rows of a workgroup (four waves)
+constexpr int kStageBytes = 28672;  // backward: rows of one tensor staged at once (112 at d = 64)
 
 // ---------------------------------------------------------------------------
 // Forward: up to two outputs, each over one or two window segments.
@@ -193,16 +200,203 @@ __global__ __launch_bounds__(kThreads) void band_fwd_f32_kernel(FwdDev a) {
 // frames) gathers dq over its bands, a key role per (branch, 16 frames) gathers
 // dk and dv over the outputs' queries that read it. Every gradient row has one
 // writer: no atomics, no workspace, deterministic.
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
+
+// Staged rows: row r's 16-byte piece p sits at piece p ^ swizzle(r), so that the
+// row pattern (piece 4j + g of rows 0 .. 15 together) and the transposed one (a
+// whole row per 16 lanes) are free of bank conflicts.
+template <int D>
+__device__ __forceinline__ int f32_swizzle(int r) {
+  return D == 64 ? r & 15 : (r >> 1) & 7;
+}
+
+// LDS byte offsets of a lane's operand reads in the 16-row block at row 0 (the
+// block at row 16 n: 64 n D further).
+template <int D>
+struct F32BlockAddr {
+  uint32_t row;    // piece g of row col (piece 4j + g: XOR 64 j)
+  uint32_t tr[4];  // features F col .. of row 4g + i
+  __device__ __forceinline__ F32BlockAddr(int col, int g) {
+    row = static_cast<uint32_t>(col * 4 * D + 16 * (g ^ f32_swizzle<D>(col)));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 4 * g + i, f = D / 16 * col;  // first feature
+      tr[i] = static_cast<uint32_t>(r * 4 * D + 16 * ((f >> 2) ^ f32_swizzle<D>(r)) + 4 * (f & 3));
+    }
+  }
+};
+
+template <int D>
+__device__ __forceinline__ void lds_row(RowFrag<float, D>& x, uint32_t a) {
+#pragma unroll
+  for (int j = 0; j < RowFrag<float, D>::NR; ++j)
+    x.r[j] = __builtin_bit_cast(u32x4, *(const lds_f32x4*)(uintptr_t)(a ^ (64 * j)));
+}
+template <int D>
+__device__ __forceinline__ void lds_feat(FeatFrag<float, D>& x, uint32_t a) {
+  if constexpr (D == 64) x.r = __builtin_bit_cast(u32x4, *(const lds_f32x4*)(uintptr_t)a);
+  else x.r = __builtin_bit_cast(u32x2, *(const lds_f32x2*)(uintptr_t)a);
+}
+
+template <int D>
+struct BwdLds {
+  static constexpr int CH = kStageBytes / (4 * D);  // rows of a stage
+  __attribute__((aligned(128))) float x[CH * D], y[CH * D];
+  __attribute__((aligned(16))) float ndn[CH];  // -D_n (key role)
+  __attribute__((aligned(16))) float l2[CH];   // lse_n log2(e) (key role)
+};
+
+// One role of one tile. x: its branch (key role) or output (query role); f0: the
+// tile's first frame (f0 < len).
+template <int D, bool KEY>
+__device__ __forceinline__ void bwd_role(const BwdDev& a, BwdLds<D>& sm, int x, int b, int h, int f0, int len, int w,
+                                         int lane) {
+  constexpr int F = D / 16, CPR = D / 4, RPI = 64 / CPR, CH = BwdLds<D>::CH;
+  constexpr int NI = (CH / RPI + 3) / 4;  // copies per wave and tensor
+  const int col = lane & 15, g = lane >> 4;
+  const int T = a.T, H = a.H, fs = H * D, last = len - 1;
+  const size_t slice = row_index(b, 0, h, T, H, D);
+  const float *q = static_cast<const float*>(a.q) + slice, *k = static_cast<const float*>(a.k) + slice;
+  const float *v = static_cast<const float*>(a.v) + slice, *o = static_cast<const float*>(a.out) + slice;
+  const float* dout = static_cast<const float*>(a.dout) + slice;
+  const float* lse = a.lse + (static_cast<size_t>(b) * H + h) * T;
+  const int r0 = f0 + kRowsPerWave * w, me = r0 + col;
+  const bool valid = me < len;
+  const int fmax = min(f0 + kTileRows - 1, last), wmax = min(r0 + kRowsPerWave - 1, last);
+
+  // own rows, the N operand of the score products (lanes past the end hold the
+  // last frame's and are masked)
+  const int own = min(me, last) * fs;
+  RowFrag<float, D> o0, o1;
+  o0.load((KEY ? k + x * a.bstride : q + a.qb[x] * a.bstride) + own, g);
+  o1.load((KEY ? v : dout) + x * a.bstride + own, g);
+  float dn = 0.f, l2 = 0.f;
+  if constexpr (!KEY) {
+    RowFrag<float, D> of;
+    of.load(o + x * a.bstride + own, g);
+#pragma unroll
+    for (int n = 0; n < RowFrag<float, D>::N; ++n) dn += o1[n] * of[n];
+    dn = sum_over_column(dn);
+    l2 = lse[x * a.lstride + min(me, last)] * kLog2e;
+  }
+  f32x4 acc0[F], acc1[F];  // dq, or dk and dv
+#pragma unroll
+  for (int f = 0; f < F; ++f) acc0[f] = acc1[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const F32BlockAddr<D> ad(col, g);
+  const uint32_t xb = lds_addr(sm.x), yb = lds_addr(sm.y);
+  const float c2 = a.scale_log2;
+  const int rl = lane / CPR, pp = lane % CPR;
+  bool first = true;
+
+  const int nrel = KEY ? a.nout : a.nbranch;
+  for (int rel = 0; rel < nrel; ++rel) {
+    const int lo = KEY ? a.c[rel] - a.ehi[x] : a.c[x] - a.ehi[rel];
+    const int hi = KEY ? a.c[rel] - a.elo[x] : a.c[x] - a.elo[rel];
+    const int blo = KEY ? -hi : lo, bhi = KEY ? -lo : hi;  // rows r + blo .. r + bhi for the tile's row r
+    const int base = f0 + blo, beg = max(0, base), end = min(last, fmax + bhi);
+    if (lo > hi || beg > end) continue;
+    const float* xp = KEY ? q + a.qb[rel] * a.bstride : k + rel * a.bstride;
+    const float* yp = (KEY ? dout : v) + rel * a.bstride;
+    const int wbeg = max(0, r0 + blo), wend = wmax < r0 ? -1 : min(last, wmax + bhi);
+    const Span see(valid, max(0, me + blo), min(last, me + bhi));
+    // frames that every valid row of the wave sees
+    const int ibeg = max(0, wmax + blo), iend = min(last, r0 + bhi);
+    // stages start a multiple of 16 rows past the first row the tile reads, so
+    // that every wave's window starts a block
+    for (int cs = base + (beg - base) / 16 * 16; cs <= end; cs += CH) {
+      const int rows = min(CH, ((end - cs) & ~15) + 16);  // in whole blocks
+      if (!first) lds_barrier();  // every wave is done with the rows before
+      first = false;
+      u32x4 ro[KEY ? NI : 1];
+      float rs[KEY ? NI : 1];
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int r = (w + 4 * i) * RPI + rl;
+        if ((w + 4 * i) * RPI < rows) {
+          const int fr = min(max(cs + r, 0), last);
+          const int off = fr * fs + 4 * (pp ^ f32_swizzle<D>(r));
+          __builtin_amdgcn_global_load_lds(xp + off, sm.x + (w + 4 * i) * 256, 16, 0, 0);
+          __builtin_amdgcn_global_load_lds(yp + off, sm.y + (w + 4 * i) * 256, 16, 0, 0);
+          if constexpr (KEY) {
+            ro[i] = ld16(o + rel * a.bstride + off);
+            rs[i] = lse[rel * a.lstride + fr];
+          }
+        }
+      }
+      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's copies are in
+      if constexpr (KEY) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          if ((w + 4 * i) * RPI < rows) {
+            const f32x4 dv = *reinterpret_cast<const f32x4*>(sm.y + (w + 4 * i) * 256 + 4 * lane);
+            const f32x4 ov = __builtin_bit_cast(f32x4, ro[i]);
+            const float d = group_sum<CPR>((dv[0] * ov[0] + dv[1] * ov[1]) + (dv[2] * ov[2] + dv[3] * ov[3]));
+            if (pp == 0) {
+              sm.ndn[(w + 4 * i) * RPI + rl] = -d;
+              sm.l2[(w + 4 * i) * RPI + rl] = rs[i] * kLog2e;
+            }
+          }
+        }
+      }
+      lds_barrier();
+#pragma unroll 1
+      for (int sb = max(0, (wbeg - cs) & ~15); sb < rows; sb += 16) {
+        const int fb = cs + sb;
+        if (fb > wend) break;
+        const uint32_t xo = xb + sb * 4 * D, yo = yb + sb * 4 * D;
+        RowFrag<float, D> xr, yr;
+        FeatFrag<float, D> xt[4], yt[4];
+        lds_row<D>(xr, xo + ad.row);
+        lds_row<D>(yr, yo + ad.row);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          lds_feat<D>(xt[i], xo + ad.tr[i]);
+          if constexpr (KEY) lds_feat<D>(yt[i], yo + ad.tr[i]);
+        }
+        f32x4 nd = {-dn, -dn, -dn, -dn}, ls = {l2, l2, l2, l2};
+        if constexpr (KEY) {
+          nd = *reinterpret_cast<const f32x4*>(&sm.ndn[sb + 4 * g]);
+          ls = *reinterpret_cast<const f32x4*>(&sm.l2[sb + 4 * g]);
+        }
+        const f32x4 s = row_product(xr, o0), dpv = row_product(yr, o1);
+        const bool inside = fb >= ibeg && fb + 15 <= iend;
+        float p[4], ds[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float pw = fast_exp2(__builtin_fmaf(s[i], c2, -ls[i]));
+          const bool in = inside || see.has(fb + 4 * g + i);
+          p[i] = in ? pw : 0.f;
+          ds[i] = in ? pw * (dpv[i] + nd[i]) : 0.f;
+        }
+        if constexpr (KEY) col_product(yt, p, acc1);
+        col_product(xt, ds, acc0);
+      }
+    }
+  }
+
+  float* const d0 = static_cast<float*>(KEY ? a.dk : a.dq) + slice + (KEY ? x : a.qb[x]) * a.bstride;
+  float* const d1 = static_cast<float*>(a.dv) + slice + x * a.bstride;
+  const int r1 = min(r0 + kRowsPerWave, T);
+  if (r0 < len && __any(valid && !(all_finite<F>(acc0) && (!KEY || all_finite<F>(acc1))))) {
+    bwd_rows_slow<float, D>(a, KEY, x, b, h, r0, len, lane);
+    if (len < r1) {
+      zero_rows<D>(d0, fs, len, r1, lane);
+      if constexpr (KEY) zero_rows<D>(d1, fs, len, r1, lane);
+    }
+  } else {
+    store_own_row<D>(d0 + static_cast<ptrdiff_t>(me) * fs, acc0, a.scale, valid, me < T, g);
+    if constexpr (KEY) store_own_row<D>(d1 + static_cast<ptrdiff_t>(me) * fs, acc1, 1.f, valid, me < T, g);
+  }
+}
+
 template <int D>
 __global__ __launch_bounds__(kThreads) void band_bwd_f32_kernel(BwdDev a) {
-  typedef float E;
-  constexpr int N = D / 4, F = D / 16;
-  const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+  __shared__ BwdLds<D> sm;
+  const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int T = a.T, H = a.H, fs = H * D;
-  const BlockRows<D> rows(fs, col, g);
   const int nroles = a.nbranch + a.nout;
-  const float c2 = a.scale_log2;
   for (int bid = blockIdx.x; bid < a.items; bid += gridDim.x) {
     // items of a slice: the key roles and query roles of tile 0, of tile 1, ...
     int bh, item;
@@ -212,140 +406,20 @@ __global__ __launch_bounds__(kThreads) void band_bwd_f32_kernel(BwdDev a) {
     const int x = key_role ? role : role - a.nbranch;  // branch or output
     const int b = bh / H, h = bh - b * H;
     const int len = clamp_len_uniform(a.lengths, b, T);
-    const int r0 = tile * kTileRows + kRowsPerWave * w;
-    if (r0 >= T) continue;
-    const size_t slice = row_index(b, 0, h, T, H, D);
-    const int r1 = min(r0 + kRowsPerWave, T);
-    E* const d0 = static_cast<E*>(key_role ? a.dk : a.dq) + slice + (key_role ? x : a.qb[x]) * a.bstride;
-    E* const d1 = static_cast<E*>(a.dv) + slice + x * a.bstride;  // key role only
-    if (r0 >= len) {
-      zero_rows<D>(d0, fs, r0, r1, lane);
-      if (key_role) zero_rows<D>(d1, fs, r0, r1, lane);
+    const int f0 = tile * kTileRows;
+    if (f0 >= len) {
+      const size_t slice = row_index(b, 0, h, T, H, D);
+      const int z0 = f0 + kRowsPerWave * w, z1 = min(z0 + kRowsPerWave, T);
+      zero_rows<D>(static_cast<float*>(key_role ? a.dk : a.dq) + slice + (key_role ? x : a.qb[x]) * a.bstride, fs, z0,
+                   z1, lane);
+      if (key_role) zero_rows<D>(static_cast<float*>(a.dv) + slice + x * a.bstride, fs, z0, z1, lane);
       continue;
     }
-    const E *q = static_cast<const E*>(a.q) + slice, *k = static_cast<const E*>(a.k) + slice;
-    const E *v = static_cast<const E*>(a.v) + slice, *o = static_cast<const E*>(a.out) + slice;
-    const E* dout = static_cast<const E*>(a.dout) + slice;
-    const float* lse = a.lse + (static_cast<size_t>(b) * H + h) * T;
-    const int me = r0 + col, last = len - 1;
-    const bool valid = me < len;
-    const int wmax = min(r0 + kRowsPerWave - 1, last);
-    const int own = min(me, last) * fs;
-    f32x4 acc0[F], acc1[F];
-#pragma unroll
-    for (int f = 0; f < F; ++f) acc0[f] = acc1[f] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (key_role) {
-      RowFrag<E, D> kf, vf;
-      kf.load(k + x * a.bstride + own, g);
-      vf.load(v + x * a.bstride + own, g);
-      // the own rows are in before the loops: a wait for them inside would also
-      // wait for the loads issued there
-      __builtin_amdgcn_s_waitcnt(0x0f70);
-      for (int oi = 0; oi < a.nout; ++oi) {
-        const int lo = a.c[oi] - a.ehi[x], hi = a.c[oi] - a.elo[x];
-        const int wlo = max(0, r0 - hi), whi = min(last, wmax - lo);
-        if (lo > hi || wlo > whi) continue;
-        const Span see(valid, max(0, me - hi), min(last, me - lo));  // queries that see this lane's key
-        const E *qp = q + a.qb[oi] * a.bstride, *dp = dout + oi * a.bstride, *op = o + oi * a.bstride;
-        const float* lp = lse + oi * a.lstride;
-        // a block's rows are loaded while the dk and dv products of the block
-        // before run, its transposed rows while its score products run
-        RowFrag<E, D> qr, dr, orow;
-        float lv;
-        auto load_rows = [&](int qb) {
-          const size_t rr = rows.row(qb, last);
-          qr.load(qp + rr, g);
-          dr.load(dp + rr, g);
-          orow.load(op + rr, g);
-          lv = lp[min(qb + col, last)];
-        };
-        load_rows(wlo);
-        for (int qb = wlo; qb <= whi; qb += 16) {
-          FeatFrag<E, D> qt[4], dt[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const size_t rt = rows.frame(qb, i, last);
-            dt[i].load(dp + rt, col);
-            qt[i].load(qp + rt, col);
-          }
-          const f32x4 s = row_product(qr, kf), dpv = row_product(dr, vf);
-          // D and lse of query col in every lane of the column, then of the
-          // queries 4g + i whose scores this lane holds
-          float dn = 0.f;
-#pragma unroll
-          for (int n = 0; n < N; ++n) dn += dr[n] * orow[n];
-          dn = sum_over_column(dn);
-          const float l2 = lv * kLog2e;
-          if (qb + 16 <= whi) load_rows(qb + 16);
-          float p[4], ds[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int src = 4 * (4 * g + i);
-            const float di = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(dn)));
-            const float li = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(l2)));
-            const bool in = see.has(qb + 4 * g + i);
-            const float pw = fast_exp2(__builtin_fmaf(s[i], c2, -li));
-            p[i] = in ? pw : 0.f;
-            ds[i] = in ? pw * (dpv[i] - di) : 0.f;
-          }
-          col_product(dt, p, acc1);
-          col_product(qt, ds, acc0);
-        }
-      }
-    } else {
-      const size_t oo = x * a.bstride;
-      RowFrag<E, D> qf, df;
-      float dn = 0.f;
-      qf.load(q + a.qb[x] * a.bstride + own, g);
-      df.load(dout + oo + own, g);
-      {
-        RowFrag<E, D> of;
-        of.load(o + oo + own, g);
-#pragma unroll
-        for (int n = 0; n < N; ++n) dn += df[n] * of[n];
-        dn = sum_over_column(dn);
-      }
-      const float l2 = lse[x * a.lstride + min(me, last)] * kLog2e;
-      __builtin_amdgcn_s_waitcnt(0x0f70);
-      for (int i = 0; i < a.nbranch; ++i) {
-        const int lo = a.c[x] - a.ehi[i], hi = a.c[x] - a.elo[i];
-        const int wlo = max(0, r0 + lo), whi = min(last, wmax + hi);
-        if (lo > hi || wlo > whi) continue;
-        const Span win(valid, max(0, me + lo), min(last, me + hi));
-        const E *kp = k + i * a.bstride, *vp = v + i * a.bstride;
-        RowFrag<E, D> kr, vr;
-        auto load_rows = [&](int kb) {
-          const size_t rr = rows.row(kb, last);
-          kr.load(kp + rr, g);
-          vr.load(vp + rr, g);
-        };
-        load_rows(wlo);
-        for (int kb = wlo; kb <= whi; kb += 16) {
-          FeatFrag<E, D> kt[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) kt[u].load(kp + rows.frame(kb, u, last), col);
-          const f32x4 s = row_product(kr, qf), dpv = row_product(vr, df);
-          if (kb + 16 <= whi) load_rows(kb + 16);
-          float ds[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const float pw = fast_exp2(__builtin_fmaf(s[u], c2, -l2));
-            ds[u] = win.has(kb + 4 * g + u) ? pw * (dpv[u] - dn) : 0.f;
-          }
-          col_product(kt, ds, acc0);
-        }
-      }
-    }
-    if (__any(valid && !(all_finite<F>(acc0) && all_finite<F>(acc1)))) {
-      bwd_rows_slow<E, D>(a, key_role, x, b, h, r0, len, lane);
-      if (len < r1) {
-        zero_rows<D>(d0, fs, len, r1, lane);
-        if (key_role) zero_rows<D>(d1, fs, len, r1, lane);
-      }
-      continue;
-    }
-    store_own_row<D>(d0 + static_cast<ptrdiff_t>(me) * fs, acc0, a.scale, valid, me < T, g);
-    if (key_role) store_own_row<D>(d1 + static_cast<ptrdiff_t>(me) * fs, acc1, 1.f, valid, me < T, g);
+    if (key_role)
+      bwd_role<D, true>(a, sm, x, b, h, f0, len, w, lane);
+    else
+      bwd_role<D, false>(a, sm, x, b, h, f0, len, w, lane);
+    lds_barrier();  // every wave is done with the stage before the next item's
   }
 }
 
