@@ -3,21 +3,14 @@
 // softmax is online (running max and sum), so only the output rows and one
 // float log-sum-exp per row reach memory.
 //
-// bfloat16 path (MFMA): a workgroup of 4 waves owns 64 consecutive queries of
-// one (sequence, head); each wave owns 16 of them. The band of keys the tile
-// needs, [t0 + lo_off, t0 + 63 + hi_off] clipped to the valid frames, is
-// streamed through LDS in chunks of 64 frames, keys and values row-major, each
-// loaded once from HBM with 16-byte coalesced reads; the next chunk's loads are
-// issued before the current chunk is computed. The value operand of the PV
-// product, which contracts over frames, is read with the transposing LDS read
-// of gfx950, so no transposed copy is ever written. Per 32-key block a wave
-// computes S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (the 16 queries are the
-// MFMA's N dimension, so
-// every lane owns exactly one query), updates the running max/sum with two
-// cross-lane exchanges, rounds the weights to bfloat16 and accumulates
-// O^T += V^T P^T with the same MFMA. Key rows are fed to the score MFMA in a
+// bfloat16 on MFMA: a wave owns 16 queries of one (sequence, head), the N
+// dimension of S^T = K Q^T (v_mfma_f32_16x16x32_bf16), so every lane owns exactly
+// one query and the softmax statistics it needs. Keys and values are staged in
+// LDS row-major by a workgroup; the value operand of the PV product, which
+// contracts over frames, is read with the transposing LDS read of gfx950, so no
+// transposed copy is ever written. Key rows are fed to the score MFMA in a
 // permuted order so that the score tile comes out in exactly the register
-// layout the weight operand of the PV MFMA needs: no shuffles between the two
+// layout the weight operand of O^T += V^T P^T needs: no shuffles between the two
 // products.
 //
 // float tensors: band_f32.hip.
@@ -28,7 +21,6 @@ namespace sa {
 namespace {
 
 constexpr int kTq = 64;       // queries per workgroup
-constexpr int kKC = 64;       // keys per LDS chunk
 constexpr int kThreads = 256;
 constexpr int kSub = 32;      // keys per MFMA sub-block of the tile kernel
 
@@ -70,16 +62,27 @@ __device__ __forceinline__ void zero_rows_bf16(uint16_t* out, float* lse, int b,
       lse[(static_cast<size_t>(b) * H + h) * T + r_begin + r] = kNegInf;
 }
 
+// Windows too wide for the tile kernel. A workgroup owns the 64 queries of one
+// tile for one output, 16 per wave; the keys and values its windows read stream
+// through LDS in chunks of 8 KB per tensor, the next chunk's loads in flight in
+// registers while a chunk is computed, one barrier per chunk. Chunks start at the
+// first row the tile reads and segments follow each other.
+//
+// What bounds it: the chain of a block (operand reads, score product,
+// exponentials, value reads, product) at five waves per SIMD, and the first
+// chunk's latency. B = 4, T = 1000, H = 16, d = 64, a window of 490, ragged: 20.5
+// us, of which 12.4 GFLOP / 3 are 2 us of matrix instructions and 25 MB 5 us of
+// traffic; 24.0 us with row addresses formed per piece, zero-filled edges and the
+// row maximum exchanged between lanes in every block. A window of 139 (H = 12):
+// 10.7 us (11.5); two-branch LLSA, B = 3, T = 1501, H = 8, Lb = 181, La = 12: 15.6 us
+// (17.5).
 template <int D>
-__global__ __launch_bounds__(kThreads) void band_fwd_bf16_kernel(DevArgs a) {
-  constexpr int RS = D + 8;                       // LDS row stride (elements), 16-byte rows
-  constexpr int NS = D / 32;                      // MFMA k-steps over the head dim
-  constexpr int NB = D / 16;                      // 16-wide blocks of the head dim
-  constexpr int CPR = D / 8;                      // 16-byte pieces per row
-  constexpr int CPT = kKC * CPR / kThreads;       // pieces per thread per tensor per chunk
-  static_assert(CPT * kThreads == kKC * CPR, "chunk must split evenly over the threads");
-  __shared__ __attribute__((aligned(16))) uint16_t k_lds[kKC * RS];
-  __shared__ __attribute__((aligned(16))) uint16_t v_lds[kKC * RS];
+__global__ __launch_bounds__(kThreads) void band_fwd_sweep_kernel(DevArgs a) {
+  constexpr int NS = D / 32, NB = D / 16, CPR = D / 8;
+  constexpr int CH = 4096 / D;                // rows of a chunk
+  constexpr int NP = CH * CPR / kThreads;     // 16-byte pieces per thread, tensor and chunk
+  constexpr int RPT = kThreads / CPR;         // rows between a thread's pieces
+  __shared__ __attribute__((aligned(128))) uint16_t s_k[2][CH * D], s_v[2][CH * D];
 
   // items of a slice: the outputs of tile 0, of tile 1, ...; the outputs of a
   // tile read the same K/V band, which the second one finds in the XCD's L2
@@ -87,140 +90,152 @@ __global__ __launch_bounds__(kThreads) void band_fwd_bf16_kernel(DevArgs a) {
   if (!xcd_slice_item(blockIdx.x, a.B * a.H, a.njobs * a.ntiles, bh, item)) return;
   const bool second = a.njobs > 1 && (item & 1);
   const int tile = a.njobs > 1 ? item >> 1 : item;
-  const int h = bh % a.H;
-  const int b = bh / a.H;
+  const int h = bh % a.H, b = bh / a.H;
   const DevJob& job = second ? a.job1 : a.job0;
-
-  const int T = a.T, H = a.H;
-  const int len = clamp_len(a.lengths, b, T);
-  const int t0 = tile * kTq;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6;
-  const int col = lane & 15, g = lane >> 4;
-  uint16_t* out = static_cast<uint16_t*>(job.out);
-  float* lse = job.lse;
-
-  if (t0 >= len) {  // padding tile: zeros, nothing read
-    zero_rows_bf16<D>(out, lse, b, h, T, H, t0, min(t0 + kTq, T), tid);
+  const int T = a.T, H = a.H, fs = H * D;
+  const int len = clamp_len_uniform(a.lengths, b, T), last = len - 1;
+  const int f0 = tile * kTq;
+  const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint16_t* const out_all = static_cast<uint16_t*>(job.out);
+  if (f0 >= len) {  // padding tile: zeros, nothing read
+    zero_rows_bf16<D>(out_all, job.lse, b, h, T, H, f0, min(f0 + kTq, T), tid);
     return;
   }
+  const size_t slice = row_index(b, 0, h, T, H, D);
+  const int fmax = min(f0 + kTq, len) - 1;  // last valid query of the tile
 
-  const int r0 = t0 + 16 * w;   // first query of this wave
-  const int t = r0 + col;       // this lane's query
-  const bool qvalid = t < len;
-  const uint16_t* qp = static_cast<const uint16_t*>(job.q);
-  const int tmax = min(t0 + kTq, len) - 1;  // last valid query of the tile
-  const int wmax = min(r0 + 15, len - 1);   // last valid query of the wave (< r0: none)
-
-  // The chunks of every segment's band, [t0 + lo_off, tmax + hi_off] clipped,
-  // are visited as one sequence so the next chunk is always in flight.
-  int klo[2], nch[2];
-#pragma unroll
-  for (int si = 0; si < 2; ++si) {
-    const DevSeg& sg = si ? job.seg1 : job.seg0;
-    klo[si] = max(0, t0 + sg.lo_off);
-    const int khi = min(len - 1, tmax + sg.hi_off);
-    nch[si] = (si < job.nseg && klo[si] <= khi) ? (khi - klo[si] + kKC) / kKC : 0;
-  }
-  const int nchunks = nch[0] + nch[1];
-  auto chunk_seg = [&](int c) { return c < nch[0] ? 0 : 1; };
-  auto chunk_start = [&](int c) { return c < nch[0] ? klo[0] + c * kKC : klo[1] + (c - nch[0]) * kKC; };
-  auto chunk_rows = [&](int c) {
-    const int si = chunk_seg(c);
-    const DevSeg& sg = si ? job.seg1 : job.seg0;
-    return min(kKC, min(len - 1, tmax + sg.hi_off) - chunk_start(c) + 1);
+  // chunks: segment si, frames from cs on, up to frame end
+  struct Pos {
+    int si, cs, end, lo, hi;
   };
-
-  uint4 kreg[CPT], vreg[CPT];
-  auto fetch = [&](int c) {
-    const int si = chunk_seg(c);
-    const DevSeg& sg = si ? job.seg1 : job.seg0;
-    const uint16_t* kp = static_cast<const uint16_t*>(sg.k);
-    const uint16_t* vp = static_cast<const uint16_t*>(sg.v);
-    const int cs = chunk_start(c), cn = chunk_rows(c);
+  auto open = [&](Pos& p, int from) {
+    for (p.si = from; p.si < job.nseg; ++p.si) {
+      const DevSeg& sg = p.si ? job.seg1 : job.seg0;
+      p.lo = sg.lo_off;
+      p.hi = sg.hi_off;
+      const int base = f0 + p.lo, beg = max(0, base);
+      p.end = min(last, fmax + p.hi);
+      if (p.lo > p.hi || beg > p.end) continue;
+      p.cs = base + (beg - base) / CH * CH;
+      return true;
+    }
+    return false;
+  };
+  // In a chunk inside the sequence the offsets of a thread's pieces are the same
+  // every time (bytes within 32 bits: a sequence has under 2^31 elements); rows
+  // outside it are replaced by its first or last one and masked.
+  const int tr = tid / CPR;
+  uint32_t inoff[NP];
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int e = tid + i * kThreads, r = e / CPR, pc = e % CPR;
-      kreg[i] = vreg[i] = make_uint4(0, 0, 0, 0);
-      if (r < cn) {
-        const size_t off = row_index(b, cs + r, h, T, H, D) + 8 * pc;
-        kreg[i] = *reinterpret_cast<const uint4*>(kp + off);
-        vreg[i] = *reinterpret_cast<const uint4*>(vp + off);
+  for (int i = 0; i < NP; ++i)
+    inoff[i] = 2u * (static_cast<uint32_t>(tr + i * RPT) * static_cast<uint32_t>(fs) + 8u * (tid % CPR));
+  u32x4 rk[NP], rv[NP];
+  auto fetch = [&](const Pos& p) {
+    const DevSeg& sg = p.si ? job.seg1 : job.seg0;
+    const int base = min(max(p.cs, 0), last);
+    const bool inside = p.cs >= 0 && p.cs + CH - 1 <= last;
+    const size_t row = slice + static_cast<size_t>(base) * fs;
+    const char* kp = reinterpret_cast<const char*>(static_cast<const uint16_t*>(sg.k) + row);
+    const char* vp = reinterpret_cast<const char*>(static_cast<const uint16_t*>(sg.v) + row);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      uint32_t off = inoff[i];
+      if (!inside) {
+        const uint32_t d = static_cast<uint32_t>(min(max(p.cs + tr + i * RPT, 0), last) - base);
+        off = 2u * (d * static_cast<uint32_t>(fs) + 8u * (tid % CPR));
       }
+      rk[i] = ld16(kp + off);
+      rv[i] = ld16(vp + off);
     }
   };
+  Pos nxt;
+  bool more = open(nxt, 0);
+  if (more) fetch(nxt);
 
+  const int r0 = f0 + 16 * w, t = r0 + col;  // the wave's first query, the lane's query
+  const bool valid = t < len;
+  const int wmax = min(r0 + 15, last);  // last valid query of the wave (< r0: none)
   bf16x8 qf[NS];
-  if (nchunks > 0) fetch(0);
+  {
+    const uint16_t* qp = static_cast<const uint16_t*>(job.q) + slice + static_cast<size_t>(min(t, last)) * fs;
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    uint4 raw = make_uint4(0, 0, 0, 0);
-    if (qvalid) raw = *reinterpret_cast<const uint4*>(qp + row_index(b, t, h, T, H, D) + 32 * s + 8 * g);
-    qf[s] = __builtin_bit_cast(bf16x8, raw);
+    for (int j = 0; j < NS; ++j) qf[j] = __builtin_bit_cast(bf16x8, ld16(qp + 32 * j + 8 * g));
   }
-
   float m = kNegInf, lsum = 0.f;
   f32x4 acc[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  for (int c = 0; c < nchunks; ++c) {
-    __syncthreads();  // previous chunk fully consumed
+  const SubBlockAddr<D, 0> ad(lane, 0);
+  const float c2 = a.scale_log2;
+  // the queries are in before the loop: a wait for them inside it would also wait
+  // for the chunk loads issued there
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  for (int n = 0; more; ++n) {
+    const Pos cur = nxt;
+    const int buf = n & 1;
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int e = tid + i * kThreads, r = e / CPR, pc = e % CPR;
-      *reinterpret_cast<uint4*>(k_lds + r * RS + 8 * pc) = kreg[i];
-      *reinterpret_cast<uint4*>(v_lds + r * RS + 8 * pc) = vreg[i];
+    for (int i = 0; i < NP; ++i) {
+      const int o = seg_off<D>(tr + i * RPT, 8 * (tid % CPR));
+      st16(s_k[buf] + o, rk[i]);
+      st16(s_v[buf] + o, rv[i]);
     }
-    const int si = chunk_seg(c);
-    const int cs = chunk_start(c), cn = chunk_rows(c);
-    if (c + 1 < nchunks) fetch(c + 1);  // in flight while this chunk is computed
-    __syncthreads();
-
-    const DevSeg& sg = si ? job.seg1 : job.seg0;
-    const int wlo = max(0, r0 + sg.lo_off);
-    const int whi = (wmax < r0) ? -1 : min(len - 1, wmax + sg.hi_off);
-    if (wlo > whi) continue;
-    // this lane's window in the segment as (start, width): key is inside iff
-    // (unsigned)(key - qlo) <= width; an empty window never matches
-    const int qlo = qvalid ? max(0, t + sg.lo_off) : 0x7fffffff;
-    const int qhi = min(len - 1, t + sg.hi_off);
-    const uint32_t qwidth = (qvalid && qhi >= qlo) ? static_cast<uint32_t>(qhi - qlo) : 0u;
-    const int qlo_l = (qvalid && qhi >= qlo) ? qlo : 0x7fffffff;
+    // chunk n is in; every wave is done with chunk n - 1, whose buffer chunk
+    // n + 1 takes
+    lds_barrier();
+    nxt.cs += CH;
+    more = nxt.cs <= nxt.end || open(nxt, nxt.si + 1);
+    if (more) fetch(nxt);
+    const int wbeg = max(0, r0 + cur.lo), wend = wmax < r0 ? -1 : min(last, wmax + cur.hi);
+    // this lane's window as (start, width): key is inside iff unsigned(key -
+    // start) <= width; an empty window never matches
+    const int qlo = max(0, t + cur.lo), qhi = min(last, t + cur.hi);
+    const bool any = valid && qhi >= qlo;
+    const int start = any ? qlo : 1 << 30;
+    const unsigned width = any ? static_cast<unsigned>(qhi - qlo) : 0u;
     // keys inside the window of every valid query of the wave
-    const int ilo = max(0, wmax + sg.lo_off), ihi = min(len - 1, r0 + sg.hi_off);
-
-    for (int sb = 0; sb < kKC; sb += 32) {
-      const int kb = cs + sb;
-      if (sb >= cn || kb > whi || kb + 31 < wlo) continue;  // uniform over the wave
-      // score tiles: block 0 row r holds key sb + 8(r/4) + r%4, block 1 the
-      // same + 4, so lane (g, col) ends up with keys kb + 8g + 0..7
-      const int kr = sb + 8 * (col >> 2) + (col & 3);
-      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+    const int ibeg = max(0, wmax + cur.lo), iend = min(last, r0 + cur.hi);
+    const uint32_t kb0 = lds_addr(s_k[buf]) + ad.ua, vb0 = lds_addr(s_v[buf]) + ad.ut;
+#pragma unroll 1
+    for (int sb = 0; sb < CH; sb += kSub) {
+      const int kb = cur.cs + sb;
+      if (kb > wend || kb + kSub - 1 < wbeg) continue;
+      const uint32_t ka = kb0 + sb * 2 * D, va = vb0 + sb * 2 * D;
+      bf16x8 kr[2 * NS];
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_row8(k_lds + kr * RS + 32 * s + 8 * g), qf[s], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_row8(k_lds + (kr + 4) * RS + 32 * s + 8 * g), qf[s], s1, 0, 0, 0);
+      for (int j = 0; j < NS; ++j) {
+        kr[2 * j] = lds_rd8(ka ^ (64 * j));
+        kr[2 * j + 1] = lds_rd8((ka ^ (64 * j)) + 8 * D);
       }
-      float z[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]};
-      if (!(kb >= ilo && kb + 31 <= ihi)) {  // block crosses a window edge: mask
-        const int base = kb + 8 * g - qlo_l;
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+      for (int j = 0; j < NS; ++j) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[2 * j], qf[j], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[2 * j + 1], qf[j], s1, 0, 0, 0);
+      }
+      f32x8 z;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        z[j] = s0[j];
+        z[j + 4] = s1[j];
+      }
+      if (!(kb >= ibeg && kb + kSub - 1 <= iend)) {  // crosses a window edge: mask
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          z[j] = static_cast<uint32_t>(base + j) <= qwidth ? z[j] : kNegInf;
+          z[j] = static_cast<unsigned>(kb + 8 * g + j - start) <= width ? z[j] : kNegInf;
       }
-      float zmax = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])),
-                         fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
-      zmax = fmaxf(zmax, __shfl_xor(zmax, 16));
-      zmax = fmaxf(zmax, __shfl_xor(zmax, 32));
-      const float mblk = zmax * a.scale_log2;
       // Lazy rescaling: a row's exponent offset m only moves when its maximum
-      // grows by more than 2^8, so the weights stay below 256 and the
-      // accumulators are rarely touched. The decision is per row (the four
-      // lanes of a row hold the same mblk and m), so each output depends on
-      // its own window only, bit for bit.
-      const bool grow = mblk > m + 8.f;
-      if (__any(grow)) {
+      // grows by more than 2^8, so the weights stay below 256, the accumulators
+      // are rarely touched and the maximum over the row's four lanes is only
+      // taken then. The decision is per row, so each output depends on its own
+      // window only, bit for bit.
+      const float zl = fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])),
+                             fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
+      if (__any(zl * c2 > m + 8.f)) {
+        float zr = fmaxf(zl, __shfl_xor(zl, 16));
+        zr = fmaxf(zr, __shfl_xor(zr, 32));
+        const float mblk = zr * c2;
+        const bool grow = mblk > m + 8.f;
         const float mnew = grow ? mblk : m;
         const float alpha = grow ? fast_exp2(m - mnew) : 1.f;  // 0 on a row's first block
         lsum *= alpha;
@@ -228,38 +243,21 @@ __global__ __launch_bounds__(kThreads) void band_fwd_bf16_kernel(DevArgs a) {
         for (int i = 0; i < NB; ++i) acc[i] *= alpha;
         m = mnew;
       }
-      const float msafe = (m == kNegInf) ? 0.f : m;
-      float psum = 0.f;
-      bf16x8 pf;
+      const float ms = m == kNegInf ? 0.f : m;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float pw = fast_exp2(__builtin_fmaf(z[j], a.scale_log2, -msafe));
-        psum += pw;
-        pf[j] = static_cast<__bf16>(pw);
-      }
-      lsum += psum;
+      for (int j = 0; j < 8; ++j) z[j] = fast_exp2(__builtin_fmaf(z[j], c2, -ms));
+      lsum += ((z[0] + z[1]) + (z[2] + z[3])) + ((z[4] + z[5]) + (z[6] + z[7]));
+      const bf16x8 pf = __builtin_convertvector(z, bf16x8);
       // O^T += V^T P^T: lane (g, col) needs V[kb + 8g + j][16i + col]
 #pragma unroll
       for (int i = 0; i < NB; ++i)
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_col8<RS>(v_lds, sb, 16 * i, lane), pf, acc[i], 0, 0, 0);
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_tr8_at<8 * D>(va ^ (32 * i)), pf, acc[i], 0, 0, 0);
     }
   }
-
-  lsum += __shfl_xor(lsum, 16);
-  lsum += __shfl_xor(lsum, 32);
-  if (t < T) {
-    uint16_t* orow = out + row_index(b, t, h, T, H, D);
-    const float inv = qvalid ? 1.f / lsum : 0.f;
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      uint2 pk;
-      pk.x = qvalid ? pack_bf16x2(acc[i][0] * inv, acc[i][1] * inv) : 0u;
-      pk.y = qvalid ? pack_bf16x2(acc[i][2] * inv, acc[i][3] * inv) : 0u;
-      *reinterpret_cast<uint2*>(orow + 16 * i + 4 * g) = pk;
-    }
-    if (lse && g == 0)
-      lse[(static_cast<size_t>(b) * H + h) * T + t] = qvalid ? (m + log2f(lsum)) * kLn2 : kNegInf;
-  }
+  lsum = sum_over_column(lsum);
+  store_rows_direct<D>(out_all + slice, fs, r0, min(16, T - r0), acc, valid ? 1.f / lsum : 0.f, valid, lane);
+  if (job.lse && g == 0 && t < T)
+    job.lse[(static_cast<size_t>(b) * H + h) * T + t] = valid ? (m + log2f(lsum)) * kLn2 : kNegInf;
 }
 
 // ---------------------------------------------------------------------------
@@ -1190,9 +1188,9 @@ hipError_t launch_band_forward(const BandForwardArgs& a, ElemType et, hipStream_
   d.ntiles = (a.T + kTq - 1) / kTq;
   const int grid = xcd_slice_grid(a.B * a.H, a.njobs * d.ntiles);
   if (a.d == 64)
-    hipLaunchKernelGGL(band_fwd_bf16_kernel<64>, dim3(grid), dim3(kThreads), 0, stream, d);
+    hipLaunchKernelGGL(band_fwd_sweep_kernel<64>, dim3(grid), dim3(kThreads), 0, stream, d);
   else
-    hipLaunchKernelGGL(band_fwd_bf16_kernel<32>, dim3(grid), dim3(kThreads), 0, stream, d);
+    hipLaunchKernelGGL(band_fwd_sweep_kernel<32>, dim3(grid), dim3(kThreads), 0, stream, d);
   return hipGetLastError();
 }
 

@@ -61,26 +61,12 @@ __device__ __forceinline__ float dot_bf16x8(bf16x8 x, bf16x8 y, float c) {
 }
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-// MFMA operand of a product that contracts over frames, read from a row-major
-// LDS tile X (row stride RS elements) with two transposing reads
+// The transposing pattern: the MFMA operand of a product that contracts over
+// frames, read from a row-major LDS tile X with two transposing reads
 // (ds_read_b64_tr_b16): lane (g = lane/16, c = lane%16) receives
 // X[r0 + 8g + j][c0 + c] for j = 0..7. Within each 16-lane group the 4 values
 // lane 4j+q loads become element j of lanes 4q..4q+3, so lane L of the group
 // points at row r0 + 8g + L/4 (then 4 rows further), columns c0 + 4(L%4).
-template <int RS>
-__device__ __forceinline__ bf16x8 lds_col8(const uint16_t* X, int r0, int c0, int lane) {
-  const int g = lane >> 4, L = lane & 15;
-  const uint16_t* p = X + (r0 + 8 * g + (L >> 2)) * RS + c0 + 4 * (L & 3);
-  const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p));
-  const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(p + 4 * RS));
-  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
-
-// MFMA operand of a product that contracts over the head dim: 8 consecutive
-// elements of one LDS row.
-__device__ __forceinline__ bf16x8 lds_row8(const uint16_t* p) {
-  return *reinterpret_cast<const bf16x8*>(p);
-}
 
 // Band segments staged in LDS by direct global->LDS copies. One copy
 // instruction moves 16 bytes per lane and fills 1 KiB of LDS contiguously
@@ -205,7 +191,7 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) char*)p));
 }
 __device__ __forceinline__ bf16x8 lds_rd8(uint32_t a) { return *(const lds_bf16x8*)(uintptr_t)a; }
-// transposing read (the lds_col8 pattern) of rows at byte address a and of the
+// transposing read (the transposing pattern) of rows at byte address a and of the
 // rows 4 further, hi bytes on
 template <int HI>
 __device__ __forceinline__ bf16x8 lds_tr8_at(uint32_t a) {
