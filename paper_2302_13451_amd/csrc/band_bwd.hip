@@ -788,7 +788,7 @@ hipError_t launch_mfma(const SaBackwardArgs& a, hipStream_t stream) {
     }
   } else {
     // bands wider than one segment stream through LDS in chunks whose loads
-    // overlap the products: 48 us where sweeping them in staged segments took 58
+    // overlap the products: 45 us where sweeping them in staged segments took 58
     // us (B = 4, T = 1000, H = 16, d = 64, a window of 490), 24.4 against 26.4 us
     // (H = 12, a window of 139) and 10.1 against 11.5 us (B = 1, T = 200, H = 8, a
     // window of 365)

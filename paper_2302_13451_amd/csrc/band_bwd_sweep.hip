@@ -13,10 +13,11 @@
 // What bounds it: the latency of a block's chain (operand reads, score products,
 // exponentials, transposed reads, gradient products) at three waves per SIMD. At
 // B = 4, T = 1000, H = 16, d = 64, a window of 490 and ragged lengths the SA
-// backward takes 48 us (58 us with the whole band of a tile staged in segments
-// of 144 rows that nothing overlapped), its matrix instructions 7 us and its LDS
-// reads 13 us of that; 9 us per sequence more, so some 12 us are launch, first
-// chunks and the last wave of workgroups. Measured slower there: reading the
+// backward takes 45 us (58 us with the whole band of a tile staged in segments
+// of 144 rows that nothing overlapped; 48 us with a tile's roles next to each
+// other), its matrix instructions 7 us and its LDS reads 13 us of that; 9 us per
+// sequence more, so some 9 us are launch, first chunks and the last wave of
+// workgroups. Measured slower there, against 48 us: reading the
 // transposed operands ahead of the products (59 us: 201 registers, two waves per
 // SIMD), four waves per SIMD (62 us, spilling) and 32 rows per wave (51 us;
 // faster only with eight times the sequences, 290 against 303 us).
@@ -296,14 +297,10 @@ __global__ __launch_bounds__(kThreads) void band_bwd_sweep_kernel(BwdDev a) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int T = a.T, H = a.H, fs = H * D;
-  const int nroles = a.nbranch + a.nout;
   for (int bid = blockIdx.x; bid < a.items; bid += gridDim.x) {
-    // items of a slice: the key roles and query roles of tile 0, of tile 1, ...
-    int bh, item;
-    if (!xcd_slice_item(bid, a.B * H, nroles * a.ntiles, bh, item)) continue;
-    const int tile = item / nroles, role = item - tile * nroles;
-    const bool key_role = role < a.nbranch;
-    const int x = key_role ? role : role - a.nbranch;  // branch or output
+    int bh, tile, x;
+    bool key_role;
+    if (!role_item(a, bid, bh, tile, key_role, x)) continue;
     const int b = bh / H, h = bh - b * H;
     const int len = clamp_len_uniform(a.lengths, b, T);
     const int f0 = tile * TR;

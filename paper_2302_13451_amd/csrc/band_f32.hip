@@ -25,7 +25,7 @@
 // 16 lines per 16 lanes (measured straight from memory: 49 L1 accesses per
 // instruction, 31 us of accesses alone). A workgroup therefore stages the rows a
 // tile reads in LDS, 112 (d = 64) at once, two workgroups per compute unit
-// overlapping each other's staging: 47 us at the same shape, of which the matrix
+// overlapping each other's staging: 46 us at the same shape, of which the matrix
 // instructions are 14 us (512 cycles of one SIMD per product of a 16 x 16 block
 // and 64 features); the rest is the latency of staging and of a wave's four to
 // five blocks at two waves per SIMD. Straight from memory 54 us, in stages of 32
@@ -396,14 +396,10 @@ __global__ __launch_bounds__(kThreads) void band_bwd_f32_kernel(BwdDev a) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int T = a.T, H = a.H, fs = H * D;
-  const int nroles = a.nbranch + a.nout;
   for (int bid = blockIdx.x; bid < a.items; bid += gridDim.x) {
-    // items of a slice: the key roles and query roles of tile 0, of tile 1, ...
-    int bh, item;
-    if (!xcd_slice_item(bid, a.B * H, nroles * a.ntiles, bh, item)) continue;
-    const int tile = item / nroles, role = item - tile * nroles;
-    const bool key_role = role < a.nbranch;
-    const int x = key_role ? role : role - a.nbranch;  // branch or output
+    int bh, tile, x;
+    bool key_role;
+    if (!role_item(a, bid, bh, tile, key_role, x)) continue;
     const int b = bh / H, h = bh - b * H;
     const int len = clamp_len_uniform(a.lengths, b, T);
     const int f0 = tile * kTileRows;
