@@ -1750,9 +1750,9 @@ bool llsa_backward_fits(int d, int Lb, int La) {
 hipError_t launch_llsa_backward(const LlsaBackwardArgs& x, ElemType et, hipStream_t stream) {
   LlsaBwdDev a{};
   // bfloat16 windows whose bands fit the persistent kernel's rings (d = 64; up to
-  // 64 sequences, or more in several launches that are each large) or one staged segment run on bfloat16 MFMA, the rest in
-  // float32 arithmetic (the segments and origins are set whether or not the
-  // staged segment fits)
+  // 64 sequences, or more in several launches that are each large) or one staged
+  // segment run here, other windows and float32 on the any-window kernels (the
+  // segments and origins are set whether or not the staged segment fits)
   const bool staged = llsa_bwd_geometry(x.d, x.Lb, x.La, a);
   const int ntiles = (x.T + kC - 1) / kC;
   const int parts = x.B <= 64 ? 1 : persist_launches(x.B, x.H, ntiles);

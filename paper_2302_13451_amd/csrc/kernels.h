@@ -124,8 +124,8 @@ hipError_t launch_llsa_backward_general(const LlsaBackwardArgs& a, ElemType et, 
 hipError_t launch_llsa_backward_f32(const LlsaBackwardArgs& a, hipStream_t stream);
 
 // Whether the window's bands fit one staged segment of the tile kernel (the
-// bfloat16 MFMA path of launch_llsa_backward outside the persistent kernel's
-// rings; every other window runs in float32 arithmetic).
+// staged path of launch_llsa_backward outside the persistent kernel's rings;
+// every other bfloat16 window streams through LDS in chunks).
 bool llsa_backward_fits(int d, int Lb, int La);
 
 struct StreamStepArgs {

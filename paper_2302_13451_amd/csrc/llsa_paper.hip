@@ -740,7 +740,7 @@ hipError_t launch_llsa_paper_backward(const LlsaPaperBwdArgs& x, ElemType et, hi
     return launch_sa_backward(s, et, stream);
   }
   // bfloat16 windows that the band pass stages in one segment: band pass and
-  // diagonal pass on bfloat16 MFMA; the rest in float32 arithmetic
+  // diagonal pass on bfloat16 MFMA; the rest on the any-window kernels
   if (et != kBF16 || !llsa_paper_backward_fits(x.d, x.Lb, x.La))
     return launch_llsa_paper_backward_general(x, et, stream);
   hipError_t e = launch_llsa_paper_backward_band(x, stream);
