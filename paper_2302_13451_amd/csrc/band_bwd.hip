@@ -1500,10 +1500,9 @@ struct PaperBwdDev {
 // first or last frame (finite data): key rows are masked by the window
 // tests, query rows by lse = +inf. Three waves per SIMD leave the roles the
 // registers to issue every operand read of a sub-block first.
-template <int D>
+template <int D, int SEG>
 __global__ __launch_bounds__(768) void llsa_paper_bwd_band_pipe_kernel(PaperBwdDev a) {
   constexpr int NT = 768;
-  constexpr int SEG = Seg<D>::kRows;
   constexpr int NS = D / 32, NB = D / 16;
   constexpr int NB16 = SEG / 16;              // 16-row blocks of a band
   constexpr int BPL = (NB16 + 3) / 4;         // ... per loader wave
@@ -1665,18 +1664,22 @@ __global__ __launch_bounds__(768) void llsa_paper_bwd_band_pipe_kernel(PaperBwdD
 
 }  // namespace
 
+// Rows of a band: every row a wave reads lies in it, 48 + sbs + 32 nblk rows from
+// the band's origin for each output channel, and the key role's own rows 64 + La
+// + Lb.
+static long long llsa_paper_band_rows(int Lb, int La) {
+  long long rows = 64LL + La + Lb;
+  for (int rel = 0; rel <= La; ++rel) {  // channel c: c for its queries' keys, La - c for its keys' queries
+    const long long nb = (16LL + Lb + (rel & 15) + kSub - 1) / kSub;
+    const long long r = 48LL + (rel & ~15) + kSub * nb;
+    rows = rows > r ? rows : r;
+  }
+  return rows;
+}
+
 bool llsa_paper_backward_fits(int d, int Lb, int La) {
   if (La < 1) return false;
-  const int seg_rows = d == 64 ? Seg<64>::kRows : Seg<32>::kRows;
-  // every row a wave reads lies in its band: 48 + sbs + 32 nblk rows from the
-  // band's origin, and the key role's own rows 64 + A + Lb
-  auto fits = [&](long long rel) {
-    const long long nb = (16LL + Lb + (rel & 15) + kSub - 1) / kSub;
-    return 48LL + (rel & ~15LL) + kSub * nb <= seg_rows;
-  };
-  for (int c = 0; c <= La; ++c)
-    if (!fits(c) || !fits(La - c)) return false;
-  return 64LL + La + Lb <= seg_rows;
+  return llsa_paper_band_rows(Lb, La) <= (d == 64 ? Seg<64>::kRows : Seg<32>::kRows);
 }
 
 hipError_t launch_llsa_paper_backward_band(const LlsaPaperBwdArgs& x, hipStream_t stream) {
@@ -1704,10 +1707,20 @@ hipError_t launch_llsa_paper_backward_band(const LlsaPaperBwdArgs& x, hipStream_
   a.scale_log2 = kLog2e * a.scale;
   a.log2_scale = -0.5f * log2f(static_cast<float>(x.d));
   const int grid = xcd_slice_grid(x.B * x.H, a.ntiles);
-  if (x.d == 64)
-    hipLaunchKernelGGL(llsa_paper_bwd_band_pipe_kernel<64>, dim3(grid), dim3(768), 0, stream, a);
-  else
-    hipLaunchKernelGGL(llsa_paper_bwd_band_pipe_kernel<32>, dim3(grid), dim3(768), 0, stream, a);
+  // An instance per row number: the loaders copy whole bands, so the rows past
+  // what a window reads cost their copies. Both passes at B = 64, T = 400, H = 8, d
+  // = 32, Lb = 64, La = 8: 505 us with 288 rows, 429 us with 144; B = 48, T = 300, H
+  // = 12, d = 64, Lb = 32, La = 8: 558 us with 144, 523 us with 112.
+  const long long rows = llsa_paper_band_rows(x.Lb, x.La);
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(768), 0, stream, a); };
+  if (x.d == 64) {
+    if (rows <= 112) launch(llsa_paper_bwd_band_pipe_kernel<64, 112>);
+    else launch(llsa_paper_bwd_band_pipe_kernel<64, Seg<64>::kRows>);
+  } else {
+    if (rows <= 112) launch(llsa_paper_bwd_band_pipe_kernel<32, 112>);
+    else if (rows <= 144) launch(llsa_paper_bwd_band_pipe_kernel<32, 144>);
+    else launch(llsa_paper_bwd_band_pipe_kernel<32, Seg<32>::kRows>);
+  }
   return hipGetLastError();
 }
 
