@@ -5,10 +5,10 @@
 //     segment;
 //   * La single frames tau = t+c-c' from channels c' = 0 .. La-1 (one per
 //     channel, on a diagonal).
-// bfloat16 with 1 <= La <= 15 and Lb < 80 runs one pass
+// bfloat16 with 1 <= La <= 16 and Lb < 80 runs one pass
 // (llsa_paper_fwd_fused_kernel): the queries (c, s - c) of an anti-diagonal
 // group s share one band, so a group is one dense block under one softmax,
-// and the final lse is written directly. Otherwise (float32, La > 15 or
+// and the final lse is written directly. Otherwise (float32, La > 16 or
 // Lb >= 80) the band forward computes each channel's band part with its
 // log-sum-exp, and a merge pass adds the diagonal frames (on MFMA for
 // La <= 15, on the vector ALUs beyond) and joins the two parts through their
@@ -290,6 +290,12 @@ __global__ __launch_bounds__(256) void llsa_paper_bwd_diag_kernel(PaperDiagDev a
 
 constexpr int kDiagWaves = 4;  // waves per workgroup, one group each
 constexpr int kMaxMfmaLa = 15;  // A + 1 queries and A keys fit one 16 x 16 tile
+// WIDE kernels: A = 16 keys still fill one tile, and the 17 queries take two, the
+// second with one query. Their weights enter the products as bfloat16 hi + lo:
+// this look-ahead ran on the vector ALUs with float32 weights before, 1030 us
+// forward and 3070 us backward at B = 16, T = 800, H = 12, d = 64, Lb = 48, now 402
+// and 1005 us (Lb = 32, B = 4, T = 300, H = 4: 105 and 121 us, now 53 and 53 us).
+constexpr int kWideLa = 16;
 
 template <int D>
 __device__ __forceinline__ bf16x8 ld_row8(const uint16_t* p, bool ok) {
@@ -318,11 +324,33 @@ __device__ __forceinline__ bf16x8 tile_tr(const uint16_t* tile, int f0, int col,
   return __builtin_shufflevector(x, bf16x4{}, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// The same with each row twice: the A operand of weights split in hi and lo.
+template <int D, bool SPLIT>
+__device__ __forceinline__ bf16x8 tile_tr_for(const uint16_t* tile, int f0, int col, int g) {
+  const bf16x8 x = tile_tr<D>(tile, f0, col, g);
+  return SPLIT ? __builtin_shufflevector(x, x, 0, 1, 2, 3, 0, 1, 2, 3) : x;
+}
+
 // Four values of a score-shaped tile as the B operand (k = 8g + e, e < 4),
 // rounded to bfloat16 in pairs.
 __device__ __forceinline__ bf16x8 as_b4(const float* x) {
   const uint32_t lo = pack_bf16x2(x[0], x[1]), hi = pack_bf16x2(x[2], x[3]);
   return __builtin_bit_cast(bf16x8, u32x4{lo, hi, 0u, 0u});
+}
+
+// SPLIT: each value as the sum of two bfloat16, the rounding's remainder in the
+// half of the operand that is zero otherwise (tile_tr_for repeats the rows), so
+// that a product keeps 16 bits of its weights at no more instructions.
+template <bool SPLIT>
+__device__ __forceinline__ bf16x8 weights_b4(const float* x) {
+  const bf16x8 b = as_b4(x);
+  if constexpr (!SPLIT) return b;
+  const u32x4 u = __builtin_bit_cast(u32x4, b);
+  float r[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    r[e] = x[e] - __uint_as_float(e & 1 ? u[e >> 1] & 0xffff0000u : u[e >> 1] << 16);
+  return __builtin_bit_cast(bf16x8, u32x4{u[0], u[1], pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3])});
 }
 
 __device__ __forceinline__ void wave_sync() {
@@ -433,7 +461,7 @@ __global__ __launch_bounds__(64 * kDiagWaves) void llsa_paper_merge_mfma_kernel(
   }
 }
 
-// The whole forward in one pass (bfloat16, La <= 15, Lb < 16 kMaxBandBlocks):
+// The whole forward in one pass (bfloat16, La <= 16, Lb < 16 kMaxBandBlocks):
 // within an anti-diagonal group (b, s, h) every query (c, s - c) reads the same
 // band, frames s - A - Lb .. s - A of channel A, besides the diagonal keys
 // (c', s - c'), c' < A. So a group is one dense block of A + 1 queries against
@@ -449,7 +477,7 @@ constexpr int kMaxBandBlocks = 5;
 constexpr int kFusedRows = 64 + 16 * kMaxBandBlocks;  // staged band rows (64 + Lb <= this)
 constexpr int kFusedWaves = 8;  // waves per workgroup of the one-pass forward
 
-template <int D>
+template <int D, bool WIDE>
 __global__ __launch_bounds__(64 * kFusedWaves) void llsa_paper_fwd_fused_kernel(PaperMergeDev a) {
   constexpr int NS = D / 32, NF = D / 16, NKB = kMaxBandBlocks, KS = D + 8, VS = D + 4;
   __shared__ __attribute__((aligned(16))) uint16_t s_k[kFusedRows * KS];
@@ -469,7 +497,6 @@ __global__ __launch_bounds__(64 * kFusedWaves) void llsa_paper_fwd_fused_kernel(
   const uint16_t* v = static_cast<const uint16_t*>(a.v);
   uint16_t* out = static_cast<uint16_t*>(a.out);
   const float c2 = a.scale * kLog2e;  // score scale, in the exponent's base 2
-  const size_t coff = col * cs, loff = col * ls;  // the lane's channel
   constexpr int CPR = D / 8;  // 16-byte pieces per row
   for (long long it = blockIdx.x; it < items; it += gridDim.x) {
     const int h = static_cast<int>(it % H);
@@ -500,13 +527,18 @@ __global__ __launch_bounds__(64 * kFusedWaves) void llsa_paper_fwd_fused_kernel(
     }
     __syncthreads();
     const int s1 = min(s0 + 64, S);
-    for (int sd = s0 + w; sd < s1; sd += kFusedWaves) {
-      const int tc = sd - col;  // frame of query col and of diagonal key col
-      const bool qrow = col <= A && tc >= 0 && tc < T;  // a row this group writes
+    constexpr int STEP = WIDE ? 2 : 1;  // items of a group: 16 queries each
+    for (int si = STEP * (s0 + w); si < STEP * s1; si += si % STEP ? STEP * kFusedWaves - 1 : WIDE ? 1 : kFusedWaves) {
+      const int sd = si / STEP;
+      const int qc = col + 16 * (si % STEP);  // channel of the lane's query
+      const int tc = sd - qc;                 // and its frame
+      const int tk = sd - col;                // frame of diagonal key col
+      const bool qrow = qc <= A && tc >= 0 && tc < T;  // a row this group writes
       const bool qv = qrow && tc < len;
-      const bool kv = col < A && tc >= 0 && tc < len;
-      const size_t crow = coff + row_index(b, tc, h, T, H, D);
-      float* const lrow = a.lse + loff + (static_cast<size_t>(b) * H + h) * T + tc;
+      const bool kv = col < A && tk >= 0 && tk < len;
+      const size_t crow = qc * cs + row_index(b, tc, h, T, H, D);
+      const size_t krow = col * cs + row_index(b, tk, h, T, H, D);
+      float* const lrow = a.lse + qc * ls + (static_cast<size_t>(b) * H + h) * T + tc;
       if (sd - A >= len) {
         // every query of the group lies past the sequence's end: zero rows
         if (qrow) {
@@ -555,8 +587,8 @@ __global__ __launch_bounds__(64 * kFusedWaves) void llsa_paper_fwd_fused_kernel(
         f32x4 st = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s2 = 0; s2 < NS; ++s2) {
-          dv[s2] = ld_row8<D>(v + crow + 32 * s2 + 8 * g, kv);
-          st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld_row8<D>(k + crow + 32 * s2 + 8 * g, kv), qa[s2], st, 0, 0,
+          dv[s2] = ld_row8<D>(v + krow + 32 * s2 + 8 * g, kv);
+          st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ld_row8<D>(k + krow + 32 * s2 + 8 * g, kv), qa[s2], st, 0, 0,
                                                        0);
         }
 #pragma unroll
@@ -593,10 +625,11 @@ __global__ __launch_bounds__(64 * kFusedWaves) void llsa_paper_fwd_fused_kernel(
       for (int kb = 0; kb <= NKB; ++kb) {
         if (kb < NKB && kb >= nkb) continue;
         const uint16_t* tile = kb < NKB ? s_v + (rb0 + 16 * kb) * VS : sv;
-        const bf16x8 pb = as_b4(sc[kb]);
+        const bf16x8 pb = weights_b4<WIDE>(sc[kb]);
 #pragma unroll
         for (int fb = 0; fb < NF; ++fb)
-          acc[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_tr<D>(tile, 16 * fb, col, g), pb, acc[fb], 0, 0, 0);
+          acc[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_tr_for<D, WIDE>(tile, 16 * fb, col, g), pb, acc[fb], 0, 0,
+                                                            0);
       }
       wave_sync();  // the tile is rewritten by the next group
       // lane (i, g) holds features 16 fb + 4g .. + 3 of query i; the row goes
@@ -607,9 +640,9 @@ __global__ __launch_bounds__(64 * kFusedWaves) void llsa_paper_fwd_fused_kernel(
   }
 }
 
-template <int D>
-__global__ __launch_bounds__(64 * kDiagWaves) __attribute__((amdgpu_waves_per_eu(5))) void llsa_paper_bwd_diag_mfma_kernel(PaperDiagDev a) {
-  constexpr int NS = D / 32, NF = D / 16, TS = 16 * (D + 4);
+template <int D, bool WIDE>
+__global__ __launch_bounds__(64 * kDiagWaves) __attribute__((amdgpu_waves_per_eu(WIDE ? 4 : 5))) void llsa_paper_bwd_diag_mfma_kernel(PaperDiagDev a) {
+  constexpr int NS = D / 32, NF = D / 16, TS = 16 * (D + 4), NQB = WIDE ? 2 : 1;
   __shared__ __attribute__((aligned(16))) uint16_t s_tile[kDiagWaves][3 * TS];  // q, k, dout rows
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int col = lane & 15, g = lane >> 4;
@@ -621,8 +654,13 @@ __global__ __launch_bounds__(64 * kDiagWaves) __attribute__((amdgpu_waves_per_eu
   const size_t cs = static_cast<size_t>(a.B) * T * H * D;
   const size_t ls = static_cast<size_t>(a.B) * H * T;
   const float scale = a.scale;
-  for (long long gi = static_cast<long long>(blockIdx.x) * kDiagWaves + w; gi < ngroups;
-       gi += static_cast<long long>(gridDim.x) * kDiagWaves) {
+  for (long long gf = static_cast<long long>(blockIdx.x) * kDiagWaves + w; gf < ngroups;
+       gf += static_cast<long long>(gridDim.x) * kDiagWaves) {
+    // from the last group to the first: the band pass went the other way, and
+    // its last rows are still in the Infinity Cache (508 to 500 us for the two
+    // passes at B = 16, T = 800, H = 12, d = 64, Lb = 64, La = 8; running both
+    // passes on half of the sequences at a time, 517 us, a quarter, 536 us)
+    const long long gi = ngroups - 1 - gf;
     const int h = static_cast<int>(gi % H);
     const int sd = static_cast<int>((gi / H) % S);
     const int b = static_cast<int>(gi / (static_cast<long long>(H) * S));
@@ -631,100 +669,112 @@ __global__ __launch_bounds__(64 * kDiagWaves) __attribute__((amdgpu_waves_per_eu
       len = a.lengths[b];
       len = len < 0 ? 0 : (len > T ? T : len);
     }
-    const int tc = sd - col;  // frame of query col and of key col
-    const bool qv = col <= A && tc >= 0 && tc < len;
-    const bool kv = col < A && tc >= 0 && tc < len;
-    const size_t row = col * cs + row_index(b, tc, h, T, H, D);
+    const int tk = sd - col;  // frame of key col
+    const bool kv = col < A && tk >= 0 && tk < len;
+    const size_t krow = col * cs + row_index(b, tk, h, T, H, D);
+    const int po = row_piece_offset(g);
     if (sd - A >= len) {
       // every query and key of the group lies past the sequence's end: dq
       // gets nothing, the key rows are zero
-      if (col < A && tc < T) {
+      if (col < A && tk < T) {
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
-          st16(a.dk + row + 32 * j + row_piece_offset(g), kZero16);
-          st16(a.dv + row + 32 * j + row_piece_offset(g), kZero16);
+          st16(a.dk + krow + 32 * j + po, kZero16);
+          st16(a.dv + krow + 32 * j + po, kZero16);
         }
       }
       continue;
     }
-    bf16x8 qa[NS], da[NS], ka[NS], va[NS];
-    float dn = 0.f;
-#pragma unroll
-    for (int s2 = 0; s2 < NS; ++s2) {
-      const int c0 = 32 * s2 + 8 * g;
-      qa[s2] = ld_row8<D>(a.q + row + c0, qv);
-      da[s2] = ld_row8<D>(a.dout + row + c0, qv);
-      ka[s2] = ld_row8<D>(a.k + row + c0, kv);
-      va[s2] = ld_row8<D>(a.v + row + c0, kv);
-      dn = dot_bf16x8(da[s2], ld_row8<D>(a.o + row + c0, qv), dn);
-    }
-    // the band pass's part of dq of query col, loaded with the operands so
-    // that its latency overlaps theirs (every query row belongs to exactly
-    // one group, so no other wave writes it): 16-byte pieces 32 j + po
-    const int po = row_piece_offset(g);
-    u32x4 dq0[NS];
-#pragma unroll
-    for (int j = 0; j < NS; ++j) dq0[j] = qv ? ld16(a.dq + row + 32 * j + po) : u32x4{0u, 0u, 0u, 0u};
-    dn += __shfl_xor(dn, 16, 64);
-    dn += __shfl_xor(dn, 32, 64);  // D of query col
-    const float lse = qv ? a.lse[col * ls + (static_cast<size_t>(b) * H + h) * T + tc] : 0.f;
-#pragma unroll
-    for (int s2 = 0; s2 < NS; ++s2) {
-      stage8<D>(sq, col, 32 * s2 + 8 * g, qa[s2]);
-      stage8<D>(sk, col, 32 * s2 + 8 * g, ka[s2]);
-      stage8<D>(sdo, col, 32 * s2 + 8 * g, da[s2]);
-    }
-    f32x4 st = {0.f, 0.f, 0.f, 0.f}, dpt = st, sq4 = st, dp = st;
-#pragma unroll
-    for (int s2 = 0; s2 < NS; ++s2) {
-      st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[s2], qa[s2], st, 0, 0, 0);   // S^T
-      dpt = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[s2], da[s2], dpt, 0, 0, 0); // dP^T
-      sq4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[s2], ka[s2], sq4, 0, 0, 0); // S
-      dp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(da[s2], va[s2], dp, 0, 0, 0);   // dP
-    }
-    // S^T layout, lane (i = col, g): pairs (i, j = 4g + e); S layout, lane
-    // (j = col, g): pairs (i = 4g + e, j)
-    float dst[4], ds[4], pw[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = 4 * g + e, tr = sd - r;
-      const bool rq = r <= A && tr >= 0 && tr < len;  // query r
-      const bool rk = r < A && tr >= 0 && tr < len;   // key r
-      const float lse_r = __shfl(lse, r, 64), dn_r = __shfl(dn, r, 64);
-      const float p_t = qv && rk ? __expf(st[e] * scale - lse) : 0.f;
-      dst[e] = p_t * (dpt[e] - dn);
-      pw[e] = rq && kv ? __expf(sq4[e] * scale - lse_r) : 0.f;
-      ds[e] = pw[e] * (dp[e] - dn_r);
-    }
-    const bf16x8 bdst = as_b4(dst), bds = as_b4(ds), bp = as_b4(pw);
-    wave_sync();
-    const bool kout = col < A && tc >= 0 && tc < T;  // a key row of this group (zeros past the length)
-    // dk, dv and dq in turn (rows written as 16-byte pieces: lanes g, g ^ 1
-    // swap their halves)
-    f32x4 gx[NF];
+    const bool kout = col < A && tk >= 0 && tk < T;  // a key row of this group (zeros past the length)
+    bf16x8 ka[NS], va[NS];
+    f32x4 gk[NF], gv[NF];
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int fb = 0; fb < NF; ++fb)
-      gx[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_tr<D>(sq, 16 * fb, col, g), bds, z, 0, 0, 0);
-    store_rows_at<D>(a.dk + row, po, kout, gx, scale, kv, lane);
+    for (int qb = 0; qb < NQB; ++qb) {  // queries 16 qb ..
+      const int c = 16 * qb + col, tc = sd - c;  // the lane's query
+      const bool qv = c <= A && tc >= 0 && tc < len;
+      const size_t row = c * cs + row_index(b, tc, h, T, H, D);
+      bf16x8 qa[NS], da[NS];
+      float dn = 0.f;
 #pragma unroll
-    for (int fb = 0; fb < NF; ++fb)
-      gx[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_tr<D>(sdo, 16 * fb, col, g), bp, z, 0, 0, 0);
-    store_rows_at<D>(a.dv + row, po, kout, gx, 1.f, kv, lane);
+      for (int s2 = 0; s2 < NS; ++s2) {
+        const int c0 = 32 * s2 + 8 * g;
+        qa[s2] = ld_row8<D>(a.q + row + c0, qv);
+        da[s2] = ld_row8<D>(a.dout + row + c0, qv);
+        if (qb == 0) {
+          ka[s2] = ld_row8<D>(a.k + krow + c0, kv);
+          va[s2] = ld_row8<D>(a.v + krow + c0, kv);
+        }
+        dn = dot_bf16x8(da[s2], ld_row8<D>(a.o + row + c0, qv), dn);
+      }
+      // the band pass's part of dq of the lane's query, loaded with the operands
+      // so that its latency overlaps theirs (every query row belongs to exactly
+      // one group, so no other wave writes it): 16-byte pieces 32 j + po
+      u32x4 dq0[NS];
 #pragma unroll
-    for (int fb = 0; fb < NF; ++fb)
-      gx[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_tr<D>(sk, 16 * fb, col, g), bdst, z, 0, 0, 0);
-    f32x8 pq[NS];
-    rows_to_pieces<D>(gx, pq);
-    if (qv) {
+      for (int j = 0; j < NS; ++j) dq0[j] = qv ? ld16(a.dq + row + 32 * j + po) : u32x4{0u, 0u, 0u, 0u};
+      dn += __shfl_xor(dn, 16, 64);
+      dn += __shfl_xor(dn, 32, 64);  // D of the lane's query
+      const float lse = qv ? a.lse[c * ls + (static_cast<size_t>(b) * H + h) * T + tc] : 0.f;
+      if (qb > 0) wave_sync();  // the tiles are rewritten
 #pragma unroll
-      for (int j = 0; j < NS; ++j) {
-        u32x4 o;
+      for (int s2 = 0; s2 < NS; ++s2) {
+        stage8<D>(sq, col, 32 * s2 + 8 * g, qa[s2]);
+        if (qb == 0) stage8<D>(sk, col, 32 * s2 + 8 * g, ka[s2]);
+        stage8<D>(sdo, col, 32 * s2 + 8 * g, da[s2]);
+      }
+      f32x4 st = {0.f, 0.f, 0.f, 0.f}, dpt = st, sq4 = st, dp = st;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          o[e] = pack_bf16x2(__uint_as_float(dq0[j][e] << 16) + scale * pq[j][2 * e],
-                             __uint_as_float(dq0[j][e] & 0xffff0000u) + scale * pq[j][2 * e + 1]);
-        st16(a.dq + row + 32 * j + po, o);
+      for (int s2 = 0; s2 < NS; ++s2) {
+        st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[s2], qa[s2], st, 0, 0, 0);   // S^T
+        dpt = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[s2], da[s2], dpt, 0, 0, 0); // dP^T
+        sq4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[s2], ka[s2], sq4, 0, 0, 0); // S
+        dp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(da[s2], va[s2], dp, 0, 0, 0);   // dP
+      }
+      // S^T layout, lane (i = col, g): pairs (i, j = 4g + e); S layout, lane
+      // (j = col, g): pairs (i = 4g + e, j)
+      float dst[4], ds[4], pw[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 4 * g + e, tr = sd - r, rqc = 16 * qb + r, tq = sd - rqc;
+        const bool rq = rqc <= A && tq >= 0 && tq < len;  // query r of the block
+        const bool rk = r < A && tr >= 0 && tr < len;     // key r
+        const float lse_r = __shfl(lse, r, 64), dn_r = __shfl(dn, r, 64);
+        const float p_t = qv && rk ? __expf(st[e] * scale - lse) : 0.f;
+        dst[e] = p_t * (dpt[e] - dn);
+        pw[e] = rq && kv ? __expf(sq4[e] * scale - lse_r) : 0.f;
+        ds[e] = pw[e] * (dp[e] - dn_r);
+      }
+      const bf16x8 bdst = weights_b4<WIDE>(dst), bds = weights_b4<WIDE>(ds), bp = weights_b4<WIDE>(pw);
+      wave_sync();
+      // dk, dv and dq in turn (rows written as 16-byte pieces: lanes g, g ^ 1
+      // swap their halves)
+#pragma unroll
+      for (int fb = 0; fb < NF; ++fb)
+        gk[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_tr_for<D, WIDE>(sq, 16 * fb, col, g), bds,
+                                                         qb ? gk[fb] : z, 0, 0, 0);
+      if (qb == NQB - 1) store_rows_at<D>(a.dk + krow, po, kout, gk, scale, kv, lane);
+#pragma unroll
+      for (int fb = 0; fb < NF; ++fb)
+        gv[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_tr_for<D, WIDE>(sdo, 16 * fb, col, g), bp,
+                                                         qb ? gv[fb] : z, 0, 0, 0);
+      if (qb == NQB - 1) store_rows_at<D>(a.dv + krow, po, kout, gv, 1.f, kv, lane);
+      f32x4 gx[NF];
+#pragma unroll
+      for (int fb = 0; fb < NF; ++fb)
+        gx[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_tr_for<D, WIDE>(sk, 16 * fb, col, g), bdst, z, 0, 0, 0);
+      f32x8 pq[NS];
+      rows_to_pieces<D>(gx, pq);
+      if (qv) {
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+          u32x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            o[e] = pack_bf16x2(__uint_as_float(dq0[j][e] << 16) + scale * pq[j][2 * e],
+                               __uint_as_float(dq0[j][e] & 0xffff0000u) + scale * pq[j][2 * e + 1]);
+          st16(a.dq + row + 32 * j + po, o);
+        }
       }
     }
     wave_sync();  // the tiles are rewritten by the next group
@@ -761,14 +811,18 @@ hipError_t launch_llsa_paper_backward(const LlsaPaperBwdArgs& x, ElemType et, hi
   m.La = x.La;
   m.lengths = x.lengths;
   m.scale = 1.f / sqrtf(static_cast<float>(x.d));
-  if (x.La <= kMaxMfmaLa) {  // one wave per anti-diagonal group
+  if (x.La <= kWideLa) {  // one wave per anti-diagonal group
     const long long groups = static_cast<long long>(x.B) * (x.T + x.La) * x.H;
     const long long blocks = (groups + kDiagWaves - 1) / kDiagWaves;
     const int grid = static_cast<int>(blocks < 65536 ? blocks : 65536);
-    if (x.d == 64)
-      hipLaunchKernelGGL(llsa_paper_bwd_diag_mfma_kernel<64>, dim3(grid), dim3(64 * kDiagWaves), 0, stream, m);
+    if (x.d == 64 && x.La <= kMaxMfmaLa)
+      hipLaunchKernelGGL((llsa_paper_bwd_diag_mfma_kernel<64, false>), dim3(grid), dim3(64 * kDiagWaves), 0, stream, m);
+    else if (x.d == 64)
+      hipLaunchKernelGGL((llsa_paper_bwd_diag_mfma_kernel<64, true>), dim3(grid), dim3(64 * kDiagWaves), 0, stream, m);
+    else if (x.La <= kMaxMfmaLa)
+      hipLaunchKernelGGL((llsa_paper_bwd_diag_mfma_kernel<32, false>), dim3(grid), dim3(64 * kDiagWaves), 0, stream, m);
     else
-      hipLaunchKernelGGL(llsa_paper_bwd_diag_mfma_kernel<32>, dim3(grid), dim3(64 * kDiagWaves), 0, stream, m);
+      hipLaunchKernelGGL((llsa_paper_bwd_diag_mfma_kernel<32, true>), dim3(grid), dim3(64 * kDiagWaves), 0, stream, m);
     return hipGetLastError();
   }
   const long long rows = static_cast<long long>(2 * x.La + 1) * x.B * (x.T + x.La) * x.H;
@@ -783,15 +837,19 @@ hipError_t launch_llsa_paper_backward(const LlsaPaperBwdArgs& x, ElemType et, hi
 
 hipError_t launch_llsa_paper_forward(const LlsaPaperArgs& x, ElemType et, hipStream_t stream) {
   const int A = x.La;
-  if (et == kBF16 && A >= 1 && A <= kMaxMfmaLa && x.Lb < 16 * kMaxBandBlocks) {  // one pass
+  if (et == kBF16 && A >= 1 && A <= kWideLa && x.Lb < 16 * kMaxBandBlocks) {  // one pass
     PaperMergeDev m{x.q, x.k, x.v, x.out, x.lse, x.B, x.T, x.H, A, x.lengths,
                     1.f / sqrtf(static_cast<float>(x.d)), x.Lb};
     const long long items = static_cast<long long>(x.B) * x.H * ((x.T + A + 63) / 64);
     const int grid = static_cast<int>(items < 65536 ? items : 65536);
-    if (x.d == 64)
-      hipLaunchKernelGGL(llsa_paper_fwd_fused_kernel<64>, dim3(grid), dim3(64 * kFusedWaves), 0, stream, m);
+    if (x.d == 64 && A <= kMaxMfmaLa)
+      hipLaunchKernelGGL((llsa_paper_fwd_fused_kernel<64, false>), dim3(grid), dim3(64 * kFusedWaves), 0, stream, m);
+    else if (x.d == 64)
+      hipLaunchKernelGGL((llsa_paper_fwd_fused_kernel<64, true>), dim3(grid), dim3(64 * kFusedWaves), 0, stream, m);
+    else if (A <= kMaxMfmaLa)
+      hipLaunchKernelGGL((llsa_paper_fwd_fused_kernel<32, false>), dim3(grid), dim3(64 * kFusedWaves), 0, stream, m);
     else
-      hipLaunchKernelGGL(llsa_paper_fwd_fused_kernel<32>, dim3(grid), dim3(64 * kFusedWaves), 0, stream, m);
+      hipLaunchKernelGGL((llsa_paper_fwd_fused_kernel<32, true>), dim3(grid), dim3(64 * kFusedWaves), 0, stream, m);
     return hipGetLastError();
   }
   const size_t cstride = static_cast<size_t>(x.B) * x.T * x.H * x.d * (et == kBF16 ? 2 : 4);
