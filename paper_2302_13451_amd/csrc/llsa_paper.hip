@@ -11,7 +11,7 @@
 // and the final lse is written directly. Otherwise (float32, La > 16 or
 // Lb >= 80) the band forward computes each channel's band part with its
 // log-sum-exp, and a merge pass adds the diagonal frames (on MFMA for
-// La <= 15, on the vector ALUs beyond) and joins the two parts through their
+// La <= 16, on the vector ALUs beyond) and joins the two parts through their
 // log-sum-exps. Rows t >= len get zero output and lse = -inf.
 #include "device_common.h"
 #include "kernels.h"
@@ -359,7 +359,7 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int D>
+template <int D, bool WIDE>
 __global__ __launch_bounds__(64 * kDiagWaves) void llsa_paper_merge_mfma_kernel(PaperMergeDev a) {
   constexpr int NS = D / 32, NF = D / 16;
   __shared__ __attribute__((aligned(16))) uint16_t s_tile[kDiagWaves][16 * (D + 4)];
@@ -375,8 +375,10 @@ __global__ __launch_bounds__(64 * kDiagWaves) void llsa_paper_merge_mfma_kernel(
   const uint16_t* v = static_cast<const uint16_t*>(a.v);
   uint16_t* out = static_cast<uint16_t*>(a.out);
   const float scale = a.scale;
-  for (long long gi = static_cast<long long>(blockIdx.x) * kDiagWaves + w; gi < ngroups;
-       gi += static_cast<long long>(gridDim.x) * kDiagWaves) {
+  constexpr int NQB = WIDE ? 2 : 1;  // items of a group: 16 queries each
+  for (long long it = static_cast<long long>(blockIdx.x) * kDiagWaves + w; it < NQB * ngroups;
+       it += static_cast<long long>(gridDim.x) * kDiagWaves) {
+    const long long gi = it / NQB;
     const int h = static_cast<int>(gi % H);
     const int sd = static_cast<int>((gi / H) % S);
     const int b = static_cast<int>(gi / (static_cast<long long>(H) * S));
@@ -385,18 +387,20 @@ __global__ __launch_bounds__(64 * kDiagWaves) void llsa_paper_merge_mfma_kernel(
       len = a.lengths[b];
       len = len < 0 ? 0 : (len > T ? T : len);
     }
-    const int tc = sd - col;  // frame of query col and of key col
-    const bool qv = col <= A && tc >= 0 && tc < len;
-    const bool kv = col < A && tc >= 0 && tc < len;
-    const size_t qrow = col * cs + row_index(b, tc, h, T, H, D);
+    const int qc = col + 16 * static_cast<int>(it % NQB);  // channel of the lane's query
+    const int tc = sd - qc, tk = sd - col;                 // its frame, and that of key col
+    const bool qv = qc <= A && tc >= 0 && tc < len;
+    const bool kv = col < A && tk >= 0 && tk < len;
+    const size_t qrow = qc * cs + row_index(b, tc, h, T, H, D);
+    const size_t krow = col * cs + row_index(b, tk, h, T, H, D);
     bf16x8 qa[NS], ka[NS], va[NS];
 #pragma unroll
     for (int s2 = 0; s2 < NS; ++s2) {
       qa[s2] = ld_row8<D>(q + qrow + 32 * s2 + 8 * g, qv);
-      ka[s2] = ld_row8<D>(k + qrow + 32 * s2 + 8 * g, kv);
-      va[s2] = ld_row8<D>(v + qrow + 32 * s2 + 8 * g, kv);
+      ka[s2] = ld_row8<D>(k + krow + 32 * s2 + 8 * g, kv);
+      va[s2] = ld_row8<D>(v + krow + 32 * s2 + 8 * g, kv);
     }
-    float* lp = a.lse + col * ls + (static_cast<size_t>(b) * H + h) * T + tc;
+    float* lp = a.lse + qc * ls + (static_cast<size_t>(b) * H + h) * T + tc;
     const float lb = qv ? *lp : kNegInf;
     // the band part of the output row, 16-byte pieces 32 j + po
     const int po = row_piece_offset(g);
@@ -429,15 +433,15 @@ __global__ __launch_bounds__(64 * kDiagWaves) void llsa_paper_merge_mfma_kernel(
     ps += __shfl_xor(ps, 32, 64);
     const float wb = lb == kNegInf ? 0.f : __expf(lb - m);  // the band part's weight
     const float den = wb + ps;
-    const bf16x8 pb = as_b4(p);
+    const bf16x8 pb = weights_b4<WIDE>(p);
     wave_sync();
     // lane (i, g) holds features 16 fb + 4g .. + 3 of query i in y[fb]; the
     // row goes out as 16-byte pieces (lanes g, g ^ 1 swap their halves)
     f32x4 y[NF];
 #pragma unroll
     for (int fb = 0; fb < NF; ++fb)
-      y[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_tr<D>(sv, 16 * fb, col, g), pb, f32x4{0.f, 0.f, 0.f, 0.f},
-                                                      0, 0, 0);
+      y[fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tile_tr_for<D, WIDE>(sv, 16 * fb, col, g), pb,
+                                                      f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
     f32x8 yp[NS];
     rows_to_pieces<D>(y, yp);
     if (qv) {
@@ -875,14 +879,18 @@ hipError_t launch_llsa_paper_forward(const LlsaPaperArgs& x, ElemType et, hipStr
   if (A == 0) return hipSuccess;  // one channel: the band is the whole window
   PaperMergeDev m{x.q, x.k, x.v, x.out, x.lse, x.B, x.T, x.H, A, x.lengths, 1.f / sqrtf(static_cast<float>(x.d)),
                   x.Lb};
-  if (et == kBF16 && A <= kMaxMfmaLa) {  // one wave per anti-diagonal group
-    const long long groups = static_cast<long long>(x.B) * (x.T + A) * x.H;
+  if (et == kBF16 && A <= kWideLa) {  // one wave per 16 queries of an anti-diagonal group
+    const long long groups = static_cast<long long>(x.B) * (x.T + A) * x.H * (A <= kMaxMfmaLa ? 1 : 2);
     const long long blocks = (groups + kDiagWaves - 1) / kDiagWaves;
     const int grid = static_cast<int>(blocks < 65536 ? blocks : 65536);
-    if (x.d == 64)
-      hipLaunchKernelGGL(llsa_paper_merge_mfma_kernel<64>, dim3(grid), dim3(64 * kDiagWaves), 0, stream, m);
-    else
-      hipLaunchKernelGGL(llsa_paper_merge_mfma_kernel<32>, dim3(grid), dim3(64 * kDiagWaves), 0, stream, m);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * kDiagWaves), 0, stream, m); };
+    if (x.d == 64) {
+      if (A <= kMaxMfmaLa) launch(llsa_paper_merge_mfma_kernel<64, false>);
+      else launch(llsa_paper_merge_mfma_kernel<64, true>);
+    } else {
+      if (A <= kMaxMfmaLa) launch(llsa_paper_merge_mfma_kernel<32, false>);
+      else launch(llsa_paper_merge_mfma_kernel<32, true>);
+    }
     return hipGetLastError();
   }
   const long long rows = static_cast<long long>(A + 1) * x.B * (x.T + A) * x.H;
